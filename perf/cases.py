@@ -1,0 +1,640 @@
+"""Performance cases: what a user of the solver has it do, through `Solver` and
+`trajectory`, over the workloads of this repository (shock tube, vortex,
+explosion, uneven batches, adjoints).
+
+A case is a dict of plain values:
+  op      "gts", "lts" (levels dyadic levels, 0: free steps), "batch" (uneven
+          instances in the same launches), "adj_gts" (adjoint of one global step
+          on a fixed mesh), "adj_lag" (the same on the moving mesh), "adj_lts"
+          (gradient through macro steps), "traj" (autograd through global steps)
+  mesh    "tube" (strip with slip walls), "vortex" (4:1 graded square),
+          "disk" (8:1 graded explosion); for "batch" tubes and disks alternate
+  n       triangles aimed at (of the whole batch)
+  M, flux, moving, levels, steps   order, flux, mesh motion, levels, steps of a pass
+
+A pass starts from averages and node positions on the device (`upload_state`,
+as a restart or an optimisation loop does), so that every pass does the same
+work, and returns the new averages and positions (and gradients) whole.
+"""
+import functools
+import math
+
+import numpy as np
+import torch
+
+from paper_1408_3719_amd import Config, Solver
+from paper_1408_3719_amd.trajectory import gts_trajectory, lagrangian_trajectory
+from workloads import concat_instances
+from workloads.mesh import disk_graded_mesh, square_graded_mesh, strip_mesh
+
+GAMMA, FAR = 1.4, 1.0e9
+
+
+def _case(name, op, mesh, n, M, levels, steps, flux="rusanov", moving=True, instances=1):
+    return dict(name=name, op=op, mesh=mesh, n=n, M=M, levels=levels, steps=steps, flux=flux, moving=moving,
+                instances=instances)
+
+
+def listed():
+    return [
+        # the shock tube of the quick start and of a parameter scan: tiny launches, many steps
+        _case("tube_gts_1k_m1", "gts", "tube", 1000, 1, 1, 20),
+        # the convergence study's small vortex, 3 levels: most launches hold few active elements
+        _case("vortex_lts_5k_m2", "lts", "vortex", 5000, 2, 3, 6),
+        # fourth order, the most arithmetic per element
+        _case("vortex_lts_20k_m3", "lts", "vortex", 20000, 3, 3, 3),
+        # the vortex at its production size
+        _case("vortex_lts_80k_m2", "lts", "vortex", 80000, 2, 3, 4),
+        # the flagship: the explosion with 4 levels, the largest single mesh
+        _case("explosion_lts_400k_m2", "lts", "disk", 400000, 2, 4, 3),
+        # global steps with every element active, the Osher-type flux of the reference results
+        _case("explosion_gts_100k_m2_osher", "gts", "disk", 100003, 2, 1, 6, flux="osher"),
+        # free local steps: many cycles over short and ragged active sets
+        _case("explosion_free_12k_m2_hll", "lts", "disk", 12001, 2, 0, 6, flux="hll"),
+        # an uneven batch of independent tubes and disks in the same launches
+        _case("batch_24x_60k_m2", "batch", "mixed", 60000, 2, 3, 3, instances=24),
+        # adjoint of one global step on a fixed mesh: design loops call it once per step
+        _case("adjoint_fixed_50k_m2", "adj_gts", "disk", 50000, 2, 1, 1, moving=False),
+        # the same on the moving mesh, averages and node positions
+        _case("adjoint_moving_50k_m2", "adj_lag", "disk", 50000, 2, 1, 1),
+        # gradient through dyadic macro steps
+        _case("adjoint_lts_50k_m2", "adj_lts", "disk", 50000, 2, 3, 4),
+        # a small optimisation loop: autograd forward and backward through global steps
+        _case("trajectory_3k_m2", "traj", "vortex", 3001, 2, 1, 8, flux="hll"),
+    ]
+
+
+#: Largest number of triangles drawn, by operation and order.
+_MOST = {"gts": (160000, 80000, 14000), "lts": (200000, 120000, 20000), "batch": (80000, 50000, 12000),
+         "adj_gts": (60000, 50000, 8000), "adj_lag": (60000, 50000, 8000), "adj_lts": (50000, 40000, 5000),
+         "traj": (12000, 8000, 1500)}
+
+
+def draw(rng):
+    op = rng.choice(["gts", "gts", "lts", "lts", "lts", "batch", "adj_gts", "adj_lag", "adj_lts", "traj"])
+    M = rng.choice([1, 2, 2, 2, 3])
+    if op == "batch":
+        M = min(M, 2)
+    # the unlimited scheme at order 4 is used on smooth flow
+    mesh = "mixed" if op == "batch" else "vortex" if M == 3 else rng.choice(["tube", "vortex", "disk"])
+    low = {"batch": 8000, "traj": 600}.get(op, 700)
+    n = int(round(math.exp(rng.uniform(math.log(low), math.log(_MOST[op][M - 1])))))
+    levels, steps, moving, instances = 1, rng.randint(2, 8), rng.random() < 0.8, 1
+    flux = rng.choice(["rusanov", "rusanov", "osher", "hll"])
+    if op == "lts":
+        levels = rng.choice([0, 2, 3, 4])
+        steps = rng.randint(1, 3)
+        if levels == 0:   # many short cycles each
+            n, steps = min(n, rng.randint(1000, 12000)), rng.randint(2, 6)
+    elif op == "batch":
+        levels, steps, instances = rng.randint(1, 3), rng.randint(1, 3), rng.randint(3, 24)
+    elif op != "gts":
+        flux = rng.choice(["rusanov", "rusanov", "hll"])
+        moving = {"adj_gts": False, "adj_lag": True}.get(op, moving)
+        steps = {"adj_lts": rng.randint(1, 3), "traj": rng.randint(2, 6)}.get(op, 1)
+        levels = rng.randint(1, 3) if op == "adj_lts" else 1
+    c = _case("", op, mesh, n, M, levels, steps, flux, moving, instances)
+    del c["name"]
+    return c
+
+
+# -- meshes and initial states ------------------------------------------------
+def _one_mesh(kind, n, seed):
+    if kind == "tube":
+        return strip_mesh(-0.5, 0.5, 0.0, 0.1, math.sqrt(0.1 * 2.3 / n), seed, "tube", slip_y=True)
+    if kind == "vortex":
+        return square_graded_mesh(math.sqrt(43.0 / n), seed, name="vortex")
+    return disk_graded_mesh(math.sqrt(1.9 / n), seed, name="disk")
+
+
+def _parts(case):
+    """(mesh kind, triangles aimed at, mesh seed) of each instance."""
+    if case["op"] != "batch":
+        return [(case["mesh"], case["n"], 7)]
+    w = np.exp(np.random.default_rng(case["n"]).uniform(0.0, math.log(8.0), case["instances"]))
+    sizes = np.maximum(600, w / w.sum() * case["n"]).astype(int)
+    return [("disk" if k % 2 else "tube", int(s), 100 + k) for k, s in enumerate(sizes)]
+
+
+@functools.lru_cache(maxsize=16)
+def _meshes(parts):
+    return [_one_mesh(*p) for p in parts]
+
+
+def _averages(kind, mesh, rng, device):
+    """Cell averages [NE][4] of the workload's initial state with its parameters
+    varied by the seed, and 0.1% noise per element (no exact ties of uniform
+    data, as the gradient workloads use). The jump of the tube and the explosion
+    is 2.2 in density and 2.5 in pressure: the scheme has no limiter, and on the
+    coarsest meshes drawn a stronger one gives a non-physical state."""
+    a = rng.uniform(-1.0, 1.0, 4)
+    u, w = np.polynomial.legendre.leggauss(6)
+    u, w = 0.5 * (u + 1.0), 0.5 * w
+    xi = (u[:, None] * (1.0 - u[None, :])).ravel()
+    eta = np.broadcast_to(u[None, :], (6, 6)).ravel()
+    wt = (w[:, None] * (w * (1.0 - u))[None, :]).ravel() * 2.0
+    p = torch.as_tensor(mesh.nodes[mesh.tris], device=device)
+    q = torch.zeros((mesh.tris.shape[0], 4), dtype=torch.float64, device=device)
+    for x1, x2, g in zip(xi, eta, wt):
+        xy = p[:, 0] + (p[:, 1] - p[:, 0]) * float(x1) + (p[:, 2] - p[:, 0]) * float(x2)
+        x, y = xy[:, 0], xy[:, 1]
+        if kind == "vortex":
+            eps = 5.0 * (1.0 + 0.05 * a[0])
+            dx, dy = x - 5.0 - 0.1 * a[1], y - 5.0 - 0.1 * a[2]
+            r2 = dx * dx + dy * dy
+            amp = eps / (2 * math.pi) * torch.exp(0.5 * (1 - r2))
+            T = 1.0 - (GAMMA - 1) * eps * eps / (8 * GAMMA * math.pi ** 2) * torch.exp(1 - r2)
+            rho, vx, vy, pr = T ** (1 / (GAMMA - 1)), 1 - amp * dy, 1 + amp * dx, T ** (GAMMA / (GAMMA - 1))
+        else:
+            inner = x < 0.02 * a[3] if kind == "tube" else torch.hypot(x, y) < 0.5 + 0.02 * a[3]
+            rho = torch.where(inner, 1.0 + 0.1 * float(a[0]), 0.45 * (1.0 + 0.1 * float(a[1])))
+            pr = torch.where(inner, 1.0 + 0.1 * float(a[2]), 0.4 * (1.0 + 0.1 * float(a[1])))
+            rho, pr = rho.to(torch.float64), pr.to(torch.float64)
+            vx = vy = torch.zeros_like(x)
+        q += float(g) * torch.stack([rho, rho * vx, rho * vy, pr / (GAMMA - 1) + 0.5 * rho * (vx * vx + vy * vy)], 1)
+    noise = torch.as_tensor(rng.standard_normal(q.shape[0]), device=device)
+    return q * (1.0 + 1e-3 * noise)[:, None]
+
+
+def _inputs(case, seed, device):
+    parts = _parts(case)
+    meshes = _meshes(tuple(parts))
+    rng = np.random.default_rng(seed)
+    q = [_averages(p[0], m, rng, device) for p, m in zip(parts, meshes)]
+    if len(parts) == 1:
+        m, first = meshes[0], None
+        nodes, tris, bedges = m.nodes, m.tris, m.bedges
+    else:
+        nodes, tris, bedges, _, first = concat_instances([(m, np.zeros((m.n_elems, 4))) for m in meshes])
+    Q = torch.cat(q).T.contiguous()
+    X = torch.as_tensor(nodes, device=device).contiguous()
+    qbar = torch.as_tensor(rng.standard_normal(tuple(Q.shape)), device=device)
+    xbar = torch.as_tensor(rng.standard_normal(tuple(X.shape)), device=device)
+    return nodes, tris, bedges, first, Q, X, qbar, xbar
+
+
+def prepare(case, seed):
+    nodes, tris, bedges, first, Q, X, qbar, xbar = _inputs(case, seed, "cuda:0")
+    cfg = Config(M=case["M"], gamma=GAMMA, levels=case["levels"], flux=case["flux"],
+                 mesh_velocity="lagrangian" if case["moving"] else "eulerian")
+    s = Solver(nodes, tris, bedges, Q, cfg, instance_first=first)
+    dt = float(s.dump("DTCFL").min())
+    return dict(case=case, solver=s, Q=Q, X=X, qbar=qbar, xbar=xbar, dt=0.5 * dt, t_free=dt * case["steps"])
+
+
+def run(state):
+    c, s, Q, X = state["case"], state["solver"], state["Q"], state["X"]
+    if c["op"] == "adj_gts":
+        return s.adjoint_gts_step(state["dt"], state["qbar"], q=Q)
+    if c["op"] == "adj_lag":
+        return s.adjoint_lagrangian_step(state["dt"], state["qbar"], state["xbar"], q=Q, x=X)
+    if c["op"] == "traj":
+        q0 = Q.detach().requires_grad_(True)
+        if not c["moving"]:
+            q1 = gts_trajectory(s, q0, state["dt"], c["steps"], every=4)
+            return q1, torch.autograd.grad(q1, q0, state["qbar"])[0]
+        x0 = X.detach().requires_grad_(True)
+        q1, x1 = lagrangian_trajectory(s, q0, x0, state["dt"], c["steps"], every=4)
+        return (q1, x1) + torch.autograd.grad([q1, x1], [q0, x0], [state["qbar"], state["xbar"]])
+    s.upload_state(Q, 0.0, X=X)
+    if c["op"] == "adj_lts":
+        gq, gx, _ = s.adjoint_lts(c["steps"], FAR, state["qbar"], state["xbar"])
+        return gq, gx, s.download_q(), s.download_x()
+    if c["op"] == "gts":
+        s.step_gts(FAR, c["steps"])
+    elif c["levels"] == 0:
+        s.step_lts(state["t_free"])
+    else:
+        s.step_lts(FAR, c["steps"])
+    return s.download_q(), s.download_x()
+
+
+def work(case):
+    """Arithmetic of the scheme: 5,000 / 25,000 / 120,000 flop per reconstruction
+    and 3,600 / 27,000 / 120,000 per predictor (M = 1, 2, 3), 250 flop per patch
+    point, each element updated as often as its size lets it; an adjoint counts
+    3 forward steps. Bytes: averages, positions and connectivity read once, the
+    results written once."""
+    M = case["M"]
+    ne, updates, NE, NV = (M + 1) * (M + 2), 0.0, 0, 0
+    for m in _meshes(tuple(_parts(case))):
+        p = m.nodes[m.tris]
+        per = sum(np.hypot(*(p[:, (k + 1) % 3] - p[:, k]).T) for k in range(3))
+        r = m.areas() / per
+        r /= r.min()
+        NE, NV = NE + m.n_elems, NV + m.n_nodes
+        if case["op"] in ("gts", "traj") or case["op"].startswith("adj_") and case["op"] != "adj_lts":
+            updates += m.n_elems * case["steps"]
+        elif case["levels"] == 0:
+            updates += float((case["steps"] / r).sum())
+        else:
+            lv = np.minimum(case["levels"] - 1, np.floor(np.log2(r)))
+            updates += case["steps"] * float((2.0 ** (case["levels"] - 1 - lv)).sum())
+    per_update = (5000, 25000, 120000)[M - 1] + (3600, 27000, 120000)[M - 1] + 1.5 * 250 * (M + 1) ** 2
+    grad = case["op"].startswith("adj_") or case["op"] == "traj"
+    state = 8.0 * (4 * NE + 2 * NV)
+    conn = 4.0 * NE * (7 * (ne - 1) + 12)
+    return {"bytes": state * (4 if grad else 2) + conn, "flops": per_update * updates * (4 if grad else 1)}
+
+
+# -- the same in plain torch, 64 bits, for meshes of a few thousand triangles --
+@functools.lru_cache(maxsize=4)
+def _tables(M):
+    """Nodal, time and quadrature tables of the reference element."""
+    ab = [(d - b, b) for d in range(M + 1) for b in range(d + 1)]
+    nodes = np.array([(i / M, j / M) for j in range(M + 1) for i in range(M + 1 - j)])
+
+    def mono(x, y, dx=0, dy=0):
+        out = []
+        for a, b in ab:
+            f = math.perm(a, dx) * math.perm(b, dy) if a >= dx and b >= dy else 0
+            out.append(f * np.asarray(x) ** max(a - dx, 0) * np.asarray(y) ** max(b - dy, 0))
+        return np.stack(out, -1)
+
+    def integral(p, q):
+        return math.factorial(p) * math.factorial(q) / math.factorial(p + q + 2)
+
+    x, y = nodes.T
+    C = np.linalg.inv(mono(x, y))
+    ref = np.array([2.0 * integral(a, b) for a, b in ab])
+    u, w = np.polynomial.legendre.leggauss(M + 1)
+    u, w = 0.5 * (u + 1.0), 0.5 * w
+    v = np.array([(0.0, 0.0), (1.0, 0.0), (0.0, 1.0)])
+    edge = np.stack([mono(*(v[e] + (v[(e + 1) % 3] - v[e]) * u[:, None]).T) @ C for e in range(3)])
+    sig = np.zeros((len(ab), len(ab)))
+    for o in range(1, M + 1):
+        for dy in range(o + 1):
+            dx = o - dy
+            for l, (a, b) in enumerate(ab):
+                for m, (c, d) in enumerate(ab):
+                    if min(a, c) >= dx and min(b, d) >= dy:
+                        sig[l, m] += (math.perm(a, dx) * math.perm(b, dy) * math.perm(c, dx) * math.perm(d, dy)
+                                      * integral(a + c - 2 * dx, b + d - 2 * dy))
+    tn = np.arange(M + 1) / M
+    lag = np.linalg.inv(np.vander(tn, increasing=True)).T          # l_q = sum_k lag[q, k] tau^k
+    k = np.arange(M + 1)
+    mass = lag @ (1.0 / (k[:, None] + k[None, :] + 1)) @ lag.T
+    der = np.where(k > 0, 1.0 / np.maximum(k[:, None] + k[None, :], 1), 0.0) * k
+    K = lag @ der @ lag.T                                          # int l_a l_b'
+    D = np.stack([sum(lag[q, j] * j * tn ** (j - 1) for j in range(1, M + 1)) for q in range(M + 1)], 1)
+    qx, qy = (u[:, None] * (1 - u[None, :])).ravel(), np.broadcast_to(u, (M + 1, M + 1)).ravel()
+    t = dict(Dx=mono(x, y, 1, 0) @ C, De=mono(x, y, 0, 1) @ C, mean=ref @ C, edge=edge, sig=sig[1:, 1:], ref=ref,
+             node=mono(x, y)[:, 1:] - ref[1:], At=np.linalg.solve(K[1:, 1:], mass[1:]),
+             Bt=-np.linalg.solve(K[1:, 1:], K[1:, 0]), Dt=D, lag=lag, nodes=nodes, gx=u, gw=w,
+             qx=qx, qy=qy, qw=(w[:, None] * (w * (1 - u))[None, :]).ravel() * 2.0)
+    t = {key: torch.as_tensor(np.ascontiguousarray(val)) for key, val in t.items()}
+    t["ab"] = ab
+    t["vtx"] = [int(np.argmin(np.abs(nodes - c).sum(1))) for c in v]
+    return t
+
+
+class _Plain:
+    """The scheme on the CPU, every state update out of place so that autograd
+    goes through a run with its schedule held fixed."""
+
+    def __init__(self, case, nodes, tris, bedges):
+        self.c, self.M = case, case["M"]
+        self.t = _tables(self.M)
+        self.tri = torch.as_tensor(tris.astype(np.int64))
+        NE, NV = len(tris), len(nodes)
+        half = {(int(t[k]), int(t[(k + 1) % 3])): (i, k) for i, t in enumerate(tris) for k in range(3)}
+        tag = {(int(a), int(b)): int(g) for a, b, g in bedges}
+        edges = []
+        for (a, b), (i, k) in half.items():
+            o = half.get((b, a))
+            if o is None or (i, k) < o:
+                edges.append((a, b, i, k) + (o or (-1, 0)) + (0 if o else tag[(a, b)],))
+        self.edge = torch.as_tensor(np.array(edges, np.int64))
+        neigh = torch.full((NE, 3), -1)
+        e = self.edge[self.edge[:, 4] >= 0]
+        neigh[e[:, 2], e[:, 3]] = e[:, 4]
+        neigh[e[:, 4], e[:, 5]] = e[:, 2]
+        self.neigh = neigh
+        nrm, pin = np.zeros((NV, 2)), np.zeros(NV, bool)
+        for a, b, g in bedges:
+            if g == 2:
+                d = nodes[b] - nodes[a]
+                n = np.array([d[1], -d[0]]) / np.hypot(*d)
+                for k in (a, b):
+                    pin[k] |= bool(np.any(nrm[k]) and abs(nrm[k, 0] * n[1] - nrm[k, 1] * n[0]) > 1e-9)
+                    nrm[k] = n
+        self.wall, self.pin = torch.as_tensor(nrm), torch.as_tensor(pin)
+        self._stencils(torch.as_tensor(nodes))
+
+    def _stencils(self, X):
+        NE, ne, far = len(self.tri), (self.M + 1) * (self.M + 2), float("inf")
+        N = torch.zeros((NE, len(X)))
+        N[torch.arange(NE)[:, None], self.tri] = 1.0
+        ring = (N @ N.T > 0).float()
+        reach = ring
+        for _ in range(self.M + 3):
+            reach = (reach @ ring > 0).float()
+        reach.fill_diagonal_(0.0)
+        P = X[self.tri]
+        bc = (P[:, 0] + P[:, 1] + P[:, 2]) / 3.0
+        d2 = (bc[None, :, 0] - bc[:, None, 0]) ** 2 + (bc[None, :, 1] - bc[:, None, 1]) ** 2
+        self.sten = torch.full((NE, 7, ne), -1)
+        # face-neighbour layers, then distance
+        face = torch.zeros((NE, NE))
+        ok = self.neigh >= 0
+        face[torch.arange(NE)[:, None].expand(NE, 3)[ok], self.neigh[ok]] = 1.0
+        seen, front = torch.eye(NE, dtype=torch.bool), torch.eye(NE)
+        key = torch.full((NE, NE), far, dtype=torch.float64)
+        key.fill_diagonal_(-1.0)
+        big = float(d2.max()) * 2.0
+        for layer in range(2 * ne):
+            front = ((front @ face > 0) & ~seen).float()
+            key = torch.where(front > 0, d2 + big * layer, key)
+            seen |= front > 0
+            if int(seen.sum(1).min()) >= ne:
+                break
+        self.sten[:, 0] = torch.topk(key, ne, largest=False).indices
+        for k in range(3):
+            o, e1, e2 = P[:, k], P[:, (k + 1) % 3] - P[:, k], P[:, (k + 2) % 3] - P[:, k]
+            dx, dy = bc[None, :, 0] - o[:, None, 0], bc[None, :, 1] - o[:, None, 1]
+            c1 = dx * e2[:, None, 1] - dy * e2[:, None, 0]
+            c2 = e1[:, None, 0] * dy - e1[:, None, 1] * dx
+            for s, inside in ((1 + k, (c1 > 0) & (c2 > 0)), (4 + k, (c1 < 0) & (c2 < 0))):
+                d = torch.where(inside & (reach > 0), d2, far)
+                val, idx = torch.topk(d, ne - 1, largest=False)
+                full = val[:, -1] < far
+                self.sten[full, s, 0] = torch.arange(NE)[full]
+                self.sten[full, s, 1:] = idx[full]
+        U = ring > 0
+        r = torch.arange(NE)[:, None, None].expand_as(self.sten)[self.sten >= 0]
+        U[r, self.sten[self.sten >= 0]] = True
+        self.sched = U | U.T
+
+    # time basis at tau (...): values, and integrals from 0
+    def _l(self, tau):
+        tau = tau.double()
+        return torch.stack([tau ** k for k in range(self.M + 1)], -1) @ self.t["lag"].T
+
+    def _L(self, tau):
+        tau = tau.double()
+        return torch.stack([tau ** (k + 1) / (k + 1) for k in range(self.M + 1)], -1) @ self.t["lag"].T
+
+    @staticmethod
+    def _area(P):
+        a, b = P[..., 1, :] - P[..., 0, :], P[..., 2, :] - P[..., 0, :]
+        return 0.5 * (a[..., 0] * b[..., 1] - b[..., 0] * a[..., 1])
+
+    @staticmethod
+    def _prim(q):
+        u, v = q[..., 1] / q[..., 0], q[..., 2] / q[..., 0]
+        return u, v, (GAMMA - 1.0) * (q[..., 3] - 0.5 * (q[..., 1] * u + q[..., 2] * v))
+
+    def _placed(self, S, j, n):
+        same = S["n"][j] == n
+        step = torch.where(same, 1, S["s"][j])
+        tau = torch.where(same, 0, n - S["n"][j]).double() / step
+        X = S["xe"][j] + (step * S["delta"])[..., None, None] * (self._L(tau)[..., None, :, None] * S["vv"][j]).sum(-2)
+        Q = (self._l(tau)[..., None] * S["avg"][j]).sum(-2)
+        return torch.where(same[..., None, None], S["xe"][j], X), torch.where(same[..., None], S["Q"][j], Q)
+
+    def _reconstruct(self, S, act):
+        """Reconstruction of `act` at its ticks, and its time steps."""
+        t, n = self.t, S["n"][act]
+        xi, qi = S["xe"][act], S["Q"][act]
+        sten = self.sten[act]
+        ok = sten[:, :, 0] >= 0
+        j = torch.where(ok[..., None], sten, act[:, None, None])[:, :, 1:]
+        X, Q = self._placed(S, j, n[:, None, None])
+        e1, e2 = xi[:, 1] - xi[:, 0], xi[:, 2] - xi[:, 0]
+        det = (e1[:, 0] * e2[:, 1] - e2[:, 0] * e1[:, 1])[:, None, None, None]
+        e1, e2 = e1[:, None, None, None], e2[:, None, None, None]
+        d = X - xi[:, 0][:, None, None, None]
+        r = torch.stack([(d[..., 0] * e2[..., 1] - d[..., 1] * e2[..., 0]) / det,
+                         (e1[..., 0] * d[..., 1] - e1[..., 1] * d[..., 0]) / det], -1)
+        A = 0.0
+        for a, b, w in zip(t["qx"].tolist(), t["qy"].tolist(), t["qw"].tolist()):
+            x, y = (r[..., 0, :] + (r[..., 1, :] - r[..., 0, :]) * a + (r[..., 2, :] - r[..., 0, :]) * b).unbind(-1)
+            A = A + w * torch.stack([x ** p * y ** q for p, q in t["ab"][1:]], -1)
+        A = torch.where(ok[..., None, None], A - t["ref"][1:], torch.eye(A.shape[-2], A.shape[-1], dtype=A.dtype))
+        F, R = torch.linalg.qr(A)
+        u = torch.linalg.solve_triangular(R, F.transpose(-1, -2) @ (Q - qi[:, None, None]), upper=True)
+        sigma = (u * (t["sig"] @ u)).sum((-1, -2))
+        lam = torch.where(torch.arange(7) == 0, 1e5, 1.0)
+        om = torch.where(ok, lam / (sigma + 1e-14) ** 8, 0.0)
+        om = om / om.sum(1, keepdim=True)
+        W = qi[:, None] + t["node"] @ (om[..., None, None] * u).sum(1)
+        nb = torch.cat([act[:, None], self.neigh[act]], 1)
+        has = nb >= 0
+        X, Q = self._placed(S, torch.where(has, nb, act[:, None]), n[:, None])
+        per = sum((X[..., (k + 1) % 3, :] - X[..., k, :]).norm(dim=-1) for k in range(3))
+        vx, vy, p = self._prim(Q)
+        ratio = 4.0 * self._area(X) / per / (torch.sqrt(vx * vx + vy * vy) + torch.sqrt(GAMMA * p / Q[..., 0]))
+        dt = 0.5 * torch.where(has, ratio, float("inf")).amin(1)
+        return W, dt.detach()
+
+    def _predict(self, W, xe, dt):
+        t, M = self.t, self.M
+        n = t["nodes"]
+        q0, x0 = W, xe[:, None, 0] + (xe[:, None, 1] - xe[:, None, 0]) * n[:, 0, None] + (xe[:, None, 2] - xe[:, None, 0]) * n[:, 1, None]
+        q, x = q0[:, None].expand(-1, M + 1, -1, -1), x0[:, None].expand(-1, M + 1, -1, -1)
+        h = dt[:, None, None, None]
+        At, Bt = t["At"], t["Bt"][:, None, None]
+
+        def vel(q):
+            return q[..., 1:3] / q[..., :1] * (1.0 if self.c["moving"] else 0.0)
+
+        for _ in range(M + 1):
+            x = torch.cat([x0[:, None], Bt * x0[:, None] + h * torch.einsum("rt,etmc->ermc", At, vel(q))], 1)
+            dx, de = t["Dx"] @ x, t["De"] @ x
+            xt = torch.einsum("rt,etmc->ermc", t["Dt"], x) / h
+            det = dx[..., 0] * de[..., 1] - de[..., 0] * dx[..., 1]
+            m = [de[..., 1] / det, -de[..., 0] / det, -dx[..., 1] / det, dx[..., 0] / det]
+            tx, te = -(m[0] * xt[..., 0] + m[1] * xt[..., 1]), -(m[2] * xt[..., 0] + m[3] * xt[..., 1])
+            u, v, p = self._prim(q)
+            f = torch.stack([q[..., 1], q[..., 1] * u + p, q[..., 2] * u, u * (q[..., 3] + p)], -1)
+            g = torch.stack([q[..., 2], q[..., 1] * v, q[..., 2] * v + p, v * (q[..., 3] + p)], -1)
+            P = 0.0
+            for D, a, b, c in ((t["Dx"], tx, m[0], m[1]), (t["De"], te, m[2], m[3])):
+                P = P - ((D @ q) * a[..., None] + (D @ f) * b[..., None] + (D @ g) * c[..., None])
+            q = torch.cat([q0[:, None], Bt * q0[:, None] + h * torch.einsum("rt,etmv->ermv", At, P)], 1)
+        avg = torch.einsum("m,etmv->etv", t["mean"], q)
+        trace = torch.einsum("kgm,etmv->ekgtv", t["edge"], q)
+        return avg, trace, vel(q[:, :, t["vtx"]]).transpose(1, 2)
+
+    def _flux(self, ql, qr, N):
+        nxy = torch.sqrt(N[..., 0] ** 2 + N[..., 1] ** 2)
+
+        def side(q):
+            u, v, p = self._prim(q)
+            un = u * N[..., 0] + v * N[..., 1]
+            z = torch.zeros_like(un)
+            f = q * (un + N[..., 2])[..., None] + torch.stack([z, p * N[..., 0], p * N[..., 1], p * un], -1)
+            return f, un + N[..., 2], torch.sqrt(GAMMA * p / q[..., 0]) * nxy
+
+        fl, ul, cl = side(ql)
+        fr, ur, cr = side(qr)
+        if self.c["flux"] == "hll":
+            sl, sr = torch.minimum(ul - cl, ur - cr)[..., None], torch.maximum(ul + cl, ur + cr)[..., None]
+            mid = (sr * fl - sl * fr + sl * sr * (qr - ql)) / torch.where(sr > sl, sr - sl, 1.0)
+            return torch.where(sl >= 0, fl, torch.where(sr <= 0, fr, mid))
+        if self.c["flux"] == "rusanov":
+            return 0.5 * (fl + fr) - 0.5 * torch.maximum(ul.abs() + cl, ur.abs() + cr)[..., None] * (qr - ql)
+        D, dq = 0.0, qr - ql
+        for s, w in zip((0.5 - math.sqrt(0.15), 0.5, 0.5 + math.sqrt(0.15)), (5 / 18, 8 / 18, 5 / 18)):
+            q = ql + s * dq
+            u, v, p = self._prim(q)
+            nx, ny = N[..., 0] / nxy, N[..., 1] / nxy
+            un, c2, H = u * nx + v * ny, GAMMA * p / q[..., 0], (q[..., 3] + p) / q[..., 0]
+            c, k = torch.sqrt(c2), 0.5 * (u * u + v * v)
+            a = (GAMMA - 1.0) * (k * dq[..., 0] - u * dq[..., 1] - v * dq[..., 2] + dq[..., 3]) / c2
+            b = (nx * dq[..., 1] + ny * dq[..., 2] - un * dq[..., 0]) / c
+            l1, l2, l4 = ((un - c) * nxy + N[..., 2]).abs(), (un * nxy + N[..., 2]).abs(), ((un + c) * nxy + N[..., 2]).abs()
+            o = torch.ones_like(u)
+            one = torch.stack([o, u, v, k], -1) * (l2 * (dq[..., 0] - a))[..., None]
+            ut = (nx * dq[..., 2] - ny * dq[..., 1]) - (v * nx - u * ny) * dq[..., 0]
+            shear = torch.stack([0 * o, -ny, nx, v * nx - u * ny], -1) * (l2 * ut)[..., None]
+            lo = torch.stack([o, u - c * nx, v - c * ny, H - un * c], -1) * (0.5 * l1 * (a - b))[..., None]
+            hi = torch.stack([o, u + c * nx, v + c * ny, H + un * c], -1) * (0.5 * l4 * (a + b))[..., None]
+            D = D + w * (one + shear + lo + hi)
+        return 0.5 * (fl + fr) - 0.5 * D
+
+    def _patches(self, S, e, Xn, tn):
+        """Fluxes over the patches swept by the edges e (corners at their ticks)."""
+        t, M = self.t, self.M
+        a, b, L, el, R, er, bc = self.edge[e].unbind(1)
+        has, Rs = R >= 0, torch.where(R >= 0, R, L)
+        tk = [k.double() for k in (S["nt"][a], S["nt"][b], tn[b], tn[a])]
+        P = [torch.cat([x, (k * S["delta"])[:, None]], 1) for x, k in zip((S["X"][a], S["X"][b], Xn[b], Xn[a]), tk)]
+        trL, trR, G = S["trace"][L, el], S["trace"][Rs, er], 0.0
+        for i in range(M + 1):
+            for h in range(M + 1):
+                c, s = float(t["gx"][i]), float(t["gx"][h])
+                dc = (1 - s) * (P[1] - P[0]) + s * (P[2] - P[3])
+                ds = (1 - c) * (P[3] - P[0]) + c * (P[2] - P[1])
+                N = torch.linalg.cross(dc, ds)
+                k = (1 - c) * (1 - s) * tk[0] + c * (1 - s) * tk[1] + c * s * tk[2] + (1 - c) * s * tk[3]
+                lL, lR = self._l((k - S["n"][L]) / S["s"][L]), self._l((k - S["n"][Rs]) / S["s"][Rs])
+                ql = (lL[..., None] * trL[:, i]).sum(1)
+                qr = (lR[..., None] * trR[:, M - i]).sum(1)
+                nn = N[:, :2] / N[:, :2].norm(dim=1, keepdim=True)
+                mn = (ql[:, 1:3] * nn).sum(1, keepdim=True)
+                wall = torch.cat([ql[:, :1], ql[:, 1:3] - 2.0 * mn * nn, ql[:, 3:]], 1)
+                qr = torch.where((bc == 2)[:, None], wall, qr)
+                qr = torch.where((bc == 1)[:, None], (lL[..., None] * S["avg"][L]).sum(1), qr)
+                G = G + float(t["gw"][i] * t["gw"][h]) * self._flux(ql, qr, N)
+        return L, R, has, G
+
+    def _choose(self, S, act):
+        """Steps in ticks at the present ticks of `act`, 2^30 to a macro step."""
+        n, N = S["n"][act].numpy(), 1 << 30
+        if not bool(torch.isfinite(S["dt"][act]).all()):
+            raise FloatingPointError("non-physical state")
+        q = S["dt"][act].numpy() / float(S["delta"])
+        if self.c["levels"] == 0 and self.c["op"] != "gts":
+            p = np.maximum(np.minimum(np.floor(np.minimum(q, 2.0 * N)), N - n), 1).astype(np.int64)
+        else:
+            p = 2 ** np.clip(np.floor(np.log2(q * (1 + 1e-15))), 0, 30).astype(np.int64)
+            p = np.where(n > 0, np.minimum(p, np.where(n > 0, n & -n, N)), p)
+        return torch.as_tensor(np.where(n >= N, 0, p))
+
+    def _set(self, S, key, idx, val):
+        S[key] = S[key].index_copy(0, idx, val)
+
+    def run(self, Q, X, macro, levels, t_end=None, dt=None):
+        """`macro` macro steps from averages Q [NE][4] and positions X; dt: global
+        steps of that length. Returns (Q, X)."""
+        NE, M, N = len(Q), self.M, 1 << 30
+        xe = X[self.tri]
+        z = torch.zeros(NE, dtype=torch.int64)
+        S = dict(Q=Q, X=X, xe=xe, A=self._area(xe), n=z, s=z, nt=torch.zeros(len(X), dtype=torch.int64), delta=torch.tensor(0.0, dtype=torch.float64),
+                 avg=Q[:, None].expand(-1, M + 1, -1), trace=Q.new_zeros((NE, 3, M + 1, M + 1, 4)),
+                 vv=Q.new_zeros((NE, 3, M + 1, 2)), mem=torch.zeros_like(Q))
+        every = torch.arange(NE)
+        S["W"], S["dt"] = self._reconstruct(S, every)
+        if t_end is not None:
+            t_end = t_end * float(S["dt"].min())
+        for _ in range(macro):
+            least = float(S["dt"].min())
+            if t_end is not None:
+                S["delta"] = torch.tensor(t_end / N, dtype=torch.float64)
+            elif dt is not None:
+                S["delta"] = torch.tensor(dt / N, dtype=torch.float64)
+            else:
+                S["delta"] = torch.tensor(least * (0.95 if levels > 1 else 1.0) * (2 ** (levels - 1) / N), dtype=torch.float64)
+            S["n"], S["nt"] = z, torch.zeros_like(S["nt"])
+            S["s"] = self._choose(S, every) if dt is None else torch.full((NE,), N)
+            S["avg"], S["trace"], S["vv"] = self._predict(S["W"], S["xe"], S["s"] * S["delta"])
+            while bool((S["n"] < N).any()):
+                self._cycle(S, dt)
+        return S["Q"], S["X"]
+
+    def _cycle(self, S, dt):
+        N, tri = 1 << 30, self.tri
+        n, s = S["n"], S["s"]
+        fut = n + s
+        hi = torch.where(self.sched, n[None, :], -1).amax(1)
+        lo = torch.where(self.sched, fut[None, :], 2 * N).amin(1)
+        act = torch.nonzero((n < N) & (hi <= fut) & (fut <= lo))[:, 0]
+        tn = S["nt"].clone()
+        tn.scatter_reduce_(0, tri[act].reshape(-1), fut[act][:, None].expand(-1, 3).reshape(-1), "amax")
+        moved = tn > S["nt"]
+        # node solver: mass-weighted mean of the ring's time-averaged velocities
+        j, k = torch.nonzero(moved[tri], as_tuple=True)
+        v = tri[j, k]
+        t0, t1 = (S["nt"][v] - n[j]).double() / s[j], (tn[v] - n[j]).double() / s[j]
+        V = ((self._L(t1) - self._L(t0))[..., None] * S["vv"][j, k]).sum(1) / (t1 - t0)[:, None]
+        mu = S["Q"][j, 0] * S["A"][j]
+        num = torch.zeros_like(S["X"]).index_add(0, v, mu[:, None] * V)
+        den = torch.zeros_like(S["X"][:, 0]).index_add(0, v, mu)
+        V = num / torch.where(moved, den, 1.0)[:, None]
+        V = V - (V * self.wall).sum(1, keepdim=True) * self.wall
+        V = torch.where(self.pin[:, None], 0.0, V)
+        Xn = S["X"] + ((tn - S["nt"]) * S["delta"])[:, None] * V
+        e = torch.nonzero(moved[self.edge[:, 0]] | moved[self.edge[:, 1]])[:, 0]
+        L, R, has, G = self._patches(S, e, Xn, tn)
+        mem = S["mem"].index_add(0, L, -G).index_add(0, R[has], G[has])
+        S["X"], S["nt"] = Xn, tn
+        xe = Xn[tri[act]]
+        An = self._area(xe)
+        Q = (S["A"][act, None] * S["Q"][act] + mem[act]) / An[:, None]
+        S["mem"] = mem.index_copy(0, act, torch.zeros_like(Q))
+        for key, val in (("Q", Q), ("xe", xe), ("A", An), ("n", fut[act])):
+            self._set(S, key, act, val)
+        W, d = self._reconstruct(S, act)
+        self._set(S, "W", act, W)
+        self._set(S, "dt", act, d)
+        self._set(S, "s", act, self._choose(S, act))
+        go = act[S["n"][act] < N]
+        if len(go):
+            out = self._predict(S["W"][go], S["xe"][go], S["s"][go] * S["delta"])
+            for key, val in zip(("avg", "trace", "vv"), out):
+                self._set(S, key, go, val)
+
+
+def exact(case, seed):
+    op, cost = case["op"], case["n"] * (case["M"] ** 2)
+    if op == "batch" or case["n"] > 5200 or cost * case["steps"] * (1 if op in ("gts", "lts") else 3) > 3e5:
+        return None
+    nodes, tris, bedges, _, Q, X, qbar, xbar = _inputs(case, seed, "cpu")
+    p = _Plain(case, nodes, tris, bedges)
+    grad = op.startswith("adj_") or op == "traj"
+    Q0, X0 = Q.T.contiguous().requires_grad_(grad), X.clone().requires_grad_(grad)
+    macro, levels = case["steps"], 1 if op == "gts" else case["levels"]
+    if op in ("adj_gts", "adj_lag", "traj"):
+        S = dict(Q=Q0.detach(), xe=X0.detach()[p.tri], n=torch.zeros(len(Q0), dtype=torch.int64))
+        S |= dict(s=S["n"], delta=torch.tensor(0.0, dtype=torch.float64), avg=S["Q"][:, None].expand(-1, case["M"] + 1, -1),
+                  vv=S["Q"].new_zeros((len(Q0), 3, case["M"] + 1, 2)))
+        dt = 0.5 * float(p._reconstruct(S, torch.arange(len(Q0)))[1].min())
+        q1, x1 = p.run(Q0, X0, macro, 1, dt=dt)
+    elif levels == 0:
+        q1, x1 = p.run(Q0, X0, 1, 0, t_end=float(macro))
+    else:
+        q1, x1 = p.run(Q0, X0, macro, levels)
+    if not grad:
+        return q1.T.contiguous(), x1
+    # the fixed-mesh adjoints take the averages' adjoint alone
+    gq, gx = torch.autograd.grad((q1.T * qbar).sum() + ((x1 * xbar).sum() if op in ("adj_lag", "adj_lts") or case["moving"] else 0.0),
+                                 (Q0, X0), allow_unused=True)
+    gq, q1, x1 = gq.T.contiguous(), q1.detach().T.contiguous(), x1.detach()
+    if op == "adj_gts":
+        return gq
+    if op == "adj_lag":
+        return gq, gx, q1, x1
+    if op == "adj_lts":
+        return gq, gx, q1, x1
+    return (q1, x1, gq, gx) if case["moving"] else (q1, gq)
