@@ -104,7 +104,7 @@ def _one_mesh(kind, n, seed):
         return strip_mesh(-0.5, 0.5, 0.0, 0.1, math.sqrt(0.1 * 2.3 / n), seed, "tube", slip_y=True)
     if kind == "vortex":
         return square_graded_mesh(math.sqrt(43.0 / n), seed, name="vortex")
-    return disk_graded_mesh(math.sqrt(1.9 / n), seed, name="disk")
+    return disk_graded_mesh(math.sqrt(1.2 / n), seed, name="disk")
 
 
 def _parts(case):
