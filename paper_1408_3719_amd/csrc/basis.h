@@ -145,50 +145,180 @@ struct MonoBasis {
 };
 
 // Means of the monomials x^a y^b (a + b <= M) over a triangle with vertices
-// (x[k], y[k]), by a rule exact to degree M with its points written out: the
-// centroid (M=1), the edge midpoints (M=2), and the vertices, edge midpoints
-// and centroid with weights 3/60, 8/60, 27/60 (M=3).
+// (x[k], y[k]), in closed form: with the vertex sums S_x = sum x_k, S_y and the
+// power sums P_pq = sum x_k^p y_k^q,
+//   mean(x) = S_x / 3, mean(xy) = (S_x S_y + P_11) / 12,
+//   mean(x^3) = (S_x^3 + 3 S_x P_20 + 2 P_30) / 60 and its polarised forms.
+// About half the operations of a quadrature over the edge midpoints (M=2: 21
+// instead of 40), no cancellation beyond that of the rule's own sums.
 template <int M>
 __device__ inline void monomial_means(const double x[3], const double y[3], double mm[]) {
-  constexpr int nb = (M + 1) * (M + 2) / 2;
-#pragma unroll
-  for (int k = 0; k < nb; ++k) mm[k] = 0.0;
-  auto point = [&](double w, double px, double py) {
-    double xp[M + 1], yp[M + 1];
-    xp[0] = 1.0;
-    yp[0] = 1.0;
-#pragma unroll
-    for (int a = 1; a <= M; ++a) {
-      xp[a] = xp[a - 1] * px;
-      yp[a] = yp[a - 1] * py;
-    }
-    int k = 0;
-#pragma unroll
-    for (int dg = 0; dg <= M; ++dg)
-#pragma unroll
-      for (int b = 0; b <= dg; ++b) {
-        mm[k] += w * xp[dg - b] * yp[b];
-        ++k;
-      }
-  };
   constexpr double third = 1.0 / 3.0;
-  if constexpr (M == 1) {
-    point(1.0, (x[0] + x[1] + x[2]) * third, (y[0] + y[1] + y[2]) * third);
-  } else if constexpr (M == 2) {
+  mm[0] = 1.0;
+  const double sx = x[0] + x[1] + x[2], sy = y[0] + y[1] + y[2];
+  mm[1] = sx * third;
+  mm[2] = sy * third;
+  if constexpr (M >= 2) {
+    const double p20 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
+    const double p11 = x[0] * y[0] + x[1] * y[1] + x[2] * y[2];
+    const double p02 = y[0] * y[0] + y[1] * y[1] + y[2] * y[2];
+    constexpr double twelfth = 1.0 / 12.0;
+    mm[3] = (sx * sx + p20) * twelfth;
+    mm[4] = (sx * sy + p11) * twelfth;
+    mm[5] = (sy * sy + p02) * twelfth;
+    if constexpr (M >= 3) {
+      double p30 = 0.0, p21 = 0.0, p12 = 0.0, p03 = 0.0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int k1 = k == 2 ? 0 : k + 1;
-      point(third, 0.5 * (x[k] + x[k1]), 0.5 * (y[k] + y[k1]));
+      for (int k = 0; k < 3; ++k) {
+        const double xx = x[k] * x[k], yy = y[k] * y[k];
+        p30 += xx * x[k];
+        p21 += xx * y[k];
+        p12 += x[k] * yy;
+        p03 += yy * y[k];
+      }
+      constexpr double sixtieth = 1.0 / 60.0;
+      const double sxx = sx * sx, syy = sy * sy;
+      mm[6] = (sx * (sxx + 3.0 * p20) + 2.0 * p30) * sixtieth;
+      mm[7] = (sy * (sxx + p20) + 2.0 * (sx * p11 + p21)) * sixtieth;
+      mm[8] = (sx * (syy + p02) + 2.0 * (sy * p11 + p12)) * sixtieth;
+      mm[9] = (sy * (syy + 3.0 * p02) + 2.0 * p03) * sixtieth;
     }
-  } else {
+  }
+}
+
+// 1/x to rounding for normal x away from the ends of the range: the hardware
+// estimate and two Newton steps, without the scaling a general division adds.
+__device__ inline double rcp_newton(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = r + r * (1.0 - x * r);
+  r = r + r * (1.0 - x * r);
+  return r;
+}
+
+// Least squares of a stencil by Householder reflections over blocks of rows
+// held in registers. Row c is (a[c], b[c]): NU unknowns, four right-hand sides.
+// A reflection clears a whole column of a block with one inverse square root
+// and one reciprocal; Givens rotations, row by row, need one inverse square
+// root per entry (55 at M=2 instead of 10) and twice the multiply-adds.
+//
+// block_qr: triangular factor of the first P >= NU rows, left in a[0..NU) (upper
+// triangle) and b[0..NU).
+template <int NU, int P>
+__device__ inline void block_qr(double (&a)[P][NU], double (&b)[P][4]) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) point(3.0 / 60.0, x[k], y[k]);
+  for (int k = 0; k < NU; ++k) {
+    double s2 = 0.0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int k1 = k == 2 ? 0 : k + 1;
-      point(8.0 / 60.0, 0.5 * (x[k] + x[k1]), 0.5 * (y[k] + y[k1]));
+    for (int p = k + 1; p < P; ++p) s2 += a[p][k] * a[p][k];
+    const double al = a[k][k];
+    const double mu2 = al * al + s2;
+    if (mu2 == 0.0) continue;
+    const double rmu = rsqrt(mu2);
+    const double mu = mu2 * rmu;
+    // reflection vector (v0, a[k+1..P)), v0 = al + sign(al) mu; 2 / v.v = rmu / (mu + |al|)
+    const double v0 = al + copysign(mu, al);
+    const double g = rmu * rcp_newton(mu + fabs(al)), gv = g * v0;
+    auto reflect = [&](auto&& top, auto&& col) {
+      double w = v0 * top();
+#pragma unroll
+      for (int p = k + 1; p < P; ++p) w += a[p][k] * col(p);
+      const double gw = g * w;
+      top() -= gv * w;
+#pragma unroll
+      for (int p = k + 1; p < P; ++p) col(p) -= gw * a[p][k];
+    };
+#pragma unroll
+    for (int c = k + 1; c < NU; ++c)
+      reflect([&]() -> double& { return a[k][c]; }, [&](int p) -> double& { return a[p][c]; });
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      reflect([&]() -> double& { return b[k][v]; }, [&](int p) -> double& { return b[p][v]; });
+    a[k][k] = -copysign(mu, al);
+  }
+}
+
+// block_fold: folds P further rows into the triangle (R, z).
+template <int NU, int P>
+__device__ inline void block_fold(double (&R)[NU][NU], double (&z)[NU][4], double (&a)[P][NU],
+                                  double (&b)[P][4]) {
+#pragma unroll
+  for (int k = 0; k < NU; ++k) {
+    double s2 = 0.0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) s2 += a[p][k] * a[p][k];
+    const double al = R[k][k];
+    const double mu2 = al * al + s2;
+    if (mu2 == 0.0) continue;
+    const double rmu = rsqrt(mu2);
+    const double mu = mu2 * rmu;
+    const double v0 = al + copysign(mu, al);
+    const double g = rmu * rcp_newton(mu + fabs(al)), gv = g * v0;
+#pragma unroll
+    for (int c = k + 1; c < NU; ++c) {
+      double w = v0 * R[k][c];
+#pragma unroll
+      for (int p = 0; p < P; ++p) w += a[p][k] * a[p][c];
+      const double gw = g * w;
+      R[k][c] -= gv * w;
+#pragma unroll
+      for (int p = 0; p < P; ++p) a[p][c] -= gw * a[p][k];
     }
-    point(27.0 / 60.0, (x[0] + x[1] + x[2]) * third, (y[0] + y[1] + y[2]) * third);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double w = v0 * z[k][v];
+#pragma unroll
+      for (int p = 0; p < P; ++p) w += a[p][k] * b[p][v];
+      const double gw = g * w;
+      z[k][v] -= gv * w;
+#pragma unroll
+      for (int p = 0; p < P; ++p) b[p][v] -= gw * a[p][k];
+    }
+    R[k][k] = -copysign(mu, al);
+  }
+}
+
+// Rows per block: the first block by block_qr, the others by block_fold.
+template <int M>
+struct LsBlocks {
+  static constexpr int rows = (M + 1) * (M + 2) - 1;
+  static constexpr int first = M == 1 ? 5 : M == 2 ? 6 : 10;
+  static constexpr int next = M == 1 ? 0 : M == 2 ? 3 : 5;
+};
+
+// The triangle (R, z) of all rows; row(c, a, b) delivers rows c = 1, 2, ... in order.
+template <int M, class Row>
+__device__ inline void ls_triangle(double (&R)[MonoBasis<M>::nu][MonoBasis<M>::nu],
+                                   double (&z)[MonoBasis<M>::nu][4], Row&& row) {
+  constexpr int nu = MonoBasis<M>::nu;
+  using B = LsBlocks<M>;
+  {
+    double a[B::first][nu], b[B::first][4];
+#pragma unroll
+    for (int p = 0; p < B::first; ++p) row(1 + p, a[p], b[p]);
+    block_qr<nu, B::first>(a, b);
+#pragma unroll
+    for (int k = 0; k < nu; ++k) {
+#pragma unroll
+      for (int c = k; c < nu; ++c) R[k][c] = a[k][c];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) z[k][v] = b[k][v];
+    }
+  }
+  if constexpr (B::next > 0) {
+    constexpr int full = (B::rows - B::first) / B::next, rest = (B::rows - B::first) % B::next;
+#pragma unroll
+    for (int f = 0; f < full; ++f) {
+      double a[B::next][nu], b[B::next][4];
+#pragma unroll
+      for (int p = 0; p < B::next; ++p) row(1 + B::first + f * B::next + p, a[p], b[p]);
+      block_fold<nu, B::next>(R, z, a, b);
+    }
+    if constexpr (rest > 0) {
+      double a[rest][nu], b[rest][4];
+#pragma unroll
+      for (int p = 0; p < rest; ++p) row(1 + B::first + full * B::next + p, a[p], b[p]);
+      block_fold<nu, rest>(R, z, a, b);
+    }
   }
 }
 

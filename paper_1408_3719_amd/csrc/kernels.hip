@@ -23,9 +23,9 @@
 // (independent meshes) keep their own time and tick length (Inst).
 //
 // Lane mappings (64-wide wavefronts):
-//   k_reconstruct: 8 lanes per element, lane s solves stencil s (s < 7), lane 7
-//                  computes the CFL step; the WENO sum is a 3-step butterfly;
-//                  the rows of a stencil are software-pipelined.
+//   k_reconstruct: 8 lanes per element, lane s solves stencil s (s < 7); the
+//                  stencil elements of a workgroup are placed once, in LDS; the
+//                  CFL step and the WENO sum go over the 8 lanes.
 //   k_predict:     nb lanes per element, floor(64/nb) elements per wavefront,
 //                  lane m owns spatial node m for all time nodes; spatial
 //                  derivatives read the other nodes of the same time slice
@@ -36,6 +36,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cfloat>
 
 #include "aderweno.h"
@@ -423,22 +424,11 @@ __device__ inline double dpp_move(double v) {
 
 // Sum over the 8 lanes of an aligned group, the same in every lane: pairs,
 // then quads, then the two quads of the group; every step adds two equal
-// partial sums, so all lanes end bit-identical and both forms give the same
-// bits. The DPP form (lane moves inside the VALU, no LDS round trip) needs a
-// few more registers, which at M=2 would take the reconstruction past 256
-// VGPRs (one wave per SIMD instead of two): it is used where that does not
-// matter.
-template <bool DPP>
+// partial sums, so all lanes end bit-identical.
 __device__ inline double group8_sum(double v) {
-  if constexpr (DPP) {
-    v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
-    v += dpp_move<0x141>(v);   // row_half_mirror: lane i <-> 7 - i within 8
-  } else {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-  }
+  v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
+  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_move<0x141>(v);   // row_half_mirror: lane i <-> 7 - i within 8
   return v;
 }
 
@@ -446,182 +436,318 @@ __device__ inline double group8_sum(double v) {
 // ---------------------------------------------------------------------------
 // Reconstruction + local time step: 8 lanes per element
 // ---------------------------------------------------------------------------
+// Stencil elements are staged per workgroup: the stencils of neighbouring
+// elements overlap (32 consecutive elements name ~2,500 rows at M=2 but only
+// ~250 different elements), and a gather of one row per lane costs the CU's L1
+// one lookup per lane and 16 bytes, which is what bounds this kernel when every
+// lane fetches its own rows. The workgroup collects the distinct (element,
+// tick) pairs its rows name in a hash table in LDS, places each of them once
+// (real data, or projected to the tick), and the rows read vertices and average
+// from LDS. With the block least squares of basis.h, per launch against rows
+// fetched by their lanes and Givens rotations: explosion of 302k triangles, M=2,
+// 4 levels 264 -> 166 us; vortex of 75k, M=2, 3 levels 93 -> 69 us; vortex of
+// 19k, M=3 107 -> 98 us; 150k triangles, M=1, global steps 120 -> 69 us; 1,064
+// triangles, M=1 13.3 -> 7.5 us. Now bound by FP64 issue in the least squares
+// (10k of 34k cycles of a workgroup) and the latency of the phases before it
+// (index loads, hash table, placing: 17k) at two workgroups per CU.
 template <int M>
-__global__ void __launch_bounds__(TPB) k_reconstruct(Dev d, const Tables* __restrict__ tb, Params P,
+struct Stage {
+  static constexpr int CAP = M == 1 ? 448 : 640;   // placed elements a round holds (80 bytes each)
+  static constexpr int TAB = M == 1 ? 1024 : 2048;   // hash entries, a power of two
+  static constexpr int REFS = NSTEN * (Sz<M>::ne - 1) + 3;   // rows and face neighbours of an element
+  // elements of a round that fits whatever they name
+  static constexpr int SUB = CAP / REFS >= 8 ? 8 : CAP / REFS >= 4 ? 4 : 2;
+  static_assert(SUB * REFS <= CAP && CAP < TAB, "a round of SUB elements must fit");
+};
+
+constexpr unsigned long long NO_KEY = ~0ull;
+
+template <int M>
+__global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruct(Dev d, const Tables* __restrict__ tb, Params P,
                                                      int use_list, int set_level) {
   using S = Sz<M>;
-  constexpr int nb = S::nb, ne = S::ne, nu = S::nu, WS = S::WS;
+  using G = Stage<M>;
+  constexpr int nb = S::nb, ne = S::ne, nu = S::nu, WS = S::WS, NR = ne - 1;
+  __shared__ unsigned long long key[G::TAB];      // tick << 32 | element
+  __shared__ unsigned short slot_of[G::TAB], entry[G::CAP];
+  __shared__ double2 placed[G::CAP * 5];          // x0 y0 x1 y1 x2 y2 Q0..Q3
+  __shared__ int count;
   const int NE = d.NE;
   const int nitems = use_list ? d.scal->n_active : NE;
-  const int sl = threadIdx.x & 7;
-  const int ngroups = (gridDim.x * blockDim.x) >> 3;
-  const int nwork = int((8L * nitems + blockDim.x - 1) / blockDim.x);
-  for (int idx = (xcd_block(nwork) * blockDim.x + threadIdx.x) >> 3; idx < nitems; idx += ngroups) {
-    const int i = use_list ? d.act_list[idx] : idx;
-    const double delta = elem_delta(d, i);   // stencil elements share the instance
-    const int nt = d.ts[i].tick;
-    const double* ri = rec<M>(d, i);
-    double Xi[6], Qi[4];
+  const int tid = threadIdx.x, sl = tid & 7, grp = tid >> 3;
+  // elements per workgroup: all 32 lane groups when the launch fills the chip
+  // twice over, else fewer, so that a short list still spreads over every CU
+  const int spread = 2 * (d.n_cu > 0 ? d.n_cu : 256);
+  int per = ((nitems + spread - 1) / spread + 3) & ~3;
+  per = per < 4 ? 4 : (per > TPB / 8 ? TPB / 8 : per);
+  const int nwork = (nitems + per - 1) / per;
+  for (int wg = xcd_block(nwork); wg < nwork; wg += gridDim.x) {
+    const int first = wg * per, last = min(nitems, first + per);
+    int round = per;
+    for (int base = first; base < last;) {
+      for (int t = tid; t < G::TAB; t += TPB) key[t] = NO_KEY;
+      if (tid == 0) count = 0;
+      __syncthreads();
+      const int idx = base + grp;
+      const bool mine = grp < round && idx < last;
+      int i = 0, nt = 0;
+      bool valid = false;
+      int at[NR];      // table entry of each row (lane 7: of the face neighbours)
+      {
+        int j[NR];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) Xi[c] = ri[XE + c];
+        for (int c = 0; c < NR; ++c) j[c] = -1;
+        if (mine) {
+          i = use_list ? d.act_list[idx] : idx;
+          nt = d.ts[i].tick;
+          if (sl < NSTEN) {
+            const int* sidx = d.sten + size_t(sl * ne) * NE + i;   // row c at sidx[c * NE]
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Qi[v] = ri[QO + v];
-    const double e1x = Xi[2] - Xi[0], e1y = Xi[3] - Xi[1];
-    const double e2x = Xi[4] - Xi[0], e2y = Xi[5] - Xi[1];
-    const double idet = 1.0 / (e1x * e2y - e2x * e1y);
-    double W[nu][4];
+            for (int c = 0; c < NR; ++c) j[c] = sidx[(c + 1) * NE];   // -1 in a dropped sector
+          } else {
 #pragma unroll
-    for (int l = 0; l < nu; ++l)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) W[l][v] = 0.0;
-    double om = 0.0;
-    bool ok = true;
-    if (sl < NSTEN && d.sten[(sl * ne) * NE + i] >= 0) {
-      double R[nu][nu], z[nu][4];
-#pragma unroll
-      for (int a = 0; a < nu; ++a) {
-#pragma unroll
-        for (int b = 0; b < nu; ++b) R[a][b] = 0.0;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) z[a][v] = 0.0;
-      }
-      // Rows are software-pipelined: while row c is folded in, the neighbour
-      // data of row c+1, the tick of row c+2 and the index of row c+3 are in
-      // flight, each load depending only on values that arrived one row earlier.
-      const int* sidx = d.sten + size_t(sl * ne) * NE + i;   // row c at sidx[c * NE]
-      int jn = sidx[2 * NE], jnn = sidx[3 * NE];              // ne >= 6
-      TickStep tc = d.ts[sidx[NE]], tn = d.ts[jn];
-      NbrRaw<M> rc;
-      fetch_nbr<M>(d, sidx[NE], tc, nt, rc);
-#pragma unroll 1
-      for (int c = 1; c < ne; ++c) {
-        double Xv[6], Qv[4];
-        ok &= place_nbr<M>(tb, rc, tc, nt, delta, Xv, Qv);
-        if (c + 1 < ne) fetch_nbr<M>(d, jn, tn, nt, rc);
-        tc = tn;
-        if (c + 2 < ne) tn = d.ts[jnn];
-        jn = jnn;
-        if (c + 3 < ne) jnn = sidx[(c + 3) * NE];
-        // vertices of the virtual element in the reference frame of element i
-        double rx[3], ry[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          double dx = Xv[2 * k] - Xi[0], dy = Xv[2 * k + 1] - Xi[1];
-          rx[k] = (dx * e2y - dy * e2x) * idet;
-          ry[k] = (e1x * dy - e1y * dx) * idet;
-        }
-        // means of the monomials over the virtual element (rule exact to degree
-        // M); the row is taken in the monomials shifted by their means on the
-        // reference triangle, which span the same space as psi_1 .. psi_nu
-        double mm[nb];
-        monomial_means<M>(rx, ry, mm);
-        double a[nu], b[4];
-#pragma unroll
-        for (int l = 0; l < nu; ++l) a[l] = mm[l + 1] - RefMeans<M>::m[l + 1];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) b[v] = Qv[v] - Qi[v];
-        // Givens rotations fold the row into the triangular factor
-#pragma unroll
-        for (int k = 0; k < nu; ++k) {
-          const double rkk = R[k][k], ak = a[k];
-          const double h2 = rkk * rkk + ak * ak;
-          if (h2 == 0.0) continue;
-          const double rh = rsqrt(h2);
-          const double cs = rkk * rh, sn = ak * rh;
-          R[k][k] = h2 * rh;
-#pragma unroll
-          for (int c2 = k + 1; c2 < nu; ++c2) {
-            const double t = cs * R[k][c2] + sn * a[c2];
-            a[c2] = cs * a[c2] - sn * R[k][c2];
-            R[k][c2] = t;
-          }
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const double t = cs * z[k][v] + sn * b[v];
-            b[v] = cs * b[v] - sn * z[k][v];
-            z[k][v] = t;
+            for (int k = 0; k < 3; ++k) j[k] = d.neigh[k * NE + i];
           }
         }
-      }
-      double u[nu][4];
+        valid = sl < NSTEN && j[0] >= 0;
+        const unsigned long long hi = (unsigned long long)(unsigned)nt << 32;
+        // The probes of all rows go out together (one LDS round trip for all of
+        // them), again and again until every row has found or made its entry;
+        // new entries take slots in the list. Ends: a table without a free entry
+        // holds TAB > CAP of them, each counted by its maker without waiting for
+        // a thread that still probes.
+        unsigned pend = 0;
 #pragma unroll
-      for (int k = nu - 1; k >= 0; --k) {
-        const double rinv = 1.0 / R[k][k];
+        for (int c = 0; c < NR; ++c) {
+          at[c] = int(((unsigned)j[c] * 2654435761u ^ (unsigned)nt * 40503u) >> 16) & (G::TAB - 1);
+          if (j[c] >= 0) pend |= 1u << c;
+        }
+        while (pend) {
+          unsigned long long old[NR];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          double t = z[k][v];
+          for (int c = 0; c < NR; ++c) {
+            old[c] = hi | (unsigned)j[c];
+            if (pend >> c & 1) old[c] = atomicCAS(&key[at[c]], NO_KEY, old[c]);
+          }
+          unsigned won = 0, next = 0;
 #pragma unroll
-          for (int c2 = k + 1; c2 < nu; ++c2) t -= R[k][c2] * u[c2][v];
-          u[k][v] = t * rinv;
+          for (int c = 0; c < NR; ++c) {
+            if (old[c] == NO_KEY)
+              won |= 1u << c;
+            else if (old[c] != (hi | (unsigned)j[c])) {
+              next |= 1u << c;
+              at[c] = (at[c] + 1) & (G::TAB - 1);
+            }
+          }
+          pend = next;
+          if (won) {
+            int slot = atomicAdd(&count, __popc(won));
+#pragma unroll
+            for (int c = 0; c < NR; ++c)
+              if (won >> c & 1) {
+                if (slot < G::CAP) {
+                  entry[slot] = (unsigned short)at[c];
+                  slot_of[at[c]] = (unsigned short)slot;
+                }
+                ++slot;
+              }
+          }
+          if (pend && __atomic_load_n(&count, __ATOMIC_RELAXED) > G::CAP) pend = 0;
         }
       }
-      // oscillation indicator (eq. eqn.sigma), summed over the variables;
-      // it depends only on the polynomial, so it is taken in the shifted
-      // monomials with their own (constant) indicator matrix
-      double sigma = 0.0;
+      __syncthreads();
+      const int n = count;
+      if (n > G::CAP) {   // elements far apart (few rows in common): smaller rounds
+        __syncthreads();
+        round = max(round / 2, G::SUB);
+        continue;
+      }
+      bool ok = true;
+      for (int s = tid; s < n; s += TPB) {
+        const unsigned long long k = key[entry[s]];
+        const int j = int(k & 0xffffffffull);
+        double X[6], Q[4];
+        ok &= project<M>(d, tb, j, int(k >> 32), elem_delta(d, j), X, Q);
+        double2* o = placed + s * 5;
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+        for (int c = 0; c < 3; ++c) o[c] = make_double2(X[2 * c], X[2 * c + 1]);
+        o[3] = make_double2(Q[0], Q[1]);
+        o[4] = make_double2(Q[2], Q[3]);
+      }
+      if (!ok) set_err(d, ERR_PRED);
+#pragma unroll
+      for (int c = 0; c < NR; ++c) at[c] = slot_of[at[c]];
+      __syncthreads();
+      if (mine) {
+        auto stencil_element = [&](int slot, double X[6], double Q[4]) {
+          const double2* o = placed + slot * 5;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const double2 v = o[c];
+            X[2 * c] = v.x;
+            X[2 * c + 1] = v.y;
+          }
+          const double2 q0 = o[3], q1 = o[4];
+          Q[0] = q0.x;
+          Q[1] = q0.y;
+          Q[2] = q1.x;
+          Q[3] = q1.y;
+        };
+        const double* ri = rec<M>(d, i);
+        double Xi[6], Qi[4];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) Xi[c] = ri[XE + c];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Qi[v] = ri[QO + v];
+        double W[nu][4];
+#pragma unroll
+        for (int l = 0; l < nu; ++l)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) W[l][v] = 0.0;
+        double om = 0.0;
+        if (valid) {
+          const double e1x = Xi[2] - Xi[0], e1y = Xi[3] - Xi[1];
+          const double e2x = Xi[4] - Xi[0], e2y = Xi[5] - Xi[1];
+          const double idet = 1.0 / (e1x * e2y - e2x * e1y);
+          const double f1x = e1x * idet, f1y = e1y * idet, f2x = e2x * idet, f2y = e2y * idet;
+          double R[nu][nu], z[nu][4];
+          ls_triangle<M>(R, z, [&](int c, double (&a)[nu], double (&b)[4]) {
+            double Xv[6], Qv[4];
+            stencil_element(at[c - 1], Xv, Qv);
+            // vertices of the virtual element in the reference frame of element i
+            double rx[3], ry[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const double dx = Xv[2 * k] - Xi[0], dy = Xv[2 * k + 1] - Xi[1];
+              rx[k] = dx * f2y - dy * f2x;
+              ry[k] = f1x * dy - f1y * dx;
+            }
+            // means of the monomials over the virtual element; the row is taken
+            // in the monomials shifted by their means on the reference triangle,
+            // which span the same space as psi_1 .. psi_nu
+            double mm[nb];
+            monomial_means<M>(rx, ry, mm);
+#pragma unroll
+            for (int l = 0; l < nu; ++l) a[l] = mm[l + 1] - RefMeans<M>::m[l + 1];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) b[v] = Qv[v] - Qi[v];
+          });
+          double u[nu][4];
+#pragma unroll
+          for (int k = nu - 1; k >= 0; --k) {
+            const double rinv = 1.0 / R[k][k];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              double t = z[k][v];
+#pragma unroll
+              for (int c2 = k + 1; c2 < nu; ++c2) t -= R[k][c2] * u[c2][v];
+              u[k][v] = t * rinv;
+            }
+          }
+          // oscillation indicator (eq. eqn.sigma), summed over the variables;
+          // it depends only on the polynomial, so it is taken in the shifted
+          // monomials with their own (constant) indicator matrix
+          double sigma = 0.0;
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int l = 0; l < nu; ++l) {
+              double t = 0.0;
+#pragma unroll
+              for (int m = 0; m < nu; ++m) t += MonoBasis<M>::c.sig[l][m] * u[m][v];
+              sigma += u[l][v] * t;
+            }
+          const double x = sigma + P.eps;
+          const double x2 = x * x, x4 = x2 * x2, x8 = x4 * x4;
+          om = (sl == 0 ? P.lambda : 1.0) / x8;
+#pragma unroll
+          for (int l = 0; l < nu; ++l)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) W[l][v] = om * u[l][v];
+        }
+        // local CFL time step over the element and its face neighbours (eq.
+        // eqn.timestep): lanes 0..2 take a neighbour each, the others the element
+        double rmin;
+        {
+          int nbs = 0;
+          bool has = false;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const int there = __shfl(at[k], 7, 8);
+            const bool hk = d.neigh[k * NE + i] >= 0;
+            if (sl == k) {
+              nbs = there;
+              has = hk;
+            }
+          }
+          double Xv[6], Qv[4];
+          if (has) {
+            stencil_element(nbs, Xv, Qv);
+          } else {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) Xv[c] = Xi[c];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Qv[v] = Qi[v];
+          }
+          rmin = cfl_ratio(Xv, Qv, P.gamma);
+          rmin = fmin(rmin, dpp_move<0xB1>(rmin));
+          rmin = fmin(rmin, dpp_move<0x4E>(rmin));
+          rmin = fmin(rmin, dpp_move<0x141>(rmin));
+        }
+        const double dt = P.cfl * rmin;
+        // nonlinear combination of eq. weno: the sum over the stencil lanes. Every
+        // lane needs one variable only, vl = sl or 7 - sl, so each step of the sum
+        // hands over the half that the partner keeps (pairs, quads, then the lane
+        // 7 - sl with the same variable): a third of the lane moves of a full
+        // butterfly over every variable, the same additions in the same order.
+        const int half = sl >> 2;
+        const bool k0 = ((sl ^ half) & 1) != 0, k1 = (((sl >> 1) ^ half) & 1) != 0;
+        double Wl[nu];
 #pragma unroll
         for (int l = 0; l < nu; ++l) {
-          double t = 0.0;
+          double t[2];
 #pragma unroll
-          for (int m = 0; m < nu; ++m) t += MonoBasis<M>::c.sig[l][m] * u[m][v];
-          sigma += u[l][v] * t;
+          for (int c = 0; c < 2; ++c) {
+            const double keep = k0 ? W[l][2 * c + 1] : W[l][2 * c], give = k0 ? W[l][2 * c] : W[l][2 * c + 1];
+            t[c] = keep + dpp_move<0xB1>(give);      // quad_perm [1,0,3,2]
+          }
+          const double keep = k1 ? t[1] : t[0], give = k1 ? t[0] : t[1];
+          const double q = keep + dpp_move<0x4E>(give);   // quad_perm [2,3,0,1]
+          Wl[l] = q + dpp_move<0x141>(q);                 // row_half_mirror
         }
-      const double x = sigma + P.eps;
-      const double x2 = x * x, x4 = x2 * x2, x8 = x4 * x4;
-      om = (sl == 0 ? P.lambda : 1.0) / x8;
+        const double iw = 1.0 / group8_sum(om);
+        const int vl = half ? 7 - sl : sl;
+        const double Qv = k1 ? (k0 ? Qi[3] : Qi[2]) : (k0 ? Qi[1] : Qi[0]);
+        // lanes 0..3 write the even nodes, lanes 4..7 the odd ones
+        double* wo = d.wnod + size_t(i) * WS + vl;
 #pragma unroll
-      for (int l = 0; l < nu; ++l)
+        for (int m = 0; m < nb; m += 2) {
+          double t0 = Qv, t1 = Qv;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) W[l][v] = om * u[l][v];
-    }
-    double dt = 0.0;
-    if (sl == 7) {
-      // local CFL time step over the element and its face neighbours (eq. eqn.timestep)
-      double rmin = cfl_ratio(Xi, Qi, P.gamma);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int j = d.neigh[k * NE + i];
-        if (j < 0) continue;
-        double Xv[6], Qv[4];
-        ok &= project<M>(d, tb, j, nt, delta, Xv, Qv);
-        rmin = fmin(rmin, cfl_ratio(Xv, Qv, P.gamma));
-      }
-      dt = P.cfl * rmin;
-    }
-    if (!ok) set_err(d, ERR_PRED);
-    // nonlinear combination of eq. weno: sum over the stencil lanes
-#pragma unroll
-    for (int l = 0; l < nu; ++l)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) W[l][v] = group8_sum<(M == 3)>(W[l][v]);
-    const double iw = 1.0 / group8_sum<(M == 3)>(om);
-    double* wo = d.wnod + size_t(i) * WS;
-#pragma unroll
-    for (int m = 0; m < nb; ++m)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        if (((m * 4 + v) & 7) != sl) continue;
-        double t = Qi[v];
-#pragma unroll
-        for (int l = 0; l < nu; ++l) t += MonoBasis<M>::c.node[m][l] * (W[l][v] * iw);
-        wo[m * 4 + v] = t;
-      }
-    if (sl == 7) {
-      d.dtcfl[i] = dt;
-      if (!(dt > 0.0 && dt < DBL_MAX)) set_err(d, ERR_DT);
-      if (set_level) {
-        const int N = d.scal->N;
-        if (nt >= N) {
-          d.ts[i].step = 0;
-        } else {
-          int over;
-          const int own = level_step(dt, delta, N, nt, d.free_steps, &over);
-          d.ts[i].step = take_step(d, i, own, nt, N, dt, delta, &over);
-          if (over) atomicAdd(&d.scal->overshoots, 1ull);
+          for (int l = 0; l < nu; ++l) {
+            t0 += MonoBasis<M>::c.node[m][l] * (Wl[l] * iw);
+            if (m + 1 < nb) t1 += MonoBasis<M>::c.node[m + 1 < nb ? m + 1 : m][l] * (Wl[l] * iw);
+          }
+          if (m + half < nb) wo[(m + half) * 4] = half ? t1 : t0;
+        }
+        if (sl == 7) {
+          d.dtcfl[i] = dt;
+          if (!(dt > 0.0 && dt < DBL_MAX)) set_err(d, ERR_DT);
+          if (set_level) {
+            const int N = d.scal->N;
+            if (nt >= N) {
+              d.ts[i].step = 0;
+            } else {
+              int over;
+              const int own = level_step(dt, elem_delta(d, i), N, nt, d.free_steps, &over);
+              d.ts[i].step = take_step(d, i, own, nt, N, dt, elem_delta(d, i), &over);
+              if (over) atomicAdd(&d.scal->overshoots, 1ull);
+            }
+          }
         }
       }
+      __syncthreads();   // the next round clears the table
+      base += round;
     }
   }
 }
@@ -958,26 +1084,26 @@ __global__ void k_cycle_begin(Dev d) {
 }
 
 // Each block owns a contiguous chunk of at most SCHED_CHUNK elements; 8 lanes
-// per element share the scan of its scheduling stencil; the block gathers its
-// active elements in LDS and reserves list space with one global atomic. A
+// per element share the scan of its scheduling stencil; the block keeps a bit
+// per active element in LDS and reserves list space with one global atomic. A
 // second list keeps the active elements that stay short of tick N: only they
 // need a predictor after their update (an element reaching tick N gets its
-// next one at the macro-step start, and no stage reads it before).
+// next one at the macro-step start, and no stage reads it before). Both lists
+// are in element order within a chunk: consecutive entries are neighbours, so
+// that the stencils a reconstruction workgroup stages overlap.
 constexpr int SCHED_CHUNK = 1024;
 
 constexpr int SCHED_TPB = 1024;   // 16 wavefronts: a chunk of 1024 elements in 8 passes
 __global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk) {
   const int cycle = d.scal->cycle;
-  constexpr int PER_PASS = SCHED_TPB / 8;
-  __shared__ int local[SCHED_CHUNK], local_live[SCHED_CHUNK];
-  __shared__ int count, gbase, count_live, gbase_live;
+  constexpr int PER_PASS = SCHED_TPB / 8, NMASK = SCHED_CHUNK / 8;   // one mask per wavefront and pass
+  __shared__ unsigned char m_act[NMASK], m_live[NMASK];
+  __shared__ unsigned short p_act[NMASK], p_live[NMASK];
+  __shared__ int gbase, gbase_live;
   const int NE = d.NE;
   const int N = d.scal->N;
   const int sub = threadIdx.x & 7;
-  if (threadIdx.x == 0) {
-    count = 0;
-    count_live = 0;
-  }
+  if (threadIdx.x < NMASK) m_act[threadIdx.x] = m_live[threadIdx.x] = 0;
   __syncthreads();
   const int begin = xcd_block() * chunk;
   const int end = min(NE, begin + chunk);
@@ -1041,39 +1167,53 @@ __global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk) {
       mx = max(mx, __shfl_xor(mx, s));
       mn = min(mn, __shfl_xor(mn, s));
     }
-    // append to both block lists with one LDS atomic per wavefront and list
     const bool isact = unf && sub == 0 && mx <= fut && fut <= mn;
     const bool islive = isact && fut < N;
+    // bits 0, 8, .. 56 of the ballots are the wavefront's 8 elements
     const unsigned long long ba = __ballot(isact), bl = __ballot(islive);
-    const int lane = __lane_id();
-    int pa = 0, pl = 0;
-    if (lane == 0) {
-      pa = ba ? atomicAdd(&count, __popcll(ba)) : 0;
-      pl = bl ? atomicAdd(&count_live, __popcll(bl)) : 0;
+    if (__lane_id() == 0 && ba) {
+      const int w = (base - begin + int(threadIdx.x >> 3)) >> 3;
+      // gather every 8th bit: the product puts them side by side at bit 56
+      m_act[w] = (unsigned char)((ba * 0x0102040810204080ull) >> 56);
+      m_live[w] = (unsigned char)((bl * 0x0102040810204080ull) >> 56);
     }
-    pa = __shfl(pa, 0);
-    pl = __shfl(pl, 0);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    if (isact) {
-      local[pa + __popcll(ba & below)] = i;
-      d.act_stamp[i] = cycle;
-    }
-    if (islive) local_live[pl + __popcll(bl & below)] = i;
+    if (isact) d.act_stamp[i] = cycle;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    gbase = gbase_live = 0;
-    if (count) {
-      const unsigned long long both = (unsigned long long)count | ((unsigned long long)count_live << 32);
-      const unsigned long long old =
-          atomicAdd(reinterpret_cast<unsigned long long*>(&d.scal->n_active), both);
-      gbase = int(old & 0xffffffffull);
-      gbase_live = int(old >> 32);
+  if (threadIdx.x < 64) {
+    // exclusive prefix of the masks' counts, two masks per lane, both lists in
+    // one word (a chunk holds at most 1024)
+    const int l = threadIdx.x;
+    static_assert(NMASK == 128, "two masks per lane");
+    const int c0 = __popc(m_act[2 * l]) | (__popc(m_live[2 * l]) << 16);
+    const int c1 = __popc(m_act[2 * l + 1]) | (__popc(m_live[2 * l + 1]) << 16);
+    int x = c0 + c1;
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+      const int y = __shfl_up(x, s);
+      if (l >= s) x += y;
+    }
+    const int e = x - c0 - c1;
+    p_act[2 * l] = (unsigned short)(e & 0xffff);
+    p_live[2 * l] = (unsigned short)(e >> 16);
+    p_act[2 * l + 1] = (unsigned short)((e + c0) & 0xffff);
+    p_live[2 * l + 1] = (unsigned short)((e + c0) >> 16);
+    if (l == 63) {
+      gbase = gbase_live = 0;
+      if (x) {
+        const unsigned long long both = (unsigned long long)(x & 0xffff) | ((unsigned long long)(x >> 16) << 32);
+        const unsigned long long old =
+            atomicAdd(reinterpret_cast<unsigned long long*>(&d.scal->n_active), both);
+        gbase = int(old & 0xffffffffull);
+        gbase_live = int(old >> 32);
+      }
     }
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < count; k += SCHED_TPB) d.act_list[gbase + k] = local[k];
-  for (int k = threadIdx.x; k < count_live; k += SCHED_TPB) d.live_list[gbase_live + k] = local_live[k];
+  const int w = threadIdx.x >> 3, below = (1 << sub) - 1;   // one element of the chunk per thread
+  const int ma = m_act[w], ml = m_live[w];
+  if (ma >> sub & 1) d.act_list[gbase + p_act[w] + __popc(ma & below)] = begin + threadIdx.x;
+  if (ml >> sub & 1) d.live_list[gbase_live + p_live[w] + __popc(ml & below)] = begin + threadIdx.x;
 }
 
 // ---------------------------------------------------------------------------
@@ -1726,8 +1866,11 @@ static int list_grid(const Dev& d, long blocks_for_all, int use_list) {
 }
 
 int launch_reconstruct(const Dev& d, const Params& p, int M, int use_list, int set_level, void* s) {
-  // 8 lanes per element
-  const int g = list_grid(d, (8L * d.NE + TPB - 1) / TPB, use_list);
+  // 8 lanes per element; a short list takes smaller shares per workgroup, down
+  // to 4 elements over two workgroups per CU (the kernel's own rule)
+  const long full = (8L * d.NE + TPB - 1) / TPB, spread = 2L * (d.n_cu > 0 ? d.n_cu : 256);
+  const long small = (long(d.NE) + 3) / 4;
+  const int g = list_grid(d, std::max(full, std::min(small, spread)), use_list);
   AW_DISPATCH(M, AW_LAUNCH_G(k_reconstruct<MM>, g, s, d, d.tab, p, use_list, set_level));
   return 0;
 }
