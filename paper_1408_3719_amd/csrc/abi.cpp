@@ -218,65 +218,59 @@ int check_err(ader_ctx* c, const aw::Scal& s) {
 }
 
 // Queue n cycles on stream st: update criterion and list, node motion, patch
-// fluxes, update, reconstruction and time step, predictor.
-int issue_cycles(ader_ctx* c, int n, hipStream_t st) {
+// fluxes, update, reconstruction and time step, predictor. first: the cycles
+// before them since the macro-step start (the two sets of list lengths
+// alternate), or -1 when the sets have to be cleared first. last_level: every
+// element ends the macro step in these cycles, so none needs a new predictor.
+int issue_cycles(ader_ctx* c, int n, hipStream_t st, int first, bool last_level = false) {
   const aw::Dev& d = c->dev;
   const aw::Params& p = c->prm;
   const int M = c->cfg.M;
   void* s = st;
+  if (first < 0 && n > 0) LCHK(c, aw::launch_cycle_begin(d, s));
   for (int k = 0; k < n; ++k) {
-    LCHK(c, timed(c, ADER_K_SCHED, st, [&] {
-      int r = aw::launch_cycle_begin(d, s);
-      return r ? r : aw::launch_sched(d, s);
-    }));
-    LCHK(c, timed(c, ADER_K_NODE, st, [&] { return aw::launch_node(d, p, M, s); }));
+    const int list = (std::max(first, 0) + k) & 1;
+    LCHK(c, timed(c, ADER_K_SCHED, st, [&] { return aw::launch_sched(d, list, s); }));
+    LCHK(c, timed(c, ADER_K_NODE, st, [&] { return aw::launch_node(d, p, M, list, s); }));
     LCHK(c, timed(c, ADER_K_PATCH, st, [&] { return aw::launch_patch(d, p, M, s); }));
-    LCHK(c, timed(c, ADER_K_UPDATE, st, [&] { return aw::launch_update(d, p, s); }));
-    LCHK(c, timed(c, ADER_K_RECON, st, [&] { return aw::launch_reconstruct(d, p, M, 1, 1, s); }));
-    LCHK(c, timed(c, ADER_K_PREDICT, st, [&] { return aw::launch_predict(d, p, M, 1, s); }));
+    LCHK(c, timed(c, ADER_K_UPDATE, st, [&] { return aw::launch_update(d, p, list, s); }));
+    LCHK(c, timed(c, ADER_K_RECON, st, [&] { return aw::launch_reconstruct(d, p, M, list, 1, s); }));
+    if (!last_level) LCHK(c, timed(c, ADER_K_PREDICT, st, [&] { return aw::launch_predict(d, p, M, list, s); }));
   }
   return 0;
 }
 
-// Tick lengths and levels of the open instances (flagged by launch_open for
-// the target time on the device beforehand), predictors. nominal = 2^(L-1)
+// Tick lengths and levels of the open instances (flagged by
+// launch_target for the target time or by the macro step before), predictors. nominal = 2^(L-1)
 // for L dyadic levels, 0 for free steps.
 int issue_macro_begin(ader_ctx* c, int nominal, hipStream_t st) {
   const double frac = nominal <= 1 ? 1.0 : c->cfg.lts_step_fraction > 0.0 ? c->cfg.lts_step_fraction : 0.95;
   LCHK(c, timed(c, ADER_K_MACRO, st,
                 [&] { return aw::launch_macro_begin(c->dev, aw::MACRO_TICKS, nominal, frac, st); }));
-  LCHK(c, timed(c, ADER_K_PREDICT, st, [&] { return aw::launch_predict(c->dev, c->prm, c->cfg.M, 0, st); }));
+  LCHK(c, timed(c, ADER_K_PREDICT, st, [&] { return aw::launch_predict(c->dev, c->prm, c->cfg.M, -1, st); }));
   return 0;
 }
 
 // One macro step of L dyadic levels: levels and predictors, 2^(L-1) cycles
-// (enough unless some element took a step below the nominal finest one), the
-// count of elements short of the macro-step end, the macro-step end when that
-// count is zero, and the count of instances still short of the target time.
-// Nothing here depends on the target time, which the kernels read from the
-// device (launch_set_target), so one captured graph serves every target.
+// (enough unless some element took a step below the nominal finest one), and
+// the macro-step end when no element is short of it, with the count of
+// instances still short of the target time. With one level every element takes
+// the whole macro step (its tick length is the smallest CFL step over 2^30, a
+// power of two, so no CFL step is below it), unless a replayed schedule says
+// otherwise. Nothing here depends on the target time, which the kernels read
+// from the device (launch_target), so one captured graph serves every target.
 int issue_macro(ader_ctx* c, int nominal, hipStream_t st) {
   int r;
   if ((r = issue_macro_begin(c, nominal, st))) return r;
-  if ((r = issue_cycles(c, nominal, st))) return r;
-  LCHK(c, timed(c, ADER_K_STATUS, st, [&] { return aw::launch_status(c->dev, st); }));
+  if ((r = issue_cycles(c, nominal, st, 0, nominal == 1 && !c->dev.replay_steps && !c->dev.replay_delta))) return r;
   LCHK(c, aw::launch_macro_end(c->dev, 1, st));
-  LCHK(c, aw::launch_open(c->dev, st));
   return 0;
 }
 
 // Cycles per host check of the free-step run, and of the cycles a dyadic
 // macro step needs beyond 2^(L-1) when elements took spare finer steps.
-constexpr int FREE_BATCH = 16;
+constexpr int FREE_BATCH = 16;   // even: the sets of list lengths alternate
 constexpr int EXTRA_BATCH = 2;
-
-// n cycles, then the count of elements short of tick N.
-int issue_cycle_batch(ader_ctx* c, int n, hipStream_t st) {
-  int r;
-  if ((r = issue_cycles(c, n, st))) return r;
-  LCHK(c, timed(c, ADER_K_STATUS, st, [&] { return aw::launch_status(c->dev, st); }));
-  return 0;
-}
 
 // Capture what `issue` queues into one executable graph.
 template <class F>
@@ -341,8 +335,7 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
   const bool graph = c->graphs && !c->prof;
   aw::Scal s;
   int r;
-  LCHK(c, aw::launch_set_target(c->dev, t_target, c->stream));
-  LCHK(c, aw::launch_open(c->dev, c->stream));
+  LCHK(c, aw::launch_target(c->dev, t_target, c->stream));
   if ((r = read_scal(c, s))) return r;
   for (int k = 0; max_macro <= 0 || k < max_macro; ++k) {
     if ((r = check_err(c, s))) return r;
@@ -361,10 +354,10 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
       for (;;) {
         if (graph) {
           if (!c->gextra &&
-              (r = capture(c, &c->gextra, [&](hipStream_t st) { return issue_cycle_batch(c, EXTRA_BATCH, st); })))
+              (r = capture(c, &c->gextra, [&](hipStream_t st) { return issue_cycles(c, EXTRA_BATCH, st, -1); })))
             return r;
           HIPCHK(c, hipGraphLaunch(c->gextra, c->stream));
-        } else if ((r = issue_cycle_batch(c, EXTRA_BATCH, c->stream))) {
+        } else if ((r = issue_cycles(c, EXTRA_BATCH, c->stream, -1))) {
           return r;
         }
         c->cycles += EXTRA_BATCH;
@@ -376,7 +369,6 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
         last = (long long)s.updates;
       }
       LCHK(c, aw::launch_macro_end(c->dev, 0, c->stream));
-      LCHK(c, aw::launch_open(c->dev, c->stream));
       if ((r = read_scal(c, s))) return r;
       c->long_macro_steps++;
     }
@@ -397,8 +389,7 @@ int run_free(ader_ctx* c, double t_target, int max_macro) {
   const bool graph = c->graphs && !c->prof;
   aw::Scal s;
   int r;
-  LCHK(c, aw::launch_set_target(c->dev, t_target, c->stream));
-  LCHK(c, aw::launch_open(c->dev, c->stream));
+  LCHK(c, aw::launch_target(c->dev, t_target, c->stream));
   if ((r = read_scal(c, s))) return r;
   for (int k = 0; max_macro <= 0 || k < max_macro; ++k) {
     if ((r = check_err(c, s))) return r;
@@ -408,10 +399,10 @@ int run_free(ader_ctx* c, double t_target, int max_macro) {
     for (;;) {
       if (graph) {
         if (!c->gcyc &&
-            (r = capture(c, &c->gcyc, [&](hipStream_t st) { return issue_cycle_batch(c, FREE_BATCH, st); })))
+            (r = capture(c, &c->gcyc, [&](hipStream_t st) { return issue_cycles(c, FREE_BATCH, st, 0); })))
           return r;
         HIPCHK(c, hipGraphLaunch(c->gcyc, c->stream));
-      } else if ((r = issue_cycle_batch(c, FREE_BATCH, c->stream))) {
+      } else if ((r = issue_cycles(c, FREE_BATCH, c->stream, 0))) {
         return r;
       }
       c->cycles += FREE_BATCH;
@@ -422,7 +413,6 @@ int run_free(ader_ctx* c, double t_target, int max_macro) {
       last = (long long)s.updates;
     }
     LCHK(c, aw::launch_macro_end(c->dev, 0, c->stream));
-    LCHK(c, aw::launch_open(c->dev, c->stream));
     if ((r = read_scal(c, s))) return r;
     c->macro_steps++;
   }
@@ -820,7 +810,11 @@ int ader_upload_state_xy(ader_ctx* c, const double* Q_dev, const double* node_xy
   s.N = 1;
   if ((r = h2d(c, d.scal, &s, sizeof(s)))) return r;
   std::vector<aw::Inst> in(d.K);
-  for (auto& x : in) x.T = t0;
+  for (int k = 0; k < d.K; ++k) {
+    in[k].T = t0;
+    in[k].min_dt_bits = ~0ull;
+    in[k].n_elems = c->inst_first[k + 1] - c->inst_first[k];
+  }
   if ((r = h2d(c, d.inst, in.data(), in.size() * sizeof(aw::Inst)))) return r;
   c->cycles = 0;
   c->macro_steps = 0;
@@ -835,7 +829,7 @@ int ader_upload_state_xy(ader_ctx* c, const double* Q_dev, const double* node_xy
   }
   LCHK(c, aw::launch_upload_q(d, Q_dev, c->stream));
   LCHK(c, aw::launch_check_state(d, c->prm.gamma, c->stream));
-  LCHK(c, aw::launch_reconstruct(d, c->prm, c->cfg.M, 0, 0, c->stream));
+  LCHK(c, aw::launch_reconstruct(d, c->prm, c->cfg.M, -1, 0, c->stream));
   aw::Scal back;
   if ((r = read_scal(c, back))) return r;
   if (back.err) return fail(c, ADER_E_STATE, "initial state has rho <= 0 or p <= 0");
@@ -972,7 +966,7 @@ int ader_debug_cycles(ader_ctx* c, int32_t n) {
   if (!c || n < 0) return ADER_E_ARG;
   if (!c->has_state) return fail(c, ADER_E_ORDER, "no state uploaded");
   c->synced = false;
-  int r = issue_cycles(c, n, c->stream);
+  int r = issue_cycles(c, n, c->stream, -1);
   if (r) return r;
   c->cycles += n;
   aw::Scal s;
@@ -985,8 +979,7 @@ int ader_debug_macro_begin(ader_ctx* c, double t_end, int32_t levels) {
   if (!c->has_state) return fail(c, ADER_E_ORDER, "no state uploaded");
   set_free(c, levels == 0);
   c->synced = false;
-  LCHK(c, aw::launch_set_target(c->dev, t_end, c->stream));
-  LCHK(c, aw::launch_open(c->dev, c->stream));
+  LCHK(c, aw::launch_target(c->dev, t_end, c->stream));
   int r = issue_macro_begin(c, levels == 0 ? 0 : 1 << (levels - 1), c->stream);
   if (r) return r;
   aw::Scal s;
@@ -1059,8 +1052,7 @@ int ader_autotune(ader_ctx* c, int32_t trials, ader_tune* chosen) {
     const double far = 1e300;
     // free steps are tuned on 3 dyadic levels: the settings only group work
     const int nominal = c->cfg.lts_levels > 0 ? 1 << (c->cfg.lts_levels - 1) : 4;
-    LCHK(c, aw::launch_set_target(c->dev, far, c->stream));
-    LCHK(c, aw::launch_open(c->dev, c->stream));
+    LCHK(c, aw::launch_target(c->dev, far, c->stream));
     HIPCHK(c, hipEventRecord(e0, c->stream));
     for (int k = 0; k < trials; ++k)
       if ((rr = issue_macro(c, nominal, c->stream))) return rr;
@@ -1366,8 +1358,7 @@ int macro_by_cycles(ader_ctx* c, double t_end, int nominal, F after, int* ran, d
   *ran = 0;
   c->synced = false;
   set_free(c, nominal == 0);
-  LCHK(c, aw::launch_set_target(d, t_end, c->stream));
-  LCHK(c, aw::launch_open(d, c->stream));
+  LCHK(c, aw::launch_target(d, t_end, c->stream));
   if ((r = read_scal(c, s))) return r;
   if ((r = check_err(c, s))) return r;
   if (s.n_open == 0) {
@@ -1384,8 +1375,7 @@ int macro_by_cycles(ader_ctx* c, double t_end, int nominal, F after, int* ran, d
   for (;;) {
     const int batch = nominal == 0 ? FREE_BATCH : (k == 0 ? nominal : 1);
     for (int b = 0; b < batch; ++b) {
-      if ((r = issue_cycles(c, 1, c->stream))) return r;
-      if (b == batch - 1) LCHK(c, aw::launch_status(d, c->stream));
+      if ((r = issue_cycles(c, 1, c->stream, k))) return r;
       if ((r = after(k + 1))) return r;
       ++k;
     }
@@ -1395,7 +1385,6 @@ int macro_by_cycles(ader_ctx* c, double t_end, int nominal, F after, int* ran, d
     if (k > (1 << 20)) return fail(c, ADER_E_DEADLOCK, "no element satisfies the update criterion");
   }
   LCHK(c, aw::launch_macro_end(d, 0, c->stream));
-  LCHK(c, aw::launch_open(d, c->stream));
   if ((r = read_scal(c, s))) return r;
   c->cycles += k;
   if (nominal > 0 && k > nominal) {

@@ -52,9 +52,9 @@ struct Params {
 struct Inst {
   double T;                        // common time at the start of the macro step
   double delta;                    // tick length of the macro step (0 while closed)
-  unsigned long long min_dt_bits;  // min CFL step over its elements (as ordered bits)
+  unsigned long long min_dt_bits;  // min CFL step over its elements (as ordered bits), ~0: none taken yet
   int open;                        // 1 while short of the target time
-  int pad;
+  int n_elems;                     // elements of the instance
 };
 
 // Device-resident scalars of the running simulation.
@@ -62,13 +62,18 @@ struct Scal {
   double t_end;     // target time of the current call (set before a run, read by the kernels)
   int N;            // ticks per macro step
   int n_open;       // instances short of the target time
-  // n_active and n_live share one 8-byte word (little-endian, n_active low):
-  // one 64-bit atomic reserves space in both lists
-  alignas(8) int n_active;  // active elements of the current cycle
-  int n_live;       // active elements that stay short of tick N (they need a new predictor)
-  int n_unfinished; // elements that have not reached tick N
+  // lengths of the cycle's lists, two sets used by alternate cycles: a cycle's
+  // node kernel clears the set of the next one, so that no launch of its own is
+  // needed between cycles. The two lengths share one 8-byte word (little-endian,
+  // n_active low): one 64-bit atomic reserves space in both lists
+  struct alignas(8) {
+    int n_active;   // active elements of the cycle
+    int n_live;     // active elements that stay short of tick N (they need a new predictor)
+  } lists[2];
+  int n_unfinished; // elements that have not reached tick N (set at the macro-step
+                    // start, less those that reach it in each cycle)
   int err;          // sticky error bits (ERR_*)
-  int cycle;        // stamp of the current cycle (advanced by the cycle's first kernel)
+  int cycle;        // stamp of the current cycle (advanced by the cycle's reconstruction)
   int pad;
   unsigned long long max_gcl_bits;  // max relative GCL residual
   unsigned long long updates;
@@ -81,9 +86,7 @@ struct Scal {
   int pad2;
 };
 
-static_assert(offsetof(Scal, n_live) == offsetof(Scal, n_active) + sizeof(int) &&
-                  offsetof(Scal, n_active) % 8 == 0,
-              "n_active and n_live must form one aligned 8-byte word");
+static_assert(offsetof(Scal, lists) % 8 == 0, "n_active and n_live must form one aligned 8-byte word");
 
 enum : int { ERR_GEOM = 1, ERR_STATE = 2, ERR_GCL = 4, ERR_PRED = 8, ERR_DT = 16, ERR_REPLAY = 32, ERR_RECORD = 64 };
 
@@ -309,23 +312,23 @@ int probe_contraction(const Tables* tab, int use_mfma, long n, int iters, const 
 // Kernel launchers (kernels.hip).  All launch on `stream`, return a
 // hipError_t as int.
 int launch_init_geometry(const Dev& d, void* stream);
-int launch_reconstruct(const Dev& d, const Params& p, int M, int use_list, int set_level,
+// list: the set of list lengths (0 or 1) of the cycle, or -1 for every element.
+int launch_reconstruct(const Dev& d, const Params& p, int M, int list, int set_level,
                        void* stream);
-int launch_predict(const Dev& d, const Params& p, int M, int use_list, void* stream);
+int launch_predict(const Dev& d, const Params& p, int M, int list, void* stream);
 int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, void* stream);
-int launch_set_target(const Dev& d, double t_end, void* stream);
+// Target time of the run, and which instances are short of it.
+int launch_target(const Dev& d, double t_end, void* stream);
 int launch_cycle_begin(const Dev& d, void* stream);
-int launch_sched(const Dev& d, void* stream);
+int launch_sched(const Dev& d, int list, void* stream);
 // Start and stop events (hipEvent_t) for the next grid launch of this host
 // thread: its timestamps are the kernel's own start and end.
 void set_next_launch_events(void* start, void* stop);
 bool next_launch_events_pending();
-int launch_node(const Dev& d, const Params& p, int M, void* stream);
+int launch_node(const Dev& d, const Params& p, int M, int list, void* stream);
 int launch_patch(const Dev& d, const Params& p, int M, void* stream);
-int launch_update(const Dev& d, const Params& p, void* stream);
-int launch_status(const Dev& d, void* stream);
+int launch_update(const Dev& d, const Params& p, int list, void* stream);
 int launch_macro_end(const Dev& d, int only_if_done, void* stream);
-int launch_open(const Dev& d, void* stream);
 int launch_download_xy(const Dev& d, double* out, void* stream);
 int launch_upload_xy(const Dev& d, const double* in, void* stream);
 int launch_download_q(const Dev& d, double* out, void* stream);

@@ -19,7 +19,7 @@
 //                 (eqs. timeTransf .. newVertPos)
 // Every write target has a single writer per kernel: no atomics on state.
 // A macro step adds the per-instance tick lengths and levels (k_min_dt,
-// k_macro_setup, k_levels) and its end (k_macro_end); instances of a batch
+// k_levels) and its end (k_macro_end); instances of a batch
 // (independent meshes) keep their own time and tick length (Inst).
 //
 // Lane mappings (64-wide wavefronts):
@@ -107,6 +107,18 @@ __device__ inline void block_max_pos(unsigned long long* ctr, double v) {
     for (int w = 0; w < int(blockDim.x / 64); ++w) t = fmax(t, part_max[w]);
     if (t > 0.0) atomic_max_pos(ctr, t);
   }
+}
+
+// Sum over a workgroup of TPB threads, in thread 0 (every thread calls it).
+__device__ inline int block_sum(int v) {
+  __shared__ int part_sum[TPB / 64];
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) v += __shfl_xor(v, s);
+  if (__lane_id() == 0) part_sum[threadIdx.x / 64] = v;
+  __syncthreads();
+  int t = 0;
+  for (int w = 0; w < TPB / 64; ++w) t += part_sum[w];
+  return t;
 }
 
 __device__ inline double pressure(const double q[4], double g) {
@@ -464,16 +476,19 @@ constexpr unsigned long long NO_KEY = ~0ull;
 
 template <int M>
 __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruct(Dev d, const Tables* __restrict__ tb, Params P,
-                                                     int use_list, int set_level) {
+                                                     int list, int set_level) {
   using S = Sz<M>;
   using G = Stage<M>;
+  const bool use_list = list >= 0;
   constexpr int nb = S::nb, ne = S::ne, nu = S::nu, WS = S::WS, NR = ne - 1;
   __shared__ unsigned long long key[G::TAB];      // tick << 32 | element
   __shared__ unsigned short slot_of[G::TAB], entry[G::CAP];
   __shared__ double2 placed[G::CAP * 5];          // x0 y0 x1 y1 x2 y2 Q0..Q3
   __shared__ int count;
   const int NE = d.NE;
-  const int nitems = use_list ? d.scal->n_active : NE;
+  const int nitems = use_list ? d.scal->lists[list].n_active : NE;
+  // the cycle's stamp has served its last reader (the update)
+  if (use_list && blockIdx.x == 0 && threadIdx.x == 0) d.scal->cycle += 1;
   const int tid = threadIdx.x, sl = tid & 7, grp = tid >> 3;
   // elements per workgroup: all 32 lane groups when the launch fills the chip
   // twice over, else fewer, so that a short list still spreads over every CU
@@ -759,8 +774,9 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
 // ---------------------------------------------------------------------------
 template <int M>
 __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict__ tb, Params P,
-                                                 int use_list) {
+                                                 int list) {
   using S = Sz<M>;
+  const bool use_list = list >= 0;
   constexpr int nb = S::nb, T = S::nt, nG = S::nG, RS = S::RS, TS = S::TS, WS = S::WS;
   constexpr int G = nb, EPW = S::EPW, WPB = TPB / 64;
   constexpr int SLOTS = EPW * WPB;       // elements per block
@@ -775,7 +791,7 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
   __shared__ double lds[(SLOTS + WPB) * LSTR];   // one extra slot per wavefront for its spare lanes
   __shared__ double c0[16][TPB];         // per lane: fixed parts of slice t = 0
   const int NE = d.NE;
-  const int nitems = use_list ? d.scal->n_live : NE;
+  const int nitems = use_list ? d.scal->lists[list].n_live : NE;
   const double g = P.gamma;
   unsigned long long npred = 0;    // predictors evaluated (counted on node 0)
   const int wv = threadIdx.x / 64, lw = threadIdx.x % 64;
@@ -1076,11 +1092,11 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
 // ---------------------------------------------------------------------------
 // Scheduling
 // ---------------------------------------------------------------------------
+// Clears both sets of list lengths: before cycles that do not follow a
+// macro-step start or another cycle of the alternation.
 __global__ void k_cycle_begin(Dev d) {
-  d.scal->n_active = 0;
-  d.scal->n_live = 0;
-  d.scal->n_unfinished = 0;
-  d.scal->cycle += 1;
+  d.scal->lists[0] = {0, 0};
+  d.scal->lists[1] = {0, 0};
 }
 
 // Each block owns a contiguous chunk of at most SCHED_CHUNK elements; 8 lanes
@@ -1094,7 +1110,7 @@ __global__ void k_cycle_begin(Dev d) {
 constexpr int SCHED_CHUNK = 1024;
 
 constexpr int SCHED_TPB = 1024;   // 16 wavefronts: a chunk of 1024 elements in 8 passes
-__global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk) {
+__global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk, int list) {
   const int cycle = d.scal->cycle;
   constexpr int PER_PASS = SCHED_TPB / 8, NMASK = SCHED_CHUNK / 8;   // one mask per wavefront and pass
   __shared__ unsigned char m_act[NMASK], m_live[NMASK];
@@ -1203,7 +1219,7 @@ __global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk) {
       if (x) {
         const unsigned long long both = (unsigned long long)(x & 0xffff) | ((unsigned long long)(x >> 16) << 32);
         const unsigned long long old =
-            atomicAdd(reinterpret_cast<unsigned long long*>(&d.scal->n_active), both);
+            atomicAdd(reinterpret_cast<unsigned long long*>(&d.scal->lists[list]), both);
         gbase = int(old & 0xffffffffull);
         gbase_live = int(old >> 32);
       }
@@ -1220,12 +1236,20 @@ __global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk) {
 // Node solver and node motion
 // ---------------------------------------------------------------------------
 template <int M>
-__global__ void __launch_bounds__(TPB) k_node(Dev d, const Tables* __restrict__ tb, Params P) {
+__global__ void __launch_bounds__(TPB) k_node(Dev d, const Tables* __restrict__ tb, Params P, int list) {
   const int cycle = d.scal->cycle;
   constexpr int T = M + 1, VV = Sz<M>::VV;
   const int NV = d.NV;
   unsigned long long nmoved = 0;   // nodes moved by this lane
-  if (blockIdx.x == 0 && threadIdx.x == 0) d.scal->updates += (unsigned long long)d.scal->n_active;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const auto l = d.scal->lists[list];
+    d.scal->updates += (unsigned long long)l.n_active;
+    d.scal->n_unfinished -= l.n_active - l.n_live;
+    d.scal->lists[1 - list] = {0, 0};   // the next cycle's
+  }
+  // the next macro step's smallest CFL steps are taken afresh
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.K; k += gridDim.x * blockDim.x)
+    d.inst[k].min_dt_bits = ~0ull;
   for (int k = xcd_block() * blockDim.x + threadIdx.x; k < NV; k += gridDim.x * blockDim.x) {
     const int r0 = d.ring_ptr[k], r1 = d.ring_ptr[k + 1];
     int newt = -1;
@@ -1440,10 +1464,10 @@ __global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__
 // Memory variables and conservative update
 // ---------------------------------------------------------------------------
 template <int M>
-__global__ void __launch_bounds__(TPB) k_update(Dev d, Params P) {
+__global__ void __launch_bounds__(TPB) k_update(Dev d, Params P, int list) {
   const int cycle = d.scal->cycle;
   const int NE = d.NE, NV = d.NV;
-  const int na = d.scal->n_active;
+  const int na = d.scal->lists[list].n_active;
   const int nwork = (na + TPB - 1) / TPB;
   double gmax = 0.0;   // largest relative GCL residual seen by this lane
   for (int idx = xcd_block(nwork) * blockDim.x + threadIdx.x; idx < na; idx += gridDim.x * blockDim.x) {
@@ -1503,11 +1527,6 @@ __global__ void __launch_bounds__(TPB) k_update(Dev d, Params P) {
 // ---------------------------------------------------------------------------
 // Macro-step boundary
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(TPB) k_reset_min(Dev d) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.K; k += gridDim.x * blockDim.x)
-    d.inst[k].min_dt_bits = ~0ull;
-}
-
 // Smallest CFL step per instance. Instances own contiguous element ranges, so
 // a wavefront's 64 consecutive elements belong to one instance except at range
 // ends: their minimum then, else each lane's, goes to the instance. A
@@ -1579,54 +1598,57 @@ __global__ void __launch_bounds__(TPB) k_min_dt(Dev d) {
   }
 }
 
-// Tick length of the macro step per open instance: for dyadic levels the
+// Tick length of the macro step of an open instance: for dyadic levels the
 // smallest CFL step times the step fraction, times dscale = 2^(L-1) / N (a
 // power of two), clamped so that N ticks do not pass the target time; for free
-// steps the interval to the target over N; 0 for closed ones. An instance that
-// had no finite positive CFL step (k_min_dt left its minimum unset) raises
-// ERR_DT.
-__global__ void __launch_bounds__(TPB) k_macro_setup(Dev d, int N, double fraction, double dscale) {
-  const double t_end = d.scal->t_end;
-  if (blockIdx.x == 0 && threadIdx.x == 0) d.scal->N = N;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.K; k += gridDim.x * blockDim.x) {
-    Inst* in = d.inst + k;
-    if (!in->open) {
-      in->delta = 0.0;
-      continue;
-    }
-    const double rest = (t_end - in->T) / double(N);
-    if (d.free_steps) {
-      in->delta = rest;
-    } else if (in->min_dt_bits == ~0ull) {
-      in->delta = 0.0;
-    } else {
-      in->delta = fmin((__longlong_as_double((long long)in->min_dt_bits) * fraction) * dscale, rest);
-    }
-    const int m = d.scal->macro_index;
-    if (d.replay_delta) {
-      if (m < d.replay_delta_n)
-        in->delta = fmin(d.replay_delta[m], rest);
-      else
-        set_err(d, ERR_REPLAY);
-    }
-    if (d.rec_delta) {
-      if (m < d.rec_delta_cap)
-        d.rec_delta[m] = in->delta;
-      else
-        set_err(d, ERR_RECORD);
-    }
-    if (!(in->delta > 0.0)) set_err(d, ERR_DT);
-  }
+// steps the interval to the target over N; a replayed length as recorded; 0
+// for closed instances and where there was no finite positive CFL step.
+__device__ inline double macro_delta(const Dev& d, const Inst& in, int N, double fraction, double dscale) {
+  if (!in.open) return 0.0;
+  const double rest = (d.scal->t_end - in.T) / double(N);
+  if (d.replay_delta && d.scal->macro_index < d.replay_delta_n)
+    return fmin(d.replay_delta[d.scal->macro_index], rest);
+  if (d.free_steps) return rest;
+  if (in.min_dt_bits == ~0ull) return 0.0;
+  return fmin((__longlong_as_double((long long)in.min_dt_bits) * fraction) * dscale, rest);
 }
 
-// Levels at the macro-step start; elements of closed instances sit at tick N
-// with no step, i.e. finished.
-__global__ void __launch_bounds__(TPB) k_levels(Dev d) {
-  const int N = d.scal->N;
-  const int n = max(d.NE, d.NV);
+// Tick lengths and levels at the macro-step start; elements of closed instances
+// sit at tick N with no step, i.e. finished. Every thread works out its
+// instance's tick length itself; the first K also keep it, with its checks and
+// records.
+__global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, double dscale) {
+  const int n = max(max(d.NE, d.NV), d.K);
+  if (blockIdx.x == 0) {
+    int unfinished = 0;
+    for (int k = threadIdx.x; k < d.K; k += TPB) unfinished += d.inst[k].open ? d.inst[k].n_elems : 0;
+    unfinished = block_sum(unfinished);
+    if (threadIdx.x == 0) {
+      d.scal->N = N;
+      d.scal->n_open = 0;             // counted at the macro-step end
+      d.scal->lists[0] = {0, 0};
+      d.scal->lists[1] = {0, 0};
+      d.scal->n_unfinished = unfinished;
+    }
+  }
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    if (i < d.K) {
+      const double delta = macro_delta(d, d.inst[i], N, fraction, dscale);
+      d.inst[i].delta = delta;
+      if (d.inst[i].open) {
+        const int m = d.scal->macro_index;
+        if (d.replay_delta && m >= d.replay_delta_n) set_err(d, ERR_REPLAY);
+        if (d.rec_delta) {
+          if (m < d.rec_delta_cap)
+            d.rec_delta[m] = delta;
+          else
+            set_err(d, ERR_RECORD);
+        }
+        if (!(delta > 0.0)) set_err(d, ERR_DT);
+      }
+    }
     if (i < d.NE) {
-      const double delta = d.inst[d.e_inst[i]].delta;
+      const double delta = macro_delta(d, d.inst[d.K == 1 ? 0 : d.e_inst[i]], N, fraction, dscale);
       TickStep me;
       if (delta > 0.0) {
         int over;
@@ -1644,67 +1666,48 @@ __global__ void __launch_bounds__(TPB) k_levels(Dev d) {
   }
 }
 
-// Ends the macro step: each instance's time advanced, ticks reset. With
+// Is an instance at time T short of the target time (the test the host applies
+// to a single time)?
+__device__ inline int short_of(double T, double t_end) {
+  return !(t_end - T <= 1e-12 * fmax(1.0, fabs(t_end)));
+}
+
+// Ends the macro step: each instance's time advanced, ticks reset, and the
+// instances still short of the target time flagged and counted. With
 // only_if_done, it does nothing unless every element has reached the end of
 // the macro step (the host then runs further cycles and ends the step itself).
 __global__ void __launch_bounds__(TPB) k_macro_end(Dev d, int only_if_done) {
   if (only_if_done && d.scal->n_unfinished != 0) return;
   const int N = d.scal->N;
+  const double t_end = d.scal->t_end;
   if (blockIdx.x == 0 && threadIdx.x == 0) d.scal->macro_index += 1;
   const int n = max(max(d.NE, d.NV), d.K);
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     if (i < d.K) {
       Inst* in = d.inst + i;
-      in->T = in->T + double(N) * in->delta;
+      const double T = in->T + double(N) * in->delta;
+      in->T = T;
+      in->open = short_of(T, t_end);
+      if (in->open) atomicAdd(&d.scal->n_open, 1);
     }
     if (i < d.NE) d.ts[i].tick = 0;
     if (i < d.NV) d.ntick[i] = 0;
   }
 }
 
-__global__ void k_set_target(Dev d, double t_end) { d.scal->t_end = t_end; }
-
-// Which instances are short of the target time (the same test the host applies
-// to a single time), and how many.
-__global__ void __launch_bounds__(TPB) k_open(Dev d) {
-  const double t_end = d.scal->t_end;
-  const double tol = 1e-12 * fmax(1.0, fabs(t_end));
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.K; k += gridDim.x * blockDim.x)
-    d.inst[k].open = !(t_end - d.inst[k].T <= tol);
-}
-
-__global__ void __launch_bounds__(TPB) k_count_open(Dev d) {
-  __shared__ int part[TPB / 64];
+// The target time of a run, and which instances are short of it, and how many
+// (one workgroup).
+__global__ void __launch_bounds__(TPB) k_target(Dev d, double t_end) {
   int c = 0;
-  for (int k = threadIdx.x; k < d.K; k += blockDim.x) c += d.inst[k].open;
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) c += __shfl_xor(c, s);
-  if (__lane_id() == 0) part[threadIdx.x / 64] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int w = 0; w < TPB / 64; ++w) t += part[w];
-    d.scal->n_open = t;
+  for (int k = threadIdx.x; k < d.K; k += blockDim.x) {
+    const int open = short_of(d.inst[k].T, t_end);
+    d.inst[k].open = open;
+    c += open;
   }
-}
-
-__global__ void k_count_reset(Dev d) { d.scal->n_unfinished = 0; }
-
-__global__ void __launch_bounds__(TPB) k_count(Dev d) {
-  __shared__ int part[TPB / 64];
-  const int N = d.scal->N;
-  int c = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d.NE; i += gridDim.x * blockDim.x)
-    c += d.ts[i].tick < N ? 1 : 0;
-  // one atomic per workgroup
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) c += __shfl_xor(c, s);
-  if (__lane_id() == 0) part[threadIdx.x / 64] = c;
-  __syncthreads();
+  c = block_sum(c);
   if (threadIdx.x == 0) {
-    int t = 0;
-    for (int w = 0; w < TPB / 64; ++w) t += part[w];
-    if (t) atomicAdd(&d.scal->n_unfinished, t);
+    d.scal->n_open = c;
+    d.scal->t_end = t_end;
   }
 }
 
@@ -1865,35 +1868,34 @@ static int list_grid(const Dev& d, long blocks_for_all, int use_list) {
   return int(b);
 }
 
-int launch_reconstruct(const Dev& d, const Params& p, int M, int use_list, int set_level, void* s) {
+int launch_reconstruct(const Dev& d, const Params& p, int M, int list, int set_level, void* s) {
   // 8 lanes per element; a short list takes smaller shares per workgroup, down
   // to 4 elements over two workgroups per CU (the kernel's own rule)
   const long full = (8L * d.NE + TPB - 1) / TPB, spread = 2L * (d.n_cu > 0 ? d.n_cu : 256);
   const long small = (long(d.NE) + 3) / 4;
-  const int g = list_grid(d, std::max(full, std::min(small, spread)), use_list);
-  AW_DISPATCH(M, AW_LAUNCH_G(k_reconstruct<MM>, g, s, d, d.tab, p, use_list, set_level));
+  const int g = list_grid(d, std::max(full, std::min(small, spread)), list >= 0);
+  AW_DISPATCH(M, AW_LAUNCH_G(k_reconstruct<MM>, g, s, d, d.tab, p, list, set_level));
   return 0;
 }
 
-int launch_predict(const Dev& d, const Params& p, int M, int use_list, void* s) {
+int launch_predict(const Dev& d, const Params& p, int M, int list, void* s) {
   AW_DISPATCH(M, {
     constexpr int per_block = Sz<MM>::EPW * (TPB / 64);
-    const int g = list_grid(d, (long(d.NE) + per_block - 1) / per_block, use_list);
-    AW_LAUNCH_G(k_predict<MM>, g, s, d, d.tab, p, use_list);
+    const int g = list_grid(d, (long(d.NE) + per_block - 1) / per_block, list >= 0);
+    AW_LAUNCH_G(k_predict<MM>, g, s, d, d.tab, p, list);
   });
   return 0;
 }
 
-int launch_set_target(const Dev& d, double t_end, void* s) {
-  AW_LAUNCH1(k_set_target, s, d, t_end);
+int launch_target(const Dev& d, double t_end, void* s) {
+  AW_LAUNCH_G(k_target, 1, s, d, t_end);
   return 0;
 }
 
 int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, void* s) {
-  AW_LAUNCH(k_reset_min, d.K, s, d);
   AW_LAUNCH(k_min_dt, (long(d.NE) + MIN_U - 1) / MIN_U, s, d);
-  AW_LAUNCH(k_macro_setup, d.K, s, d, N, fraction, double(nominal) / double(N));
-  AW_LAUNCH(k_levels, d.NE > d.NV ? d.NE : d.NV, s, d);
+  const long n = std::max(long(std::max(d.NE, d.NV)), long(d.K));
+  AW_LAUNCH(k_levels, n, s, d, N, fraction, double(nominal) / double(N));
   return 0;
 }
 
@@ -1902,7 +1904,7 @@ int launch_cycle_begin(const Dev& d, void* s) {
   return 0;
 }
 
-int launch_sched(const Dev& d, void* s) {
+int launch_sched(const Dev& d, int list, void* s) {
   // chunks of at most SCHED_CHUNK elements, at least ~1024 blocks when possible,
   // unless a chunk size was chosen; at least one pass of SCHED_TPB / 8 elements.
   // Each block reserves its list space with one atomic, and atomics on one
@@ -1910,7 +1912,7 @@ int launch_sched(const Dev& d, void* s) {
   int chunk = d.sched_chunk > 0 ? d.sched_chunk : (d.NE + 1023) / 1024;
   chunk = chunk < SCHED_TPB / 8 ? SCHED_TPB / 8 : (chunk > SCHED_CHUNK ? SCHED_CHUNK : chunk);
   const int blocks = (d.NE + chunk - 1) / chunk;
-  AW_LAUNCH_GB(k_sched, blocks, SCHED_TPB, s, d, chunk);
+  AW_LAUNCH_GB(k_sched, blocks, SCHED_TPB, s, d, chunk, list);
   return 0;
 }
 
@@ -1928,8 +1930,8 @@ static int sweep_grid(const Dev& d, long n) {
   return int(b);
 }
 
-int launch_node(const Dev& d, const Params& p, int M, void* s) {
-  AW_DISPATCH(M, AW_LAUNCH_G(k_node<MM>, sweep_grid(d, d.NV), s, d, d.tab, p));
+int launch_node(const Dev& d, const Params& p, int M, int list, void* s) {
+  AW_DISPATCH(M, AW_LAUNCH_G(k_node<MM>, sweep_grid(d, d.NV), s, d, d.tab, p, list));
   return 0;
 }
 
@@ -1941,18 +1943,9 @@ int launch_patch(const Dev& d, const Params& p, int M, void* s) {
 // The update kernel runs over the cycle's active list, whose length only the
 // device knows: a grid sized for every element (or the persistent grid of the
 // launch settings), blocks beyond the list exit at once.
-int launch_update(const Dev& d, const Params& p, void* s) {
+int launch_update(const Dev& d, const Params& p, int list, void* s) {
   const int g = list_grid(d, (long(d.NE) + TPB - 1) / TPB, 1);
-  AW_DISPATCH(d.M, AW_LAUNCH_G(k_update<MM>, g, s, d, p));
-  return 0;
-}
-
-int launch_status(const Dev& d, void* s) {
-  AW_LAUNCH1(k_count_reset, s, d);
-  {
-    const int g = grid_for(d.NE), cap = 2 * (d.n_cu > 0 ? d.n_cu : 256);
-    AW_LAUNCH_G(k_count, g < cap ? g : cap, s, d);
-  }
+  AW_DISPATCH(d.M, AW_LAUNCH_G(k_update<MM>, g, s, d, p, list));
   return 0;
 }
 
@@ -1960,12 +1953,6 @@ int launch_macro_end(const Dev& d, int only_if_done, void* s) {
   long n = d.NE > d.NV ? d.NE : d.NV;
   if (d.K > n) n = d.K;
   AW_LAUNCH(k_macro_end, n, s, d, only_if_done);
-  return 0;
-}
-
-int launch_open(const Dev& d, void* s) {
-  AW_LAUNCH(k_open, d.K, s, d);
-  AW_LAUNCH_G(k_count_open, 1, s, d);
   return 0;
 }
 
