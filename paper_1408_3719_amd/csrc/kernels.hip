@@ -196,14 +196,15 @@ __device__ inline void osher_dissipation(const Tables* tb, const double ql[4], c
 
 // Numerical flux through the unnormalised space-time normal N of a patch
 // quadrature point: Rusanov (eq. eqn.rusanov), Osher-type (eq. eqn.osher) or HLL.
-__device__ inline void numerical_flux(int flux, const Tables* tb, const double ql[4],
+template <int FLUX>
+__device__ inline void numerical_flux(const Tables* tb, const double ql[4],
                                       const double qr[4], const double N[3], double g,
                                       double out[4]) {
   const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
   double fl[4], fr[4], unl, cl, unr, cr;
   stflux(ql, N, nxy, g, fl, unl, cl);
   stflux(qr, N, nxy, g, fr, unr, cr);
-  if (flux == ADER_FLUX_HLL) {
+  if constexpr (FLUX == ADER_FLUX_HLL) {
     // signal speeds bounded over both states; upwind when both have one sign
     const double sl = fmin(unl - cl, unr - cr), sr = fmax(unl + cl, unr + cr);
     if (sl >= 0.0) {
@@ -217,7 +218,7 @@ __device__ inline void numerical_flux(int flux, const Tables* tb, const double q
 #pragma unroll
       for (int v = 0; v < 4; ++v) out[v] = (sr * fl[v] - sl * fr[v] + sl * sr * (qr[v] - ql[v])) * id;
     }
-  } else if (flux == ADER_FLUX_OSHER) {
+  } else if constexpr (FLUX == ADER_FLUX_OSHER) {
     double D[4];
     osher_dissipation(tb, ql, qr, N, nxy, g, D);
 #pragma unroll
@@ -1315,26 +1316,25 @@ __global__ void __launch_bounds__(TPB) k_node(Dev d, const Tables* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Space-time patch fluxes: one lane per edge; an edge with a moved node
-// sweeps a patch, whose flux and normal integral go to the memory-variable
-// slots of the edge in its two elements (each slot has one writer per cycle:
-// its edge)
+// Space-time patch fluxes: an edge with a moved node sweeps a patch, whose flux
+// and normal integral go to the memory-variable slots of the edge in its two
+// elements (each slot has one writer per cycle: its edge). The flux is a
+// template argument, so that a kernel holds one flux's registers.
 // ---------------------------------------------------------------------------
-template <int M>
-__global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__ tb, Params P) {
-  const int cycle = d.scal->cycle;
-  constexpr int T = M + 1, nG = M + 1, TS = Sz<M>::TS;
-  const int NV = d.NV, NF = d.NF;
-  const double g = P.gamma;
-  unsigned long long npatch = 0;   // patches integrated by this lane
-  for (int e = xcd_block() * blockDim.x + threadIdx.x; e < NF; e += gridDim.x * blockDim.x) {
-    const int a = d.e_a[e], b = d.e_b[e];
-    const bool ma = d.node_stamp[a] == cycle, mb = d.node_stamp[b] == cycle;
-    if (!ma && !mb) continue;
+
+// A swept patch: corners (x, y, t) old a, old b, new b, new a and their ticks,
+// the elements left and right with their ticks and steps, the boundary tag.
+struct PatchCorners {
+  double P1[3], P2[3], P3[3], P4[3], n1, n2, n3, n4;
+  int L, R, bc;
+  TickStep tL, tR;
+  __device__ inline void load(const Dev& d, int a, int b, bool ma, bool mb) {
+    const int NV = d.NV;
     const double delta = node_delta(d, a);
-    double P1[3], P2[3], P3[3], P4[3];
-    const double n1 = d.ntick[a], n2 = d.ntick[b];
-    const double n3 = mb ? d.ntick_new[b] : n2, n4 = ma ? d.ntick_new[a] : n1;
+    n1 = d.ntick[a];
+    n2 = d.ntick[b];
+    n3 = mb ? d.ntick_new[b] : n2;
+    n4 = ma ? d.ntick_new[a] : n1;
     P1[0] = d.X[a];
     P1[1] = d.X[NV + a];
     P1[2] = n1 * delta;
@@ -1347,11 +1347,111 @@ __global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__
     P4[0] = ma ? d.Xnew[a] : P1[0];
     P4[1] = ma ? d.Xnew[NV + a] : P1[1];
     P4[2] = n4 * delta;
-    const int L = d.e_L[e], el = d.e_el[e], R = d.e_R[e], er = d.e_er[e], bc = d.e_bc[e];
-    const TickStep tL = d.ts[L];
-    TickStep tR{0, 1};
-    if (R >= 0) tR = d.ts[R];
-    if (tL.step <= 0 || tR.step <= 0) {
+  }
+};
+
+// Adds the nG points of Gauss row gq along the edge (eqs. G_ij, eqn.STint) to the
+// flux G and the normal integral Nn; trL, trR: the edge's traces in L and in R
+// (read in reverse order).
+template <int M, int FLUX>
+__device__ inline void patch_row(const Dev& d, const Tables* __restrict__ tb, double g, int gq, const PatchCorners& C,
+                                 const double* trL, const double* trR, double G[4], double Nn[3]) {
+  constexpr int T = M + 1, nG = M + 1;
+  double qL[T][4], qR[T][4];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      qL[t][v] = trL[(gq * T + t) * 4 + v];
+      qR[t][v] = trR[((nG - 1 - gq) * T + t) * 4 + v];
+    }
+  const double c = tb->gchi[gq];
+#pragma unroll 1
+  for (int h = 0; h < nG; ++h) {
+    const double tt = tb->gchi[h];
+    const double w = tb->gw[gq] * tb->gw[h];
+    double dchi[3], dtau[3], N[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      dchi[k] = (1.0 - tt) * (C.P2[k] - C.P1[k]) + tt * (C.P3[k] - C.P4[k]);
+      dtau[k] = (1.0 - c) * (C.P4[k] - C.P1[k]) + c * (C.P3[k] - C.P2[k]);
+    }
+    N[0] = dchi[1] * dtau[2] - dchi[2] * dtau[1];
+    N[1] = dchi[2] * dtau[0] - dchi[0] * dtau[2];
+    N[2] = dchi[0] * dtau[1] - dchi[1] * dtau[0];
+    const double tk = (1.0 - c) * (1.0 - tt) * C.n1 + c * (1.0 - tt) * C.n2 + c * tt * C.n3 + (1.0 - c) * tt * C.n4;
+    double lL[T];
+    time_basis<M>(tick_ratio(tk - C.tL.tick, C.tL.step), lL);
+    double ql[4], qr[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double s = 0.0;
+#pragma unroll
+      for (int t = 0; t < T; ++t) s += lL[t] * qL[t][v];
+      ql[v] = s;
+    }
+    if (C.R >= 0) {
+      double lR[T];
+      time_basis<M>(tick_ratio(tk - C.tR.tick, C.tR.step), lR);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double s = 0.0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) s += lR[t] * qR[t][v];
+        qr[v] = s;
+      }
+    } else if (C.bc == 2) {
+      // slip wall: mirror the normal momentum
+      const double inxy = rsqrt(N[0] * N[0] + N[1] * N[1]);
+      const double nx = N[0] * inxy, ny = N[1] * inxy;
+      const double mn = ql[1] * nx + ql[2] * ny;
+      qr[0] = ql[0];
+      qr[1] = ql[1] - 2.0 * mn * nx;
+      qr[2] = ql[2] - 2.0 * mn * ny;
+      qr[3] = ql[3];
+    } else {
+      // transmissive: the inner element's predicted cell mean at this
+      // time (a ghost copy of the element; the inner trace as outer state
+      // leaves the face without dissipation and lets boundary modes grow)
+      const double* rl = rec<M>(d, C.L);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double s = 0.0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) s += lL[t] * rl[AVG + t * 4 + v];
+        qr[v] = s;
+      }
+    }
+    double fn[4];
+    numerical_flux<FLUX>(tb, ql, qr, N, g, fn);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) G[v] += w * fn[v];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) Nn[k] += w * N[k];
+  }
+}
+
+// One lane per edge.
+template <int M, int FLUX>
+__global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__ tb, Params P) {
+  const int cycle = d.scal->cycle;
+  constexpr int T = M + 1, nG = M + 1, TS = Sz<M>::TS;
+  const int NV = d.NV, NF = d.NF;
+  const double g = P.gamma;
+  unsigned long long npatch = 0;   // patches integrated by this lane
+  for (int e = xcd_block() * blockDim.x + threadIdx.x; e < NF; e += gridDim.x * blockDim.x) {
+    const int a = d.e_a[e], b = d.e_b[e];
+    const bool ma = d.node_stamp[a] == cycle, mb = d.node_stamp[b] == cycle;
+    if (!ma && !mb) continue;
+    PatchCorners C;
+    C.load(d, a, b, ma, mb);
+    const int el = d.e_el[e], er = d.e_er[e];
+    const int L = C.L = d.e_L[e], R = C.R = d.e_R[e];
+    C.bc = d.e_bc[e];
+    C.tL = d.ts[L];
+    C.tR = TickStep{0, 1};
+    if (R >= 0) C.tR = d.ts[R];
+    if (C.tL.step <= 0 || C.tR.step <= 0) {
       set_err(d, ERR_PRED);
       continue;
     }
@@ -1370,81 +1470,9 @@ __global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__
     }
     double G[4] = {0, 0, 0, 0}, Nn[3] = {0, 0, 0};
 #pragma unroll 1
-    for (int gq = 0; gq < nG; ++gq) {
-      double qL[T][4], qR[T][4];
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          qL[t][v] = trL[(gq * T + t) * 4 + v];
-          qR[t][v] = trR[((nG - 1 - gq) * T + t) * 4 + v];
-        }
-      const double c = tb->gchi[gq];
-#pragma unroll 1
-      for (int h = 0; h < nG; ++h) {
-        const double tt = tb->gchi[h];
-        const double w = tb->gw[gq] * tb->gw[h];
-        double dchi[3], dtau[3], N[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          dchi[k] = (1.0 - tt) * (P2[k] - P1[k]) + tt * (P3[k] - P4[k]);
-          dtau[k] = (1.0 - c) * (P4[k] - P1[k]) + c * (P3[k] - P2[k]);
-        }
-        N[0] = dchi[1] * dtau[2] - dchi[2] * dtau[1];
-        N[1] = dchi[2] * dtau[0] - dchi[0] * dtau[2];
-        N[2] = dchi[0] * dtau[1] - dchi[1] * dtau[0];
-        const double tk = (1.0 - c) * (1.0 - tt) * n1 + c * (1.0 - tt) * n2 + c * tt * n3 + (1.0 - c) * tt * n4;
-        double lL[T];
-        time_basis<M>(tick_ratio(tk - tL.tick, tL.step), lL);
-        double ql[4], qr[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          double s = 0.0;
-#pragma unroll
-          for (int t = 0; t < T; ++t) s += lL[t] * qL[t][v];
-          ql[v] = s;
-        }
-        if (R >= 0) {
-          double lR[T];
-          time_basis<M>(tick_ratio(tk - tR.tick, tR.step), lR);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            double s = 0.0;
-#pragma unroll
-            for (int t = 0; t < T; ++t) s += lR[t] * qR[t][v];
-            qr[v] = s;
-          }
-        } else if (bc == 2) {
-          // slip wall: mirror the normal momentum
-          const double inxy = rsqrt(N[0] * N[0] + N[1] * N[1]);
-          const double nx = N[0] * inxy, ny = N[1] * inxy;
-          const double mn = ql[1] * nx + ql[2] * ny;
-          qr[0] = ql[0];
-          qr[1] = ql[1] - 2.0 * mn * nx;
-          qr[2] = ql[2] - 2.0 * mn * ny;
-          qr[3] = ql[3];
-        } else {
-          // transmissive: the inner element's predicted cell mean at this
-          // time (a ghost copy of the element; the inner trace as outer state
-          // leaves the face without dissipation and lets boundary modes grow)
-          const double* rl = rec<M>(d, L);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            double s = 0.0;
-#pragma unroll
-            for (int t = 0; t < T; ++t) s += lL[t] * rl[AVG + t * 4 + v];
-            qr[v] = s;
-          }
-        }
-        double fn[4];
-        numerical_flux(P.flux, tb, ql, qr, N, g, fn);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) G[v] += w * fn[v];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) Nn[k] += w * N[k];
-      }
-    }
-    // inflow-positive memory variables: the flux leaves L and enters R
+    for (int gq = 0; gq < nG; ++gq)
+      patch_row<M, FLUX>(d, tb, g, gq, C, trL, trR, G, Nn);
+        // inflow-positive memory variables: the flux leaves L and enters R
 #pragma unroll
     for (int v = 0; v < 4; ++v) sl[v] = mL[v] - G[v];
 #pragma unroll
@@ -1456,6 +1484,87 @@ __global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__
       for (int k = 0; k < 3; ++k) sr[4 + k] = mR[4 + k] + Nn[k];
     }
     ++npatch;
+  }
+  block_add(&d.scal->n_patch, npatch);
+}
+
+// One lane per Gauss row: nG lanes of a wavefront share an edge. The wavefront
+// looks at 64 / nG consecutive edges, so every swept one has its lanes. A patch
+// is a serial chain of nG^2 points behind four dependent loads; on a mesh that
+// leaves the chip short of wavefronts the chain is what counts (9k-triangle
+// explosion, HLL: 18.7 -> 8.0 us per launch; 4.7k vortex, M=2 13.6 -> 8.4; 19k
+// vortex, M=3 20.1 -> 14.2), on a large one the repeated index loads cost more
+// (75k vortex 26.9 us against 22.6 with a lane per edge; 302k explosion 83
+// against 67).
+template <int M, int FLUX>
+__global__ void __launch_bounds__(TPB) k_patch_split(Dev d, const Tables* __restrict__ tb, Params P) {
+  const int cycle = d.scal->cycle;
+  constexpr int T = M + 1, nG = M + 1, TS = Sz<M>::TS, SPAN = 64 / nG;
+  const int NF = d.NF;
+  unsigned long long npatch = 0;   // patches integrated (counted on an edge's lane 0)
+  const int wv = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int gq = lane % nG, lead = lane - gq;
+  const int stride = gridDim.x * (TPB / 64) * SPAN;
+  for (int base = (xcd_block() * (TPB / 64) + wv) * SPAN; base < NF; base += stride) {
+    const int e = base + lane / nG;
+    bool live = lane < SPAN * nG && e < NF;
+    int a = 0, b = 0;
+    bool ma = false, mb = false;
+    if (live) {
+      a = d.e_a[e];
+      b = d.e_b[e];
+      ma = d.node_stamp[a] == cycle;
+      mb = d.node_stamp[b] == cycle;
+      live = ma || mb;
+    }
+    if (!__any(live)) continue;
+    double G[4] = {0, 0, 0, 0}, Nn[3] = {0, 0, 0};
+    double* slot = nullptr;     // lane 0 of an edge adds to the left slot, lane 1 to the right one
+    double mem[7];
+    if (live) {
+      PatchCorners C;
+      C.load(d, a, b, ma, mb);
+      const int el = d.e_el[e], er = d.e_er[e];
+      const int L = C.L = d.e_L[e], R = C.R = d.e_R[e];
+      C.bc = d.e_bc[e];
+      C.tL = d.ts[L];
+      C.tR = TickStep{0, 1};
+      if (R >= 0) C.tR = d.ts[R];
+      const double* trL = d.trace + size_t(L) * TS + el * nG * T * 4;
+      const double* trR = R >= 0 ? d.trace + size_t(R) * TS + er * nG * T * 4 : trL;
+      if (gq == 0) slot = d.mem + (size_t(L) * 3 + el) * MEM_W;
+      if (gq == 1 && R >= 0) slot = d.mem + (size_t(R) * 3 + er) * MEM_W;
+      if (slot) {
+#pragma unroll
+        for (int c = 0; c < 7; ++c) mem[c] = slot[c];
+      }
+      if (C.tL.step <= 0 || C.tR.step <= 0) {
+        set_err(d, ERR_PRED);
+        slot = nullptr;
+      } else {
+        patch_row<M, FLUX>(d, tb, P.gamma, gq, C, trL, trR, G, Nn);
+        if (gq == 0) ++npatch;
+      }
+    }
+    // sums over the edge's lanes, the same in each of them
+    auto sum = [&](double x) {
+      double s = __shfl(x, lead);
+#pragma unroll
+      for (int q = 1; q < nG; ++q) s += __shfl(x, lead + q);
+      return s;
+    };
+#pragma unroll
+    for (int v = 0; v < 4; ++v) G[v] = sum(G[v]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) Nn[k] = sum(Nn[k]);
+    // inflow-positive memory variables: the flux leaves L and enters R
+    if (slot) {
+      const double sgn = gq == 0 ? -1.0 : 1.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) slot[v] = mem[v] + sgn * G[v];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) slot[4 + k] = mem[4 + k] + sgn * Nn[k];
+    }
   }
   block_add(&d.scal->n_patch, npatch);
 }
@@ -1935,8 +2044,26 @@ int launch_node(const Dev& d, const Params& p, int M, int list, void* s) {
   return 0;
 }
 
+// A lane per Gauss row while that makes at most 8 wavefronts per CU, else a lane
+// per edge (k_patch_split has both sides' times; in between, 30k-triangle
+// explosion, 3 levels, M=2, 9 wavefronts per CU: 15.0 us against 14.5).
+template <int M, int FLUX>
+static int patch_grid(const Dev& d, const Params& p, void* s) {
+  constexpr int span = 64 / (M + 1);
+  const long waves = (long(d.NF) + span - 1) / span;
+  if (waves <= 8 * long(d.n_cu > 0 ? d.n_cu : 256))
+    AW_LAUNCH_G((k_patch_split<M, FLUX>), sweep_grid(d, waves * 64), s, d, d.tab, p);
+  else
+    AW_LAUNCH_G((k_patch<M, FLUX>), sweep_grid(d, d.NF), s, d, d.tab, p);
+  return 0;
+}
+
 int launch_patch(const Dev& d, const Params& p, int M, void* s) {
-  AW_DISPATCH(M, AW_LAUNCH_G(k_patch<MM>, sweep_grid(d, d.NF), s, d, d.tab, p));
+  AW_DISPATCH(M, {
+    return p.flux == ADER_FLUX_HLL     ? patch_grid<MM, ADER_FLUX_HLL>(d, p, s)
+           : p.flux == ADER_FLUX_OSHER ? patch_grid<MM, ADER_FLUX_OSHER>(d, p, s)
+                                       : patch_grid<MM, ADER_FLUX_RUSANOV>(d, p, s);
+  });
   return 0;
 }
 
