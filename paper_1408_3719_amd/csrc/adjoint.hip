@@ -95,183 +95,6 @@ struct AZ {
                        LB = L_SIG + 1;
 };
 
-// Euler fluxes f, g (eq. eulerTerms) with p from eq. eqn.eos.
-__device__ inline void euler_fg(const double q[4], double gam, double f[4], double g[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r, E = q[3];
-  const double p = (gam - 1.0) * (E - 0.5 * r * (u * u + v * v));
-  f[0] = r * u;
-  f[1] = r * u * u + p;
-  f[2] = r * u * v;
-  f[3] = u * (E + p);
-  g[0] = r * v;
-  g[1] = r * u * v;
-  g[2] = r * v * v + p;
-  g[3] = v * (E + p);
-}
-
-// Adjoint of the primitive variables (rho, u, v, p, E written as rb, ub, vb,
-// pb, Eb) pulled back to the conserved ones: qb += d(rho, u, v, p, E)/dq ^T (.).
-__device__ inline void prim_pullback(const double q[4], double gam, double rb, double ub, double vb,
-                                     double pb, double Eb, double qb[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double gm = gam - 1.0;
-  Eb += gm * pb;
-  rb += -gm * 0.5 * (u * u + v * v) * pb;
-  ub += -gm * r * u * pb;
-  vb += -gm * r * v * pb;
-  qb[0] += rb - (ub * u + vb * v) / r;
-  qb[1] += ub / r;
-  qb[2] += vb / r;
-  qb[3] += Eb;
-}
-
-// qb += J_f(q)^T fb + J_g(q)^T gb
-__device__ inline void euler_fg_vjp(const double q[4], double gam, const double fb[4],
-                                    const double gb[4], double qb[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r, E = q[3];
-  const double p = (gam - 1.0) * (E - 0.5 * r * (u * u + v * v));
-  const double H = E + p;
-  double rb = 0.0, ub = 0.0, vb = 0.0, pb = 0.0, Eb = 0.0;
-  rb += fb[0] * u;            ub += fb[0] * r;
-  rb += fb[1] * u * u;        ub += fb[1] * 2.0 * r * u;   pb += fb[1];
-  rb += fb[2] * u * v;        ub += fb[2] * r * v;         vb += fb[2] * r * u;
-  ub += fb[3] * H;            Eb += fb[3] * u;             pb += fb[3] * u;
-  rb += gb[0] * v;            vb += gb[0] * r;
-  rb += gb[1] * u * v;        ub += gb[1] * r * v;         vb += gb[1] * r * u;
-  rb += gb[2] * v * v;        vb += gb[2] * 2.0 * r * v;   pb += gb[2];
-  vb += gb[3] * H;            Eb += gb[3] * v;             pb += gb[3] * v;
-  prim_pullback(q, gam, rb, ub, vb, pb, Eb, qb);
-}
-
-// ALE signal speed |u.N_xy + N_t| + c |N_xy| (eq. eqn.rusanov)
-__device__ inline double signal_speed(const double q[4], const double N[3], double nxy, double gam) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double p = (gam - 1.0) * (q[3] - 0.5 * r * (u * u + v * v));
-  return fabs(u * N[0] + v * N[1] + N[2]) + sqrt(gam * p / r) * nxy;
-}
-
-// qb += sb * d(signal speed)/dq
-__device__ inline void signal_speed_vjp(const double q[4], const double N[3], double nxy, double gam,
-                                        double sb, double qb[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double p = (gam - 1.0) * (q[3] - 0.5 * r * (u * u + v * v));
-  const double un = u * N[0] + v * N[1] + N[2];
-  const double sg = (un > 0.0) ? 1.0 : (un < 0.0 ? -1.0 : 0.0);
-  const double c = sqrt(gam * p / r);
-  const double cb = sb * nxy;
-  prim_pullback(q, gam, -cb * c / (2.0 * r), sb * sg * N[0], sb * sg * N[1], cb * gam / (2.0 * c * r),
-                0.0, qb);
-}
-
-// Adjoint of the Rusanov flux 0.5 (F(ql) + F(qr)) . N - 0.5 smax (qr - ql).
-__device__ inline void rusanov_vjp(const double ql[4], const double qr[4], const double N[3],
-                                   double gam, const double Gb[4], double qlb[4], double qrb[4]) {
-  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
-  const double sl = signal_speed(ql, N, nxy, gam), sr = signal_speed(qr, N, nxy, gam);
-  const bool left = sl >= sr;
-  const double smax = left ? sl : sr;
-  double fb[4], gb[4], sbar = 0.0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    fb[v] = 0.5 * N[0] * Gb[v];
-    gb[v] = 0.5 * N[1] * Gb[v];
-    qlb[v] += 0.5 * N[2] * Gb[v] + 0.5 * smax * Gb[v];
-    qrb[v] += 0.5 * N[2] * Gb[v] - 0.5 * smax * Gb[v];
-    sbar -= 0.5 * Gb[v] * (qr[v] - ql[v]);
-  }
-  euler_fg_vjp(ql, gam, fb, gb, qlb);
-  euler_fg_vjp(qr, gam, fb, gb, qrb);
-  if (left)
-    signal_speed_vjp(ql, N, nxy, gam, sbar, qlb);
-  else
-    signal_speed_vjp(qr, N, nxy, gam, sbar, qrb);
-}
-
-// ALE signal speeds u.N_xy + N_t -/+ c|N_xy|
-__device__ inline void hll_speeds(const double q[4], const double N[3], double nxy, double gam,
-                                  double& lo, double& hi) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double p = (gam - 1.0) * (q[3] - 0.5 * r * (u * u + v * v));
-  const double un = u * N[0] + v * N[1] + N[2];
-  const double c = sqrt(gam * p / r) * nxy;
-  lo = un - c;
-  hi = un + c;
-}
-
-// qb += sb * d(u.N_xy + N_t + sgn * c|N_xy|)/dq
-__device__ inline void hll_speed_vjp(const double q[4], const double N[3], double nxy, double gam,
-                                     double sgn, double sb, double qb[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double p = (gam - 1.0) * (q[3] - 0.5 * r * (u * u + v * v));
-  const double c = sqrt(gam * p / r);
-  const double cb = sgn * sb * nxy;
-  prim_pullback(q, gam, -cb * c / (2.0 * r), sb * N[0], sb * N[1], cb * gam / (2.0 * c * r), 0.0, qb);
-}
-
-// qb += J_ft(q)^T gb with ft = f N_x + g N_y + q N_t
-__device__ inline void ft_vjp(const double q[4], const double N[3], double gam, const double gb[4],
-                              double qb[4]) {
-  double fb[4], gg[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    fb[v] = N[0] * gb[v];
-    gg[v] = N[1] * gb[v];
-    qb[v] += N[2] * gb[v];
-  }
-  euler_fg_vjp(q, gam, fb, gg, qb);
-}
-
-// Adjoint of the HLL flux: speeds bounded over both states (the left state's
-// speed on ties), upwind when both have one sign, else
-// (sr F(ql) - sl F(qr) + sl sr (qr - ql)) / (sr - sl).
-__device__ inline void hll_vjp(const double ql[4], const double qr[4], const double N[3], double gam,
-                               const double Gb[4], double qlb[4], double qrb[4]) {
-  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
-  double l1, r1, l2, r2;
-  hll_speeds(ql, N, nxy, gam, l1, r1);
-  hll_speeds(qr, N, nxy, gam, l2, r2);
-  const bool left_lo = l1 <= l2, left_hi = r1 >= r2;
-  const double sl = left_lo ? l1 : l2, sr = left_hi ? r1 : r2;
-  if (sl >= 0.0) {
-    ft_vjp(ql, N, gam, Gb, qlb);
-    return;
-  }
-  if (sr <= 0.0) {
-    ft_vjp(qr, N, gam, Gb, qrb);
-    return;
-  }
-  double fl[4], fr[4], f[4], g[4];
-  euler_fg(ql, gam, f, g);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) fl[v] = f[v] * N[0] + g[v] * N[1] + ql[v] * N[2];
-  euler_fg(qr, gam, f, g);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) fr[v] = f[v] * N[0] + g[v] * N[1] + qr[v] * N[2];
-  const double id = 1.0 / (sr - sl);
-  double flb[4], frb[4], slb = 0.0, srb = 0.0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const double d = qr[v] - ql[v];
-    const double F = (sr * fl[v] - sl * fr[v] + sl * sr * d) * id;
-    flb[v] = sr * id * Gb[v];
-    frb[v] = -sl * id * Gb[v];
-    qrb[v] += sl * sr * id * Gb[v];
-    qlb[v] -= sl * sr * id * Gb[v];
-    srb += Gb[v] * (fl[v] + sl * d - F) * id;
-    slb += Gb[v] * (-fr[v] + sr * d + F) * id;
-  }
-  ft_vjp(ql, N, gam, flb, qlb);
-  ft_vjp(qr, N, gam, frb, qrb);
-  if (left_lo)
-    hll_speed_vjp(ql, N, nxy, gam, -1.0, slb, qlb);
-  else
-    hll_speed_vjp(qr, N, nxy, gam, -1.0, slb, qrb);
-  if (left_hi)
-    hll_speed_vjp(ql, N, nxy, gam, 1.0, srb, qlb);
-  else
-    hll_speed_vjp(qr, N, nxy, gam, 1.0, srb, qrb);
-}
-
 __device__ inline double group8_sum(double v) {
   v += __shfl_xor(v, 1);
   v += __shfl_xor(v, 2);
@@ -295,6 +118,34 @@ __device__ inline double group8_sum_dpp(double v) {
   v += dpp_move<0x141>(v);   // row_half_mirror: lane i <-> 7 - i within 8
   return v;
 }
+
+// Patch kernels of the adjoints: nG lanes of a wavefront share an edge, one per
+// Gauss row along it (64 / nG edges per wavefront, the remaining lanes spare).
+// The products of a point are long serial chains, so a lane per edge runs nG^2
+// of them in a row at one wavefront per SIMD.
+template <int M>
+struct EdgeLanes {
+  static constexpr int nG = M + 1, SPAN = 64 / nG;
+  int row, lead;   // Gauss row of this lane, first lane of its edge
+  bool use;        // not one of the spare lanes
+  __device__ inline EdgeLanes() {
+    const int lane = threadIdx.x % 64;
+    row = lane % nG;
+    lead = lane - row;
+    use = lane < SPAN * nG;
+  }
+  // first edge of the wavefront, and the stride of the grid
+  __device__ inline int base() const { return (blockIdx.x * (TPB / 64) + int(threadIdx.x / 64)) * SPAN; }
+  __device__ inline int stride() const { return gridDim.x * (TPB / 64) * SPAN; }
+  __device__ inline int edge() const { return int(threadIdx.x % 64) / nG; }
+  // the sum over the edge's lanes, in each of them; every lane of the wavefront calls it
+  __device__ inline double sum(double x) const {
+    double s = __shfl(x, lead);
+#pragma unroll
+    for (int q = 1; q < nG; ++q) s += __shfl(x, lead + q);
+    return s;
+  }
+};
 
 // Row of the least-squares system for stencil element j seen from element i:
 // the means over T_j, mapped into the reference frame of T_i (vertices Xi,
@@ -750,7 +601,7 @@ __global__ void __launch_bounds__(TPB) k_adj_pred_fwd(Dev d, const Tables* __res
       for (int t = 0; t < T; ++t) {
         double f[nb][4], g[nb][4];
 #pragma unroll
-        for (int m = 0; m < nb; ++m) euler_fg(q[m][t], P.gamma, f[m], g[m]);
+        for (int m = 0; m < nb; ++m) lag::euler_f_g(q[m][t], P.gamma, f[m], g[m]);
 #pragma unroll
         for (int kk = 0; kk < nb; ++kk)
 #pragma unroll
@@ -803,58 +654,64 @@ __global__ void __launch_bounds__(TPB) k_adj_pred_fwd(Dev d, const Tables* __res
 }
 
 // Adjoint of the fluxes through the space-time faces of the fixed edges.
-template <int M>
+template <int M, bool HLL>
 __global__ void __launch_bounds__(TPB) k_adj_patch(Dev d, const Tables* __restrict__ tb, Params P,
                                                    AdjWork w, double dt) {
   using S = AZ<M>;
   constexpr int T = S::T, nG = S::nG, TS = S::TS;
   const int NE = d.NE, NV = d.NV, NF = d.NF;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < NF; e += gridDim.x * blockDim.x) {
-    const int a = d.e_a[e], b = d.e_b[e];
-    const int L = d.e_L[e], el = d.e_el[e], R = d.e_R[e], er = d.e_er[e], bc = d.e_bc[e];
-    const double P1[3] = {d.X[a], d.X[NV + a], 0.0};
-    const double P2[3] = {d.X[b], d.X[NV + b], 0.0};
-    const double P3[3] = {d.X[b], d.X[NV + b], dt};
-    const double P4[3] = {d.X[a], d.X[NV + a], dt};
-    // flux adjoint: Q_L' = Q_L - G / |T_L|, Q_R' = Q_R + G / |T_R|
-    double Gb[4];
-    const double AL = d.rec[size_t(L) * S::RS + AO];
-    const double AR = R >= 0 ? d.rec[size_t(R) * S::RS + AO] : 1.0;
+  const EdgeLanes<M> ln;
+  for (int base = ln.base(); base < NF; base += ln.stride()) {
+    const int e = base + ln.edge();
+    const bool live = ln.use && e < NF;
+    bool open_edge = false;
+    double bA[T][4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      Gb[v] = -w.qbar_next[size_t(v) * NE + L] / AL;
-      if (R >= 0) Gb[v] += w.qbar_next[size_t(v) * NE + R] / AR;
-    }
-    const double* trL = w.trace + size_t(L) * TS + el * nG * T * 4;
-    const double* trR = R >= 0 ? w.trace + size_t(R) * TS + er * nG * T * 4 : trL;
-    const bool open_edge = R < 0 && bc != 2;
-    const double* avL = w.avg + size_t(L) * T * 4;
-    double bL[nG][T][4], bR[nG][T][4], bA[T][4];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-#pragma unroll
-      for (int g = 0; g < nG; ++g)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          bL[g][t][v] = 0.0;
-          bR[g][t][v] = 0.0;
-        }
+    for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) bA[t][v] = 0.0;
-    }
+    if (live) {
+      const int a = d.e_a[e], b = d.e_b[e];
+      const int L = d.e_L[e], el = d.e_el[e], R = d.e_R[e], er = d.e_er[e], bc = d.e_bc[e];
+      const double P1[3] = {d.X[a], d.X[NV + a], 0.0};
+      const double P2[3] = {d.X[b], d.X[NV + b], 0.0};
+      const double P3[3] = {P2[0], P2[1], dt};
+      const double P4[3] = {P1[0], P1[1], dt};
+      // flux adjoint: Q_L' = Q_L - G / |T_L|, Q_R' = Q_R + G / |T_R|
+      double Gb[4];
+      const double AL = d.rec[size_t(L) * S::RS + AO];
+      const double AR = R >= 0 ? d.rec[size_t(R) * S::RS + AO] : 1.0;
 #pragma unroll
-    for (int gq = 0; gq < nG; ++gq) {
+      for (int v = 0; v < 4; ++v) {
+        Gb[v] = -w.qbar_next[size_t(v) * NE + L] / AL;
+        if (R >= 0) Gb[v] += w.qbar_next[size_t(v) * NE + R] / AR;
+      }
+      open_edge = R < 0 && bc != 2;
+      const int gq = ln.row;
+      const double* trL = w.trace + size_t(L) * TS + (el * nG + gq) * T * 4;
+      const double* trR = R >= 0 ? w.trace + size_t(R) * TS + (er * nG + nG - 1 - gq) * T * 4 : trL;
+      const double* avL = w.avg + size_t(L) * T * 4;
+      double aL[T][4], aR[T][4], bL[T][4], bR[T][4];
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          aL[t][v] = trL[t * 4 + v];
+          aR[t][v] = open_edge ? avL[t * 4 + v] : trR[t * 4 + v];   // transmissive: the inner element's means
+          bL[t][v] = 0.0;
+          bR[t][v] = 0.0;
+        }
       const double c = tb->gchi[gq];
+      double dtau[3];
 #pragma unroll
+      for (int k = 0; k < 3; ++k) dtau[k] = (1.0 - c) * (P4[k] - P1[k]) + c * (P3[k] - P2[k]);
+#pragma unroll 1
       for (int h = 0; h < nG; ++h) {
         const double tt = tb->gchi[h];
         const double wgt = tb->gw[gq] * tb->gw[h];
-        double dchi[3], dtau[3], N[3];
+        double dchi[3], N[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          dchi[k] = (1.0 - tt) * (P2[k] - P1[k]) + tt * (P3[k] - P4[k]);
-          dtau[k] = (1.0 - c) * (P4[k] - P1[k]) + c * (P3[k] - P2[k]);
-        }
+        for (int k = 0; k < 3; ++k) dchi[k] = (1.0 - tt) * (P2[k] - P1[k]) + tt * (P3[k] - P4[k]);
         N[0] = dchi[1] * dtau[2] - dchi[2] * dtau[1];
         N[1] = dchi[2] * dtau[0] - dchi[0] * dtau[2];
         N[2] = dchi[0] * dtau[1] - dchi[1] * dtau[0];
@@ -868,14 +725,15 @@ __global__ void __launch_bounds__(TPB) k_adj_patch(Dev d, const Tables* __restri
           double s = 0.0, s2 = 0.0;
 #pragma unroll
           for (int t = 0; t < T; ++t) {
-            s += l[t] * trL[(gq * T + t) * 4 + v];
-            s2 += l[t] * trR[((nG - 1 - gq) * T + t) * 4 + v];
+            s += l[t] * aL[t][v];
+            s2 += l[t] * aR[t][v];
           }
           ql[v] = s;
           qr[v] = s2;
         }
         double nx = 0.0, ny = 0.0;
-        if (R < 0 && bc == 2) {
+        const bool wall = R < 0 && bc == 2;
+        if (wall) {
           const double inxy = 1.0 / sqrt(N[0] * N[0] + N[1] * N[1]);
           nx = N[0] * inxy;
           ny = N[1] * inxy;
@@ -884,70 +742,63 @@ __global__ void __launch_bounds__(TPB) k_adj_patch(Dev d, const Tables* __restri
           qr[1] = ql[1] - 2.0 * mn * nx;
           qr[2] = ql[2] - 2.0 * mn * ny;
           qr[3] = ql[3];
-        } else if (open_edge) {
-          // transmissive: the inner element's predicted mean at this time
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            double s = 0.0;
-#pragma unroll
-            for (int t = 0; t < T; ++t) s += l[t] * avL[t * 4 + v];
-            qr[v] = s;
-          }
         }
         double Gw[4], qlb[4] = {0, 0, 0, 0}, qrb[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int v = 0; v < 4; ++v) Gw[v] = wgt * Gb[v];
-        if (P.flux == ADER_FLUX_HLL)
-          hll_vjp(ql, qr, N, P.gamma, Gw, qlb, qrb);
+        double Nb[3] = {0, 0, 0};   // the mesh is fixed: not used
+        if constexpr (HLL)
+          lag::hll_flux_vjp(ql, qr, N, P.gamma, Gw, qlb, qrb, Nb);
         else
-          rusanov_vjp(ql, qr, N, P.gamma, Gw, qlb, qrb);
-        if (R >= 0) {
-#pragma unroll
-          for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) bR[nG - 1 - gq][t][v] += l[t] * qrb[v];
-        } else if (bc == 2) {
+          lag::rusanov_flux_vjp(ql, qr, N, P.gamma, Gw, qlb, qrb, Nb);
+        if (wall) {
           // the mirror map is a symmetric reflection of the momentum
           const double mb = qrb[1] * nx + qrb[2] * ny;
           qlb[0] += qrb[0];
           qlb[1] += qrb[1] - 2.0 * mb * nx;
           qlb[2] += qrb[2] - 2.0 * mb * ny;
           qlb[3] += qrb[3];
-        } else {
-#pragma unroll
-          for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) bA[t][v] += l[t] * qrb[v];
         }
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) bL[gq][t][v] += l[t] * qlb[v];
+          for (int v = 0; v < 4; ++v) {
+            bL[t][v] += l[t] * qlb[v];
+            bR[t][v] += l[t] * qrb[v];
+          }
       }
-    }
-    double* oL = w.tbar + size_t(L) * TS + el * nG * T * 4;
-#pragma unroll
-    for (int g = 0; g < nG; ++g)
+      double* oL = w.tbar + size_t(L) * TS + (el * nG + gq) * T * 4;
 #pragma unroll
       for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) oL[(g * T + t) * 4 + v] = bL[g][t][v];
-    if (open_edge) {
-      // adjoint of the inner element's means, in this edge's own slot
-      double* aL = w.abar + size_t(e) * T * 4;
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) aL[t * 4 + v] = bA[t][v];
-    }
-    if (R >= 0) {
-      double* oR = w.tbar + size_t(R) * TS + er * nG * T * 4;
-#pragma unroll
-      for (int g = 0; g < nG; ++g)
+        for (int v = 0; v < 4; ++v) oL[t * 4 + v] = bL[t][v];
+      if (R >= 0) {
+        double* oR = w.tbar + size_t(R) * TS + (er * nG + nG - 1 - gq) * T * 4;
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) oR[(g * T + t) * 4 + v] = bR[g][t][v];
+          for (int v = 0; v < 4; ++v) oR[t * 4 + v] = bR[t][v];
+      }
+      if (open_edge) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) bA[t][v] = bR[t][v];
+      }
+    }
+    // adjoint of the inner element's means, in a transmissive edge's own slot
+    if (__any(open_edge)) {
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bA[t][v] = ln.sum(bA[t][v]);
+      if (open_edge && ln.row == 0) {
+        double* aL = w.abar + size_t(e) * T * 4;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) aL[t * 4 + v] = bA[t][v];
+      }
     }
   }
 }
@@ -1041,7 +892,7 @@ __global__ void __launch_bounds__(TPB) k_adj_pred_rev(Dev d, const Tables* __res
             gb[v] = -(mt[1] * ax + mt[3] * ae);
             q[v] = st[size_t((m * T + t) * 4 + v) * NE];
           }
-          euler_fg_vjp(q, P.gamma, fb, gb, acc);
+          lag::euler_f_g_vjp(q, P.gamma, fb, gb, acc);
 #pragma unroll
           for (int v = 0; v < 4; ++v) nq[m][t][v] = acc[v] + (t == 0 ? nb0[m][v] : 0.0);
         }
@@ -1399,43 +1250,62 @@ __global__ void __launch_bounds__(TPB) k_lag_area_new(Dev d, LagWork w) {
 // positive) and, in the same pass, its adjoint for Gbar = -Qbar'_L / |T_L'| + Qbar'_R / |T_R'|
 // onto the traces, the inner element's means (transmissive edge) and the
 // four corners.
-template <int M>
+template <int M, bool HLL>
 __global__ void __launch_bounds__(TPB) k_lag_patch(Dev d, const Tables* __restrict__ tb, Params P, LagWork w,
                                                    double dt) {
   using S = AZ<M>;
   constexpr int T = S::T, nG = S::nG, TS = S::TS, NT = nG * T * 4;
   const int NE = d.NE, NF = d.NF;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < NF; e += gridDim.x * blockDim.x) {
-    const int a = d.e_a[e], b = d.e_b[e];
-    const int L = d.e_L[e], el = d.e_el[e], R = d.e_R[e], er = d.e_er[e];
-    const bool hasR = R >= 0;
-    const int kind = hasR ? lag::INTERIOR : (d.e_bc[e] == 2 ? lag::SLIP : lag::TRANSMISSIVE);
-    const double xa[2] = {w.x[2 * a], w.x[2 * a + 1]}, xb[2] = {w.x[2 * b], w.x[2 * b + 1]};
-    const double xan[2] = {w.xn[2 * a], w.xn[2 * a + 1]}, xbn[2] = {w.xn[2 * b], w.xn[2 * b + 1]};
-    const double* trL = w.a.trace + size_t(L) * TS + el * NT;
-    const double* trR = hasR ? w.a.trace + size_t(R) * TS + er * NT : trL;
-    const double* avL = w.a.avg + size_t(L) * T * 4;
-    double Gb[4];
-    const double anL = w.an[L], anR = hasR ? w.an[R] : 1.0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      Gb[v] = -w.a.qbar_next[size_t(v) * NE + L] / anL;
-      if (hasR) Gb[v] += w.a.qbar_next[size_t(v) * NE + R] / anR;
-    }
+  const EdgeLanes<M> ln;
+  for (int base = ln.base(); base < NF; base += ln.stride()) {
+    const int e = base + ln.edge();
+    const bool live = ln.use && e < NF;
+    int L = 0, el = 0, R = -1, er = 0, kind = lag::INTERIOR;
     double G[4] = {0.0, 0.0, 0.0, 0.0}, bA[T * 4];
 #pragma unroll
     for (int k = 0; k < T * 4; ++k) bA[k] = 0.0;
     double c[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double* oL = w.a.tbar + size_t(L) * TS + el * NT;
-    double* oR = hasR ? w.a.tbar + size_t(R) * TS + er * NT : oL;
-    lag::patch_flux_vjp<M>(*tb, P.gamma, xa, xb, xan, xbn, dt, trL, trR, avL, kind, Gb, G, oL, oR, bA, c, c + 2,
-                           c + 4, c + 6, P.flux == ADER_FLUX_HLL);
+    if (live) {
+      const int a = d.e_a[e], b = d.e_b[e];
+      L = d.e_L[e];
+      el = d.e_el[e];
+      R = d.e_R[e];
+      er = d.e_er[e];
+      const bool hasR = R >= 0;
+      kind = hasR ? lag::INTERIOR : (d.e_bc[e] == 2 ? lag::SLIP : lag::TRANSMISSIVE);
+      const double xa[2] = {w.x[2 * a], w.x[2 * a + 1]}, xb[2] = {w.x[2 * b], w.x[2 * b + 1]};
+      const double xan[2] = {w.xn[2 * a], w.xn[2 * a + 1]}, xbn[2] = {w.xn[2 * b], w.xn[2 * b + 1]};
+      const double* trL = w.a.trace + size_t(L) * TS + el * NT;
+      const double* trR = hasR ? w.a.trace + size_t(R) * TS + er * NT : trL;
+      const double* avL = w.a.avg + size_t(L) * T * 4;
+      double Gb[4];
+      const double anL = w.an[L], anR = hasR ? w.an[R] : 1.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        Gb[v] = -w.a.qbar_next[size_t(v) * NE + L] / anL;
+        if (hasR) Gb[v] += w.a.qbar_next[size_t(v) * NE + R] / anR;
+      }
+      double* oL = w.a.tbar + size_t(L) * TS + el * NT;
+      double* oR = hasR ? w.a.tbar + size_t(R) * TS + er * NT : oL;
+      lag::patch_flux_vjp<M>(*tb, P.gamma, xa, xb, xan, xbn, dt, trL, trR, avL, kind, Gb, G, oL, oR, bA, c, c + 2,
+                             c + 4, c + 6, HLL, ln.row, ln.row + 1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) G[v] = ln.sum(G[v]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) c[k] = ln.sum(c[k]);
+    const bool open_edge = live && kind == lag::TRANSMISSIVE;
+    if (__any(open_edge)) {
+#pragma unroll
+      for (int k = 0; k < T * 4; ++k) bA[k] = ln.sum(bA[k]);
+    }
+    if (!live || ln.row != 0) continue;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       w.gslot[(size_t(L) * 3 + el) * 4 + v] = -G[v];
-      if (hasR) w.gslot[(size_t(R) * 3 + er) * 4 + v] = G[v];
+      if (R >= 0) w.gslot[(size_t(R) * 3 + er) * 4 + v] = G[v];
     }
-    if (kind == lag::TRANSMISSIVE) {
+    if (open_edge) {
       double* aL = w.a.abar + size_t(e) * T * 4;
 #pragma unroll
       for (int k = 0; k < T * 4; ++k) aL[k] = bA[k];
@@ -1936,6 +1806,12 @@ int grid_for(long n) {
   return int(b);
 }
 
+// Threads of a launch with nG lanes per edge over n edges (EdgeLanes).
+template <int M>
+long edge_lanes(long n) {
+  return (n + EdgeLanes<M>::SPAN - 1) / EdgeLanes<M>::SPAN * 64;
+}
+
 #define AD_LAUNCH(kern, n, stream, ...)                                                      \
   do {                                                                                       \
     hipLaunchKernelGGL(kern, dim3(grid_for(n)), dim3(TPB), 0, (hipStream_t)(stream),         \
@@ -1949,7 +1825,10 @@ int adjoint_gts(const Dev& d, const Params& p, const AdjWork& w, double dt, bool
   if (from_ctx) AD_LAUNCH(k_adj_state<M>, d.NE, s, d, w);
   AD_LAUNCH((k_adj_recon<M, false>), 8L * d.NE, s, d, d.tab, p, w, LtsWork{});
   AD_LAUNCH(k_adj_pred_fwd<M>, d.NE, s, d, d.tab, p, w, dt);
-  AD_LAUNCH(k_adj_patch<M>, d.NF, s, d, d.tab, p, w, dt);
+  if (p.flux == ADER_FLUX_HLL)
+    AD_LAUNCH((k_adj_patch<M, true>), edge_lanes<M>(d.NF), s, d, d.tab, p, w, dt);
+  else
+    AD_LAUNCH((k_adj_patch<M, false>), edge_lanes<M>(d.NF), s, d, d.tab, p, w, dt);
   AD_LAUNCH(k_adj_pred_rev<M>, d.NE, s, d, d.tab, p, w, dt);
   AD_LAUNCH((k_adj_recon<M, true>), 8L * d.NE, s, d, d.tab, p, w, LtsWork{});
   AD_LAUNCH(k_adj_gather<M>, 8L * d.NE, s, d, w);
@@ -1974,7 +1853,10 @@ int adjoint_lagrangian(const Dev& d, const Params& p, LagWork w, double dt, bool
   AD_LAUNCH_BLOCKS(k_lag_pred_fwd<M>, pb, s, d, d.tab, p, w, dt, LtsWork{});
   AD_LAUNCH(k_lag_node_fwd<M>, d.NV, s, d, d.tab, w, dt);
   AD_LAUNCH(k_lag_area_new<M>, d.NE, s, d, w);
-  AD_LAUNCH(k_lag_patch<M>, d.NF, s, d, d.tab, p, w, dt);
+  if (p.flux == ADER_FLUX_HLL)
+    AD_LAUNCH((k_lag_patch<M, true>), edge_lanes<M>(d.NF), s, d, d.tab, p, w, dt);
+  else
+    AD_LAUNCH((k_lag_patch<M, false>), edge_lanes<M>(d.NF), s, d, d.tab, p, w, dt);
   AD_LAUNCH(k_lag_update_rev<M>, d.NE, s, d, w);
   AD_LAUNCH(k_lag_node_rev<M>, d.NV, s, d, d.tab, w, dt);
   AD_LAUNCH_BLOCKS(k_lag_pred_rev<M>, pb, s, d, d.tab, p, w, dt, LtsWork{});
@@ -2188,53 +2070,68 @@ __global__ void __launch_bounds__(TPB) k_lts_update_rev(Dev d, LtsWork lw) {
   }
 }
 
-// Swept patches in reverse, one lane per edge with a moved node: the flux's
+// Swept patches in reverse, nG lanes per edge with a moved node: the flux's
 // adjoint is that of the memory variables it was added to (inflow positive
 // into R, outflow from L); onto both sides' traces (added), the inner mean
 // (transmissive, per edge) and the four corners (per edge).
-template <int M>
+template <int M, bool HLL>
 __global__ void __launch_bounds__(TPB) k_lts_patch(Dev d, const Tables* __restrict__ tb, Params P, LtsWork lw) {
   using S = AZ<M>;
   constexpr int T = S::T, nG = S::nG, TS = S::TS, NT = nG * T * 4;
   const int NV = d.NV, n_e = lw.counts[2];
-  for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n_e; idx += gridDim.x * blockDim.x) {
-    const int e = lw.edge_list[idx];
-    const int a = d.e_a[e], b = d.e_b[e];
-    const bool ma = lw.nflag[a] != 0, mvb = lw.nflag[b] != 0;
-    const double* X0 = lw.s0.X;
-    const double* X1 = lw.s1.X;
-    const double xa[2] = {X0[a], X0[NV + a]}, xb[2] = {X0[b], X0[NV + b]};
-    const double xan[2] = {ma ? X1[a] : xa[0], ma ? X1[NV + a] : xa[1]};
-    const double xbn[2] = {mvb ? X1[b] : xb[0], mvb ? X1[NV + b] : xb[1]};
-    const int L = d.e_L[e], el = d.e_el[e], R = d.e_R[e], er = d.e_er[e];
-    const bool hasR = R >= 0;
-    const int kind = hasR ? lag::INTERIOR : (d.e_bc[e] == 2 ? lag::SLIP : lag::TRANSMISSIVE);
-    lag::PatchTimes pt;
-    pt.tk[0] = double(lw.s0.ntick[a]);
-    pt.tk[1] = double(lw.s0.ntick[b]);
-    pt.tk[2] = double(lw.s1.ntick[b]);
-    pt.tk[3] = double(lw.s1.ntick[a]);
-    const TickStep tL = lw.s0.ts[L];
-    const TickStep tR = hasR ? lw.s0.ts[R] : tL;
-    pt.nL = double(tL.tick);
-    pt.sL = double(tL.step);
-    pt.nR = double(tR.tick);
-    pt.sR = double(tR.step);
-    pt.delta = lw.delta;
-    const double* trL = lw.s0.trace + size_t(L) * TS + el * NT;
-    const double* trR = hasR ? lw.s0.trace + size_t(R) * TS + er * NT : trL;
-    const double* avL = lw.s0.rec + size_t(L) * S::RS + rec_off_avg();
-    double Gb[4], G[4] = {0.0, 0.0, 0.0, 0.0}, bA[T * 4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Gb[v] = -lw.mb[size_t(L) * 4 + v] + (hasR ? lw.mb[size_t(R) * 4 + v] : 0.0);
+  const EdgeLanes<M> ln;
+  for (int base = ln.base(); base < n_e; base += ln.stride()) {
+    const int idx = base + ln.edge();
+    const bool live = ln.use && idx < n_e;
+    int e = 0, kind = lag::INTERIOR;
+    double bA[T * 4];
 #pragma unroll
     for (int k = 0; k < T * 4; ++k) bA[k] = 0.0;
     double c[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double* oL = lw.g.a.tbar + size_t(L) * TS + el * NT;
-    double* oR = hasR ? lw.g.a.tbar + size_t(R) * TS + er * NT : oL;
-    lag::patch_flux_vjp_lts<M>(*tb, P.gamma, xa, xb, xan, xbn, pt, trL, trR, avL, kind, Gb, G, oL, oR, bA, c,
-                               c + 2, c + 4, c + 6, P.flux == ADER_FLUX_HLL);
-    if (kind == lag::TRANSMISSIVE) {
+    if (live) {
+      e = lw.edge_list[idx];
+      const int a = d.e_a[e], b = d.e_b[e];
+      const bool ma = lw.nflag[a] != 0, mvb = lw.nflag[b] != 0;
+      const double* X0 = lw.s0.X;
+      const double* X1 = lw.s1.X;
+      const double xa[2] = {X0[a], X0[NV + a]}, xb[2] = {X0[b], X0[NV + b]};
+      const double xan[2] = {ma ? X1[a] : xa[0], ma ? X1[NV + a] : xa[1]};
+      const double xbn[2] = {mvb ? X1[b] : xb[0], mvb ? X1[NV + b] : xb[1]};
+      const int L = d.e_L[e], el = d.e_el[e], R = d.e_R[e], er = d.e_er[e];
+      const bool hasR = R >= 0;
+      kind = hasR ? lag::INTERIOR : (d.e_bc[e] == 2 ? lag::SLIP : lag::TRANSMISSIVE);
+      lag::PatchTimes pt;
+      pt.tk[0] = double(lw.s0.ntick[a]);
+      pt.tk[1] = double(lw.s0.ntick[b]);
+      pt.tk[2] = double(lw.s1.ntick[b]);
+      pt.tk[3] = double(lw.s1.ntick[a]);
+      const TickStep tL = lw.s0.ts[L];
+      const TickStep tR = hasR ? lw.s0.ts[R] : tL;
+      pt.nL = double(tL.tick);
+      pt.sL = double(tL.step);
+      pt.nR = double(tR.tick);
+      pt.sR = double(tR.step);
+      pt.delta = lw.delta;
+      const double* trL = lw.s0.trace + size_t(L) * TS + el * NT;
+      const double* trR = hasR ? lw.s0.trace + size_t(R) * TS + er * NT : trL;
+      const double* avL = lw.s0.rec + size_t(L) * S::RS + rec_off_avg();
+      double Gb[4], G[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Gb[v] = -lw.mb[size_t(L) * 4 + v] + (hasR ? lw.mb[size_t(R) * 4 + v] : 0.0);
+      double* oL = lw.g.a.tbar + size_t(L) * TS + el * NT;
+      double* oR = hasR ? lw.g.a.tbar + size_t(R) * TS + er * NT : oL;
+      lag::patch_flux_vjp_lts<M>(*tb, P.gamma, xa, xb, xan, xbn, pt, trL, trR, avL, kind, Gb, G, oL, oR, bA, c,
+                                 c + 2, c + 4, c + 6, HLL, ln.row, ln.row + 1);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) c[k] = ln.sum(c[k]);
+    const bool open_edge = live && kind == lag::TRANSMISSIVE;
+    if (__any(open_edge)) {
+#pragma unroll
+      for (int k = 0; k < T * 4; ++k) bA[k] = ln.sum(bA[k]);
+    }
+    if (!live || ln.row != 0) continue;
+    if (open_edge) {
       double* aL = lw.abar_e + size_t(e) * T * 4;
 #pragma unroll
       for (int k = 0; k < T * 4; ++k) aL[k] = bA[k];
@@ -2510,7 +2407,10 @@ int lts_cycle_rev(const Dev& d, const Params& p, const LtsWork& w, void* s) {
   if ((r = lts_pred_rev<M>(d, p, w, s))) return r;
   if ((r = lts_recon_rev<M>(d, p, w, s))) return r;
   AD_LAUNCH(k_lts_update_rev<M>, d.NE, s, d, w);
-  AD_LAUNCH(k_lts_patch<M>, d.NF, s, d, d.tab, p, w);
+  if (p.flux == ADER_FLUX_HLL)
+    AD_LAUNCH((k_lts_patch<M, true>), edge_lanes<M>(d.NF), s, d, d.tab, p, w);
+  else
+    AD_LAUNCH((k_lts_patch<M, false>), edge_lanes<M>(d.NF), s, d, d.tab, p, w);
   AD_LAUNCH(k_lts_node_rev<M>, d.NV, s, d, d.tab, w);
   AD_LAUNCH(k_lts_elem<M>, d.NE, s, d, w);
   return 0;

@@ -13,8 +13,11 @@
 
 #if defined(__HIPCC__)
 #define AWHD __host__ __device__
+// a loop kept as a loop: unrolled, a patch's points hold all their values at once
+#define AW_NO_UNROLL _Pragma("unroll 1")
 #else
 #define AWHD
+#define AW_NO_UNROLL
 #endif
 
 namespace aw {
@@ -67,59 +70,96 @@ AWHD inline void tint01(const Tables& tb, double I[M + 1]) {
   }
 }
 
-AWHD inline void euler_f_g(const double q[4], double gam, double f[4], double g[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r, E = q[3];
-  const double p = (gam - 1.0) * (E - 0.5 * r * (u * u + v * v));
-  f[0] = r * u;
-  f[1] = r * u * u + p;
-  f[2] = r * u * v;
-  f[3] = u * (E + p);
-  g[0] = r * v;
-  g[1] = r * u * v;
-  g[2] = r * v * v + p;
-  g[3] = v * (E + p);
+// 1/x to rounding, and 1/sqrt(x). On the device the reciprocal is the hardware's
+// estimate with two Newton steps: a general division also scales its operands
+// against overflow, which the densities, pressures and normals here do not need.
+AWHD inline double rcp(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double r = __builtin_amdgcn_rcp(x);
+  r = r + r * (1.0 - x * r);
+  return r + r * (1.0 - x * r);
+#else
+  return 1.0 / x;
+#endif
+}
+AWHD inline double inv_sqrt(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return rsqrt(x);
+#else
+  return 1.0 / std::sqrt(x);
+#endif
 }
 
-// qb += J_f(q)^T fb + J_g(q)^T gb
+AWHD inline void euler_f_g(const double q[4], double gam, double f[4], double g[4]) {
+  const double ir = rcp(q[0]), u = q[1] * ir, v = q[2] * ir;
+  const double p = (gam - 1.0) * (q[3] - 0.5 * (q[1] * u + q[2] * v));
+  const double H = q[3] + p;
+  f[0] = q[1];
+  f[1] = q[1] * u + p;
+  f[2] = q[1] * v;
+  f[3] = u * H;
+  g[0] = q[2];
+  g[1] = f[2];
+  g[2] = q[2] * v + p;
+  g[3] = v * H;
+}
+
+// qb += J_f(q)^T fb + J_g(q)^T gb, from f = q u + p (0, 1, 0, u) and
+// g = q v + p (0, 0, 1, v): one reciprocal
 AWHD inline void euler_f_g_vjp(const double q[4], double gam, const double fb[4], const double gb[4],
                                double qb[4]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r, E = q[3];
-  const double gm = gam - 1.0;
-  const double p = gm * (E - 0.5 * r * (u * u + v * v));
-  const double H = E + p;
-  double rb = 0.0, ub = 0.0, vb = 0.0, pb = 0.0, Eb = 0.0;
-  rb += fb[0] * u;       ub += fb[0] * r;
-  rb += fb[1] * u * u;   ub += fb[1] * 2.0 * r * u;   pb += fb[1];
-  rb += fb[2] * u * v;   ub += fb[2] * r * v;         vb += fb[2] * r * u;
-  ub += fb[3] * H;       Eb += fb[3] * u;             pb += fb[3] * u;
-  rb += gb[0] * v;       vb += gb[0] * r;
-  rb += gb[1] * u * v;   ub += gb[1] * r * v;         vb += gb[1] * r * u;
-  rb += gb[2] * v * v;   vb += gb[2] * 2.0 * r * v;   pb += gb[2];
-  vb += gb[3] * H;       Eb += gb[3] * v;             pb += gb[3] * v;
-  // p = gm (E - (q1^2 + q2^2) / (2 q0)), u = q1 / q0, v = q2 / q0, r = q0
-  Eb += gm * pb;
-  rb += -gm * 0.5 * (u * u + v * v) * pb;
-  ub += -gm * r * u * pb;
-  vb += -gm * r * v * pb;
-  qb[0] += rb - (ub * u + vb * v) / r;
-  qb[1] += ub / r;
-  qb[2] += vb / r;
-  qb[3] += Eb;
+  const double ir = rcp(q[0]), u = q[1] * ir, v = q[2] * ir, gm = gam - 1.0;
+  const double k = 0.5 * (u * u + v * v);
+  const double p = gm * (q[3] - q[0] * k);
+  const double ub = fb[0] * q[0] + fb[1] * q[1] + fb[2] * q[2] + fb[3] * (q[3] + p);
+  const double vb = gb[0] * q[0] + gb[1] * q[1] + gb[2] * q[2] + gb[3] * (q[3] + p);
+  const double pb = gm * (fb[1] + u * fb[3] + gb[2] + v * gb[3]);
+  qb[0] += fb[0] * u + gb[0] * v - ir * (u * ub + v * vb) + k * pb;
+  qb[1] += fb[1] * u + gb[1] * v + ir * ub - u * pb;
+  qb[2] += fb[2] * u + gb[2] * v + ir * vb - v * pb;
+  qb[3] += fb[3] * u + gb[3] * v + pb;
 }
 
 // ------------------------------------------------------------------------
-// Rusanov flux through an unnormalised space-time normal and its product
+// Rusanov and HLL fluxes through an unnormalised space-time normal N and their
+// products. One side: F~(q) . N = q (U + N_t) + p (0, N_x, N_y, U) with
+// U = u . N_xy, the ALE speed un = U + N_t and the sound speed c.
 // ------------------------------------------------------------------------
-AWHD inline double rus_speed(const double q[4], const double N[3], double gam, double* un_out, double* c_out) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double p = (gam - 1.0) * (q[3] - 0.5 * r * (u * u + v * v));
-  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
-  const double un = u * N[0] + v * N[1] + N[2];
-  const double c = sqrt(gam * p / r);
-  *un_out = un;
-  *c_out = c;
-  return fabs(un) + c * nxy;
-}
+struct FluxSide {
+  double ir, u, v, k, p, U, un, c;
+  AWHD inline FluxSide(const double q[4], const double N[3], double gam) {
+    ir = rcp(q[0]);
+    u = q[1] * ir;
+    v = q[2] * ir;
+    k = 0.5 * (u * u + v * v);
+    p = (gam - 1.0) * (q[3] - q[0] * k);
+    U = u * N[0] + v * N[1];
+    un = U + N[2];
+    c = sqrt(gam * p * ir);
+  }
+  AWHD inline void flux(const double q[4], const double N[3], double F[4]) const {
+    F[0] = q[0] * un;
+    F[1] = q[1] * un + p * N[0];
+    F[2] = q[2] * un + p * N[1];
+    F[3] = q[3] * un + p * U;
+  }
+  // qb, Nb += the product of (w, unb, cnb) with the Jacobian of (F~ . N, un, c |N_xy|)
+  AWHD inline void vjp(const double q[4], const double N[3], double nxy, double inxy, double gam, const double w[4],
+                       double unb, double cnb, double qb[4], double Nb[3]) const {
+    const double wq = w[0] * q[0] + w[1] * q[1] + w[2] * q[2] + w[3] * q[3];
+    const double Ub = wq + p * w[3] + unb, gm = gam - 1.0;
+    const double ch = 0.5 * cnb * nxy;   // half the adjoint of c = sqrt(gam p / rho)
+    const double pb = gm * (w[1] * N[0] + w[2] * N[1] + w[3] * U + (ch != 0.0 ? ch * gam * ir * rcp(c) : 0.0));
+    qb[0] += w[0] * un - U * ir * Ub + k * pb - ch * c * ir;
+    qb[1] += w[1] * un + N[0] * ir * Ub - u * pb;
+    qb[2] += w[2] * un + N[1] * ir * Ub - v * pb;
+    qb[3] += w[3] * un + pb;
+    const double cn = cnb * c * inxy;
+    Nb[0] += u * Ub + p * w[1] + cn * N[0];
+    Nb[1] += v * Ub + p * w[2] + cn * N[1];
+    Nb[2] += wq + unb;
+  }
+};
 
 // qlb, qrb, Nb += the product of Fb with the Rusanov flux's Jacobian (the
 // larger signal speed taken from the left state on ties, d|x|/dx = 0 at 0);
@@ -127,149 +167,65 @@ AWHD inline double rus_speed(const double q[4], const double N[3], double gam, d
 AWHD inline void rusanov_flux_vjp(const double ql[4], const double qr[4], const double N[3], double gam,
                                   const double Fb[4], double qlb[4], double qrb[4], double Nb[3],
                                   double* F = nullptr) {
-  double fl[4], gl[4], fr[4], gr[4], unl, cl, unr, cr;
-  euler_f_g(ql, gam, fl, gl);
-  euler_f_g(qr, gam, fr, gr);
-  const double sl = rus_speed(ql, N, gam, &unl, &cl), sr = rus_speed(qr, N, gam, &unr, &cr);
+  const double nn = N[0] * N[0] + N[1] * N[1], inxy = inv_sqrt(nn), nxy = sqrt(nn);
+  const FluxSide l(ql, N, gam), r(qr, N, gam);
+  const double sl = fabs(l.un) + l.c * nxy, sr = fabs(r.un) + r.c * nxy;
   const bool left = sl >= sr;
   const double s = left ? sl : sr;
-  if (F)
-    for (int v = 0; v < 4; ++v)
-      F[v] = 0.5 * ((fl[v] + fr[v]) * N[0] + (gl[v] + gr[v]) * N[1] + (ql[v] + qr[v]) * N[2]) -
-             0.5 * s * (qr[v] - ql[v]);
-  double fb[4], gb[4], sb = 0.0;
-  for (int v = 0; v < 4; ++v) {
-    fb[v] = 0.5 * N[0] * Fb[v];
-    gb[v] = 0.5 * N[1] * Fb[v];
-    qlb[v] += 0.5 * N[2] * Fb[v] + 0.5 * s * Fb[v];
-    qrb[v] += 0.5 * N[2] * Fb[v] - 0.5 * s * Fb[v];
-    sb -= 0.5 * Fb[v] * (qr[v] - ql[v]);
-    Nb[0] += 0.5 * Fb[v] * (fl[v] + fr[v]);
-    Nb[1] += 0.5 * Fb[v] * (gl[v] + gr[v]);
-    Nb[2] += 0.5 * Fb[v] * (ql[v] + qr[v]);
+  if (F) {
+    double fl[4], fr[4];
+    l.flux(ql, N, fl);
+    r.flux(qr, N, fr);
+    for (int v = 0; v < 4; ++v) F[v] = 0.5 * (fl[v] + fr[v]) - 0.5 * s * (qr[v] - ql[v]);
   }
-  euler_f_g_vjp(ql, gam, fb, gb, qlb);
-  euler_f_g_vjp(qr, gam, fb, gb, qrb);
-  // s = |u N0 + v N1 + N2| + c |N_xy| of the state that gives the maximum
-  const double* q = left ? ql : qr;
-  double* qsb = left ? qlb : qrb;
-  const double un = left ? unl : unr, c = left ? cl : cr;
-  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
-  const double sg = un > 0.0 ? 1.0 : (un < 0.0 ? -1.0 : 0.0);
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  Nb[0] += sb * (sg * u + c * N[0] / nxy);
-  Nb[1] += sb * (sg * v + c * N[1] / nxy);
-  Nb[2] += sb * sg;
-  // through u, v and c = sqrt(gam p / r)
-  const double gm = gam - 1.0;
-  const double ub = sb * sg * N[0], vb = sb * sg * N[1];
-  const double cb = sb * nxy;
-  const double p = gm * (q[3] - 0.5 * r * (u * u + v * v));
-  double rb = -cb * c / (2.0 * r), pb = cb * gam / (2.0 * c * r);
-  double ubb = ub - gm * r * u * pb, vbb = vb - gm * r * v * pb;
-  rb += -gm * 0.5 * (u * u + v * v) * pb;
-  (void)p;
-  qsb[0] += rb - (ubb * u + vbb * v) / r;
-  qsb[1] += ubb / r;
-  qsb[2] += vbb / r;
-  qsb[3] += gm * pb;
-}
-
-// ------------------------------------------------------------------------
-// HLL flux through an unnormalised space-time normal and its product
-// ------------------------------------------------------------------------
-// F~(q) . N = f N_x + g N_y + q N_t; its product: qb += J^T fb, Nb += (f . fb, g . fb, q . fb)
-AWHD inline void ft_dot(const double q[4], const double N[3], double gam, double out[4]) {
-  double f[4], g[4];
-  euler_f_g(q, gam, f, g);
-  for (int v = 0; v < 4; ++v) out[v] = f[v] * N[0] + g[v] * N[1] + q[v] * N[2];
-}
-
-AWHD inline void ft_dot_vjp(const double q[4], const double N[3], double gam, const double ob[4], double qb[4],
-                            double Nb[3]) {
-  double f[4], g[4], fb[4], gb[4];
-  euler_f_g(q, gam, f, g);
+  double w[4], sb = 0.0;
   for (int v = 0; v < 4; ++v) {
-    fb[v] = N[0] * ob[v];
-    gb[v] = N[1] * ob[v];
-    qb[v] += N[2] * ob[v];
-    Nb[0] += f[v] * ob[v];
-    Nb[1] += g[v] * ob[v];
-    Nb[2] += q[v] * ob[v];
+    w[v] = 0.5 * Fb[v];
+    qlb[v] += s * w[v];
+    qrb[v] -= s * w[v];
+    sb -= w[v] * (qr[v] - ql[v]);
   }
-  euler_f_g_vjp(q, gam, fb, gb, qb);
-}
-
-// u . N_xy + N_t + sgn c |N_xy| and its product with sb onto q and N
-AWHD inline double hll_speed(const double q[4], const double N[3], double gam, double sgn) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double p = (gam - 1.0) * (q[3] - 0.5 * r * (u * u + v * v));
-  return u * N[0] + v * N[1] + N[2] + sgn * sqrt(gam * p / r) * sqrt(N[0] * N[0] + N[1] * N[1]);
-}
-
-AWHD inline void hll_speed_vjp(const double q[4], const double N[3], double gam, double sgn, double sb, double qb[4],
-                               double Nb[3]) {
-  const double r = q[0], u = q[1] / r, v = q[2] / r;
-  const double gm = gam - 1.0;
-  const double p = gm * (q[3] - 0.5 * r * (u * u + v * v));
-  const double c = sqrt(gam * p / r);
-  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
-  Nb[0] += sb * (u + sgn * c * N[0] / nxy);
-  Nb[1] += sb * (v + sgn * c * N[1] / nxy);
-  Nb[2] += sb;
-  // through u, v and c = sqrt(gam p / r)
-  const double cb = sgn * sb * nxy;
-  double rb = -cb * c / (2.0 * r), pb = cb * gam / (2.0 * c * r);
-  const double ub = sb * N[0] - gm * r * u * pb, vb = sb * N[1] - gm * r * v * pb;
-  rb += -gm * 0.5 * (u * u + v * v) * pb;
-  qb[0] += rb - (ub * u + vb * v) / r;
-  qb[1] += ub / r;
-  qb[2] += vb / r;
-  qb[3] += gm * pb;
+  // s = |un| + c |N_xy| of the state that gives the maximum
+  const double un = left ? l.un : r.un;
+  const double unb = un > 0.0 ? sb : (un < 0.0 ? -sb : 0.0);
+  l.vjp(ql, N, nxy, inxy, gam, w, left ? unb : 0.0, left ? sb : 0.0, qlb, Nb);
+  r.vjp(qr, N, nxy, inxy, gam, w, left ? 0.0 : unb, left ? 0.0 : sb, qrb, Nb);
 }
 
 // qlb, qrb, Nb += the product of Fb with the HLL flux's Jacobian: signal
-// speeds bounded over both states (the left state's speed on ties), upwind
-// when both have one sign, else (sr F(ql) - sl F(qr) + sl sr (qr - ql)) /
-// (sr - sl); the flux itself into F when F is not null.
+// speeds un -/+ c |N_xy| bounded over both states (the left state's speed on
+// ties), upwind when both have one sign, else (sr F(ql) - sl F(qr) +
+// sl sr (qr - ql)) / (sr - sl); the flux itself into F when F is not null.
 AWHD inline void hll_flux_vjp(const double ql[4], const double qr[4], const double N[3], double gam,
                               const double Fb[4], double qlb[4], double qrb[4], double Nb[3], double* F = nullptr) {
-  const double l1 = hll_speed(ql, N, gam, -1.0), r1 = hll_speed(ql, N, gam, 1.0);
-  const double l2 = hll_speed(qr, N, gam, -1.0), r2 = hll_speed(qr, N, gam, 1.0);
-  const bool left_lo = l1 <= l2, left_hi = r1 >= r2;
-  const double sl = left_lo ? l1 : l2, sr = left_hi ? r1 : r2;
+  const double nn = N[0] * N[0] + N[1] * N[1], inxy = inv_sqrt(nn), nxy = sqrt(nn);
+  const FluxSide l(ql, N, gam), r(qr, N, gam);
+  const double cl = l.c * nxy, cr = r.c * nxy;
+  const bool left_lo = l.un - cl <= r.un - cr, left_hi = l.un + cl >= r.un + cr;
+  const double sl = left_lo ? l.un - cl : r.un - cr, sr = left_hi ? l.un + cl : r.un + cr;
   double fl[4], fr[4];
-  ft_dot(ql, N, gam, fl);
-  ft_dot(qr, N, gam, fr);
-  if (sl >= 0.0) {
-    if (F)
-      for (int v = 0; v < 4; ++v) F[v] = fl[v];
-    ft_dot_vjp(ql, N, gam, Fb, qlb, Nb);
-    return;
-  }
-  if (sr <= 0.0) {
-    if (F)
-      for (int v = 0; v < 4; ++v) F[v] = fr[v];
-    ft_dot_vjp(qr, N, gam, Fb, qrb, Nb);
-    return;
-  }
-  const double id = 1.0 / (sr - sl);
+  l.flux(ql, N, fl);
+  r.flux(qr, N, fr);
+  const bool up_l = sl >= 0.0, up_r = !up_l && sr <= 0.0;
+  const double id = up_l || up_r ? 0.0 : rcp(sr - sl);
+  // weights of F(ql), F(qr) and qr - ql
+  const double wl = up_l ? 1.0 : up_r ? 0.0 : sr * id, wr = up_l ? 0.0 : up_r ? 1.0 : -sl * id, wd = sl * sr * id;
   double flb[4], frb[4], slb = 0.0, srb = 0.0;
   for (int v = 0; v < 4; ++v) {
     const double d = qr[v] - ql[v];
-    const double Fv = (sr * fl[v] - sl * fr[v] + sl * sr * d) * id;
+    const double Fv = wl * fl[v] + wr * fr[v] + wd * d;
     if (F) F[v] = Fv;
-    flb[v] = sr * id * Fb[v];
-    frb[v] = -sl * id * Fb[v];
-    qrb[v] += sl * sr * id * Fb[v];
-    qlb[v] -= sl * sr * id * Fb[v];
+    flb[v] = wl * Fb[v];
+    frb[v] = wr * Fb[v];
+    qrb[v] += wd * Fb[v];
+    qlb[v] -= wd * Fb[v];
     srb += Fb[v] * (fl[v] + sl * d - Fv) * id;
     slb += Fb[v] * (-fr[v] + sr * d + Fv) * id;
   }
-  ft_dot_vjp(ql, N, gam, flb, qlb, Nb);
-  ft_dot_vjp(qr, N, gam, frb, qrb, Nb);
-  hll_speed_vjp(left_lo ? ql : qr, N, gam, -1.0, slb, left_lo ? qlb : qrb, Nb);
-  hll_speed_vjp(left_hi ? ql : qr, N, gam, 1.0, srb, left_hi ? qlb : qrb, Nb);
+  // lo = un - c |N_xy|, hi = un + c |N_xy|
+  const double ll = left_lo ? slb : 0.0, lh = left_hi ? srb : 0.0, rl = left_lo ? 0.0 : slb, rh = left_hi ? 0.0 : srb;
+  l.vjp(ql, N, nxy, inxy, gam, flb, ll + lh, lh - ll, qlb, Nb);
+  r.vjp(qr, N, nxy, inxy, gam, frb, rl + rh, rh - rl, qrb, Nb);
 }
 
 // ------------------------------------------------------------------------
@@ -284,7 +240,7 @@ enum { INTERIOR = 0, TRANSMISSIVE = 1, SLIP = 2 };
 
 // q with the momentum reflected about the unit normal of N's space part
 AWHD inline void mirror(const double q[4], const double N[3], double out[4]) {
-  const double inxy = 1.0 / sqrt(N[0] * N[0] + N[1] * N[1]);
+  const double inxy = inv_sqrt(N[0] * N[0] + N[1] * N[1]);
   const double nx = N[0] * inxy, ny = N[1] * inxy;
   const double mn = q[1] * nx + q[2] * ny;
   out[0] = q[0];
@@ -295,8 +251,8 @@ AWHD inline void mirror(const double q[4], const double N[3], double out[4]) {
 
 // qb, Nb += the product of ob with mirror's Jacobian
 AWHD inline void mirror_vjp(const double q[4], const double N[3], const double ob[4], double qb[4], double Nb[3]) {
-  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
-  const double nx = N[0] / nxy, ny = N[1] / nxy;
+  const double inxy = inv_sqrt(N[0] * N[0] + N[1] * N[1]);
+  const double nx = N[0] * inxy, ny = N[1] * inxy;
   const double mn = q[1] * nx + q[2] * ny, mb = ob[1] * nx + ob[2] * ny;
   qb[0] += ob[0];
   qb[1] += ob[1] - 2.0 * mb * nx;
@@ -305,8 +261,8 @@ AWHD inline void mirror_vjp(const double q[4], const double N[3], const double o
   // n = N_xy / |N_xy|: nbar = -2 (mb q_m + mn ob_m), projected off n
   const double bx = -2.0 * (mb * q[1] + mn * ob[1]), by = -2.0 * (mb * q[2] + mn * ob[2]);
   const double bn = bx * nx + by * ny;
-  Nb[0] += (bx - bn * nx) / nxy;
-  Nb[1] += (by - bn * ny) / nxy;
+  Nb[0] += (bx - bn * nx) * inxy;
+  Nb[1] += (by - bn * ny) * inxy;
 }
 template <int M>
 AWHD inline void patch_corners(const double xa[2], const double xb[2], const double xan[2], const double xbn[2],
@@ -351,18 +307,22 @@ AWHD inline void patch_states(const double* trL, const double* trR, const double
 // The flux through the patch, G (added to; Rusanov, or HLL when hll), and the
 // products of Gb with its Jacobian: the rows of the trace adjoints trLb and (interior) trRb are
 // written, the means' adjoint avLb (transmissive) and the four corner nodes'
-// adjoints (xab, xbb, xanb, xbnb: x, y) are added to.
+// adjoints (xab, xbb, xanb, xbnb: x, y) are added to. Gauss rows row0 .. row1 - 1
+// along the edge only (all of them by default): the products of the whole edge
+// are the sums over its rows.
 template <int M>
 AWHD inline void patch_flux_vjp(const Tables& tb, double gam, const double xa[2], const double xb[2],
                                 const double xan[2], const double xbn[2], double dt, const double* trL,
                                 const double* trR, const double* avL, int kind, const double Gb[4], double G[4],
                                 double* trLb, double* trRb, double* avLb, double xab[2], double xbb[2],
-                                double xanb[2], double xbnb[2], bool hll = false) {
+                                double xanb[2], double xbnb[2], bool hll = false, int row0 = 0, int row1 = M + 1) {
   constexpr int T = M + 1, nG = M + 1;
   double P[4][3], Pb[4][3] = {};
   patch_corners<M>(xa, xb, xan, xbn, dt, P);
-  for (int gq = 0; gq < nG; ++gq) {
+  AW_NO_UNROLL
+  for (int gq = row0; gq < row1; ++gq) {
     double rl[T][4] = {}, rr[T][4] = {};
+    AW_NO_UNROLL
     for (int h = 0; h < nG; ++h) {
       double N[3], lt[M + 1], dc[3], dtau[3], ql[4], qr[4];
       patch_point<M>(tb, gq, h, P, N, lt, dc, dtau);
@@ -379,8 +339,7 @@ AWHD inline void patch_flux_vjp(const Tables& tb, double gam, const double xa[2]
       for (int s = 0; s < T; ++s)
         for (int v = 0; v < 4; ++v) {
           rl[s][v] += lt[s] * qlb[v];
-          if (kind == INTERIOR) rr[s][v] += lt[s] * qrb[v];
-          if (kind == TRANSMISSIVE) avLb[s * 4 + v] += lt[s] * qrb[v];
+          rr[s][v] += lt[s] * qrb[v];
         }
       // N = dchi x dtau
       double dcb[3], dtb[3];
@@ -402,6 +361,7 @@ AWHD inline void patch_flux_vjp(const Tables& tb, double gam, const double xa[2]
       for (int v = 0; v < 4; ++v) {
         trLb[(gq * T + s) * 4 + v] = rl[s][v];
         if (kind == INTERIOR) trRb[((nG - 1 - gq) * T + s) * 4 + v] = rr[s][v];
+        if (kind == TRANSMISSIVE) avLb[s * 4 + v] += rr[s][v];
       }
   }
   for (int c = 0; c < 2; ++c) {
@@ -429,15 +389,18 @@ AWHD inline void patch_flux_vjp_lts(const Tables& tb, double gam, const double x
                                     const double xan[2], const double xbn[2], const PatchTimes& pt,
                                     const double* trL, const double* trR, const double* avL, int kind,
                                     const double Gb[4], double G[4], double* trLb, double* trRb, double* avLb,
-                                    double xab[2], double xbb[2], double xanb[2], double xbnb[2], bool hll) {
+                                    double xab[2], double xbb[2], double xanb[2], double xbnb[2], bool hll, int row0 = 0,
+                                    int row1 = M + 1) {
   constexpr int T = M + 1, nG = M + 1;
   double P[4][3], Pb[4][3] = {};
   P[0][0] = xa[0];  P[0][1] = xa[1];  P[0][2] = pt.tk[0] * pt.delta;
   P[1][0] = xb[0];  P[1][1] = xb[1];  P[1][2] = pt.tk[1] * pt.delta;
   P[2][0] = xbn[0]; P[2][1] = xbn[1]; P[2][2] = pt.tk[2] * pt.delta;
   P[3][0] = xan[0]; P[3][1] = xan[1]; P[3][2] = pt.tk[3] * pt.delta;
-  for (int gq = 0; gq < nG; ++gq) {
+  AW_NO_UNROLL
+  for (int gq = row0; gq < row1; ++gq) {
     double rl[T][4] = {}, rr[T][4] = {};
+    AW_NO_UNROLL
     for (int h = 0; h < nG; ++h) {
       double N[3], lt[M + 1], dc[3], dtau[3], ql[4], qr[4];
       patch_point<M>(tb, gq, h, P, N, lt, dc, dtau);
@@ -470,8 +433,7 @@ AWHD inline void patch_flux_vjp_lts(const Tables& tb, double gam, const double x
       for (int s = 0; s < T; ++s)
         for (int v = 0; v < 4; ++v) {
           rl[s][v] += lL[s] * qlb[v];
-          if (kind == INTERIOR) rr[s][v] += lR[s] * qrb[v];
-          if (kind == TRANSMISSIVE) avLb[s * 4 + v] += lL[s] * qrb[v];
+          rr[s][v] += (kind == INTERIOR ? lR[s] : lL[s]) * qrb[v];
         }
       double dcb[3], dtb[3];
       dcb[0] = dtau[1] * Nb[2] - dtau[2] * Nb[1];
@@ -491,6 +453,7 @@ AWHD inline void patch_flux_vjp_lts(const Tables& tb, double gam, const double x
       for (int v = 0; v < 4; ++v) {
         trLb[(gq * T + s) * 4 + v] += rl[s][v];
         if (kind == INTERIOR) trRb[((nG - 1 - gq) * T + s) * 4 + v] += rr[s][v];
+        if (kind == TRANSMISSIVE) avLb[s * 4 + v] += rr[s][v];
       }
   }
   for (int c = 0; c < 2; ++c) {
