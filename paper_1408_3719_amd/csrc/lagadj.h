@@ -238,10 +238,12 @@ AWHD inline void hll_flux_vjp(const double ql[4], const double qr[4], const doub
 // ------------------------------------------------------------------------
 enum { INTERIOR = 0, TRANSMISSIVE = 1, SLIP = 2 };
 
-// q with the momentum reflected about the unit normal of N's space part
+// q with the momentum reflected about the unit normal of N's space part. A
+// general division: on a wall along an axis the normal is then exactly +-1, both
+// sides' signal speeds tie exactly and the tie goes to the left state.
 AWHD inline void mirror(const double q[4], const double N[3], double out[4]) {
-  const double inxy = inv_sqrt(N[0] * N[0] + N[1] * N[1]);
-  const double nx = N[0] * inxy, ny = N[1] * inxy;
+  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
+  const double nx = N[0] / nxy, ny = N[1] / nxy;
   const double mn = q[1] * nx + q[2] * ny;
   out[0] = q[0];
   out[1] = q[1] - 2.0 * mn * nx;
@@ -251,8 +253,8 @@ AWHD inline void mirror(const double q[4], const double N[3], double out[4]) {
 
 // qb, Nb += the product of ob with mirror's Jacobian
 AWHD inline void mirror_vjp(const double q[4], const double N[3], const double ob[4], double qb[4], double Nb[3]) {
-  const double inxy = inv_sqrt(N[0] * N[0] + N[1] * N[1]);
-  const double nx = N[0] * inxy, ny = N[1] * inxy;
+  const double nxy = sqrt(N[0] * N[0] + N[1] * N[1]);
+  const double nx = N[0] / nxy, ny = N[1] / nxy;
   const double mn = q[1] * nx + q[2] * ny, mb = ob[1] * nx + ob[2] * ny;
   qb[0] += ob[0];
   qb[1] += ob[1] - 2.0 * mb * nx;
@@ -261,8 +263,8 @@ AWHD inline void mirror_vjp(const double q[4], const double N[3], const double o
   // n = N_xy / |N_xy|: nbar = -2 (mb q_m + mn ob_m), projected off n
   const double bx = -2.0 * (mb * q[1] + mn * ob[1]), by = -2.0 * (mb * q[2] + mn * ob[2]);
   const double bn = bx * nx + by * ny;
-  Nb[0] += (bx - bn * nx) * inxy;
-  Nb[1] += (by - bn * ny) * inxy;
+  Nb[0] += (bx - bn * nx) / nxy;
+  Nb[1] += (by - bn * ny) / nxy;
 }
 template <int M>
 AWHD inline void patch_corners(const double xa[2], const double xb[2], const double xan[2], const double xbn[2],
