@@ -42,6 +42,12 @@ struct ader_ctx {
   double* delta_buf = nullptr;     // tick-length replay
   int* rec_buf = nullptr;          // schedule record: steps, then positions
   double* rec_delta_buf = nullptr; // schedule record: tick lengths
+  // status report of the device (Scal, then the instances) in pinned host memory;
+  // fresh while nothing has been queued that changes them
+  char* rep = nullptr;
+  int rep_K = 0;
+  bool rep_fresh = false;
+  double prev_delta = 0.0;   // tick length of instance 0 at the report before
   // the library's fixed adjoint scratch on this context's GPU (ader_bind_workspace)
   void* static_work = nullptr;
   size_t static_bytes = 0;
@@ -197,10 +203,20 @@ int timed(ader_ctx* c, int k, hipStream_t st, F launch) {
   return r;
 }
 
+const aw::Scal& rep_scal(const ader_ctx* c) { return *reinterpret_cast<const aw::Scal*>(c->rep); }
+const aw::Inst* rep_inst(const ader_ctx* c) {
+  return reinterpret_cast<const aw::Inst*>(c->rep + aw::report_inst_offset());
+}
+
+// The device's status, written to pinned memory by a kernel of its own (a copy
+// into pageable memory costs a staging copy more).
 int read_scal(ader_ctx* c, aw::Scal& s) {
-  HIPCHK(c, hipMemcpyAsync(&s, c->dev.scal, sizeof(s), hipMemcpyDeviceToHost, c->stream));
+  c->prev_delta = rep_inst(c)[0].delta;
+  LCHK(c, aw::launch_report(c->dev, c->rep, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->prof) flush_events(c);
+  s = rep_scal(c);
+  c->rep_fresh = true;
   return 0;
 }
 
@@ -322,10 +338,44 @@ void set_free(ader_ctx* c, bool free_steps) {
   c->dev.free_steps = free_steps;
 }
 
+// Status at the start of a run, the target time being t_target: as of the last
+// report when that is still fresh (the same test for open instances as the
+// device's), else read.
+int run_start(ader_ctx* c, double t_target, aw::Scal& s) {
+  LCHK(c, aw::launch_target(c->dev, t_target, c->stream));
+  if (!c->rep_fresh) return read_scal(c, s);
+  s = rep_scal(c);
+  s.n_open = 0;
+  for (int k = 0; k < c->dev.K; ++k)
+    s.n_open += !(t_target - rep_inst(c)[k].T <= 1e-12 * std::fmax(1.0, std::fabs(t_target)));
+  return 0;
+}
+
+// Global steps queued between two status reads. An idle wait and a report cost
+// ~20 us, a step of a small mesh ~50 us of kernels; a step queued past the
+// target does nothing, but takes its launches.
+constexpr int GTS_BATCH = 8;
+
+// Global steps to queue before the next status read: as many as the last tick
+// length needs to reach the target, at most GTS_BATCH.
+int gts_batch(const ader_ctx* c, double t_target) {
+  const double steps_per = double(aw::MACRO_TICKS);
+  double need = 0.0;
+  for (int k = 0; k < c->dev.K; ++k) {
+    const aw::Inst& in = rep_inst(c)[k];
+    if (!in.open && k > 0) continue;
+    const double delta = k == 0 ? std::fmax(in.delta, c->prev_delta) : in.delta;
+    if (!(delta > 0.0)) return 1;
+    need = std::fmax(need, (t_target - in.T) / (steps_per * delta));
+  }
+  return need >= double(GTS_BATCH) ? GTS_BATCH : std::max(1, int(std::ceil(need)));
+}
+
 // Macro steps of L dyadic levels until t_target; returns 0 or an error code.
 // One host synchronisation per macro step of 2^(L-1) cycles; when some element
 // has not reached the macro-step end by then (it took spare finer steps), more
 // cycles in captured batches of EXTRA_BATCH with a status read after each.
+// Global steps (one level) always end their step and are queued in batches.
 int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
   if (!c->has_state) return fail(c, ADER_E_ORDER, "no state uploaded");
   if (!std::isfinite(t_target)) return fail(c, ADER_E_ARG, "t_target is not finite");
@@ -333,25 +383,35 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
   set_free(c, false);
   const int nominal = 1 << (levels - 1);
   const bool graph = c->graphs && !c->prof;
+  const aw::Dev& d = c->dev;
+  const bool batched = graph && nominal == 1 && !d.replay_steps && !d.replay_delta && !d.rec_steps;
   aw::Scal s;
   int r;
-  LCHK(c, aw::launch_target(c->dev, t_target, c->stream));
-  if ((r = read_scal(c, s))) return r;
-  for (int k = 0; max_macro <= 0 || k < max_macro; ++k) {
+  if ((r = run_start(c, t_target, s))) return r;
+  for (int k = 0; max_macro <= 0 || k < max_macro;) {
     if ((r = check_err(c, s))) return r;
     if (s.n_open == 0) break;      // every instance has reached t_target
+    int queued = 1;
+    if (batched) {
+      queued = gts_batch(c, t_target);
+      if (max_macro > 0) queued = std::min(queued, max_macro - k);
+    }
+    const int index = s.macro_index;
+    c->rep_fresh = false;
     if (graph) {
       if ((r = ensure_graph(c, nominal))) return r;
-      HIPCHK(c, hipGraphLaunch(c->gexec, c->stream));
+      for (int q = 0; q < queued; ++q) HIPCHK(c, hipGraphLaunch(c->gexec, c->stream));
     } else if ((r = issue_macro(c, nominal, c->stream))) {
       return r;
     }
-    c->cycles += nominal;
     if ((r = read_scal(c, s))) return r;
+    const int ended = s.macro_index - index;   // of the queued steps, those that had an open instance
+    c->cycles += nominal * (batched ? ended : 1);
     if ((r = check_err(c, s))) return r;
     if (s.n_unfinished != 0) {
       long long last = (long long)s.updates;
       for (;;) {
+        c->rep_fresh = false;
         if (graph) {
           if (!c->gextra &&
               (r = capture(c, &c->gextra, [&](hipStream_t st) { return issue_cycles(c, EXTRA_BATCH, st, -1); })))
@@ -368,11 +428,13 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
         if ((long long)s.updates == last) return fail(c, ADER_E_DEADLOCK, "no element satisfies the update criterion");
         last = (long long)s.updates;
       }
+      c->rep_fresh = false;
       LCHK(c, aw::launch_macro_end(c->dev, 0, c->stream));
       if ((r = read_scal(c, s))) return r;
       c->long_macro_steps++;
     }
-    c->macro_steps++;
+    c->macro_steps += batched ? ended : 1;
+    k += batched ? std::max(ended, 1) : 1;
   }
   c->synced = true;
   return 0;
@@ -389,11 +451,11 @@ int run_free(ader_ctx* c, double t_target, int max_macro) {
   const bool graph = c->graphs && !c->prof;
   aw::Scal s;
   int r;
-  LCHK(c, aw::launch_target(c->dev, t_target, c->stream));
-  if ((r = read_scal(c, s))) return r;
+  if ((r = run_start(c, t_target, s))) return r;
   for (int k = 0; max_macro <= 0 || k < max_macro; ++k) {
     if ((r = check_err(c, s))) return r;
     if (s.n_open == 0) break;
+    c->rep_fresh = false;
     if ((r = issue_macro_begin(c, 0, c->stream))) return r;
     long long last = -1;
     for (;;) {
@@ -420,11 +482,9 @@ int run_free(ader_ctx* c, double t_target, int max_macro) {
   return 0;
 }
 
+// The instances as of the last read_scal.
 int read_insts(ader_ctx* c, std::vector<aw::Inst>& in) {
-  in.resize(c->dev.K);
-  HIPCHK(c, hipMemcpyAsync(in.data(), c->dev.inst, in.size() * sizeof(aw::Inst), hipMemcpyDeviceToHost,
-                           c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  in.assign(rep_inst(c), rep_inst(c) + c->dev.K);
   return 0;
 }
 
@@ -756,6 +816,20 @@ int ader_bind_workspace(ader_ctx* c, void* dev_ptr, size_t bytes) {
   if ((r = h2d(c, d.e_inst, c->e_inst.data(), NE * sizeof(int)))) return r;
   if ((r = h2d(c, d.v_inst, c->v_inst.data(), NV * sizeof(int)))) return r;
   std::vector<aw::Inst> in0(d.K);
+  for (int k = 0; k < d.K; ++k) {
+    in0[k].min_dt_bits = ~0ull;
+    in0[k].n_elems = c->inst_first[k + 1] - c->inst_first[k];
+  }
+  if (c->rep && c->rep_K != d.K) {
+    HIPCHK(c, hipHostFree(c->rep));
+    c->rep = nullptr;
+  }
+  if (!c->rep) {
+    HIPCHK(c, hipHostMalloc((void**)&c->rep, aw::report_bytes(d.K), hipHostMallocMapped | hipHostMallocCoherent));
+    c->rep_K = d.K;
+  }
+  std::memset(c->rep, 0, aw::report_bytes(d.K));
+  c->rep_fresh = false;
   if ((r = h2d(c, d.inst, in0.data(), in0.size() * sizeof(aw::Inst)))) return r;
   if ((r = h2d(c, d.tri, tri.data(), tri.size() * sizeof(int)))) return r;
   if ((r = h2d(c, d.elem_edges, ee.data(), ee.size() * sizeof(int)))) return r;
@@ -798,43 +872,36 @@ int ader_upload_state_xy(ader_ctx* c, const double* Q_dev, const double* node_xy
   aw::Dev& d = c->dev;
   c->has_state = false;
   c->synced = false;
+  c->rep_fresh = false;
   int r;
   std::vector<double> xy;
-  if (node_xy_dev) {
-    LCHK(c, aw::launch_upload_xy(d, node_xy_dev, c->stream));
-  } else {
+  if (!node_xy_dev) {
     xy = to_soa(t.xy, t.NV, 2);
     if ((r = h2d(c, d.X, xy.data(), xy.size() * sizeof(double)))) return r;
   }
-  aw::Scal s{};
-  s.N = 1;
-  if ((r = h2d(c, d.scal, &s, sizeof(s)))) return r;
-  std::vector<aw::Inst> in(d.K);
-  for (int k = 0; k < d.K; ++k) {
-    in[k].T = t0;
-    in[k].min_dt_bits = ~0ull;
-    in[k].n_elems = c->inst_first[k + 1] - c->inst_first[k];
-  }
-  if ((r = h2d(c, d.inst, in.data(), in.size() * sizeof(aw::Inst)))) return r;
   c->cycles = 0;
   c->macro_steps = 0;
   c->extra_cycles = 0;
   c->long_macro_steps = 0;
-  LCHK(c, aw::launch_init_geometry(d, c->stream));
-  if (node_xy_dev) {
-    // caller positions: refuse inverted elements before any kernel uses them
-    aw::Scal g;
-    if ((r = read_scal(c, g))) return r;
-    if (g.err & aw::ERR_GEOM) return fail(c, ADER_E_GEOM, "node positions give an inverted or degenerate element");
-  }
-  LCHK(c, aw::launch_upload_q(d, Q_dev, c->stream));
-  LCHK(c, aw::launch_check_state(d, c->prm.gamma, c->stream));
+  LCHK(c, aw::launch_upload_begin(d, node_xy_dev, t0, c->stream));
+  LCHK(c, aw::launch_upload_state(d, Q_dev, c->prm.gamma, c->stream));
   LCHK(c, aw::launch_reconstruct(d, c->prm, c->cfg.M, -1, 0, c->stream));
   aw::Scal back;
   if ((r = read_scal(c, back))) return r;
+  if (node_xy_dev && (back.err & aw::ERR_GEOM))
+    return fail(c, ADER_E_GEOM, "node positions give an inverted or degenerate element");
   if (back.err) return fail(c, ADER_E_STATE, "initial state has rho <= 0 or p <= 0");
   c->has_state = true;
   c->synced = true;
+  return ADER_OK;
+}
+
+// Statistics at the end of a run, whose last status read is still fresh.
+static int run_stats(ader_ctx* c, ader_stats* st) {
+  if (!c->rep_fresh) return ader_get_stats(c, st);
+  std::vector<aw::Inst> in;
+  read_insts(c, in);
+  fill_stats(c, rep_scal(c), in, st);
   return ADER_OK;
 }
 
@@ -842,7 +909,7 @@ int ader_step_gts(ader_ctx* c, double t_target, int32_t max_steps, ader_stats* s
   if (!c) return ADER_E_ARG;
   int r = run_macro(c, t_target, max_steps, 1);
   if (r) return r;
-  return st ? ader_get_stats(c, st) : ADER_OK;
+  return st ? run_stats(c, st) : ADER_OK;
 }
 
 int ader_step_lts(ader_ctx* c, double t_target, int32_t max_macro_steps, ader_stats* st) {
@@ -850,7 +917,7 @@ int ader_step_lts(ader_ctx* c, double t_target, int32_t max_macro_steps, ader_st
   int r = c->cfg.lts_levels == 0 ? run_free(c, t_target, max_macro_steps)
                                  : run_macro(c, t_target, max_macro_steps, c->cfg.lts_levels);
   if (r) return r;
-  return st ? ader_get_stats(c, st) : ADER_OK;
+  return st ? run_stats(c, st) : ADER_OK;
 }
 
 int ader_download_state(ader_ctx* c, double* Q_dev, double* node_xy_dev, double* elem_t_dev) {
@@ -937,6 +1004,7 @@ int ader_debug_inject(ader_ctx* c, int32_t what, const void* host, size_t bytes)
     return fail(c, ADER_E_ARG, "memory variables are kept per element edge and cannot be injected");
   Arr a = lookup(c, what);
   if (a.bytes == 0 || bytes != a.bytes) return fail(c, ADER_E_ARG, "size mismatch");
+  c->rep_fresh = false;
   if (what == ADER_DBG_SCAL) {
     aw::Scal s;
     std::vector<aw::Inst> in;
@@ -950,6 +1018,7 @@ int ader_debug_inject(ader_ctx* c, int32_t what, const void* host, size_t bytes)
     s.t_end = v[3];
     if ((r = h2d(c, c->dev.scal, &s, sizeof(s)))) return r;
     if ((r = h2d(c, c->dev.inst, in.data(), sizeof(aw::Inst)))) return r;
+    c->rep_fresh = false;
   } else if (!a.dev) {
     int r = packed_io(c, what, nullptr, host, bytes);
     if (r) return r;
@@ -1042,6 +1111,7 @@ int ader_autotune(ader_ctx* c, int32_t trials, ader_tune* chosen) {
     c->macro_steps = macro;
   };
   auto restore = [&]() -> int {
+    c->rep_fresh = false;
     HIPCHK(c, hipMemcpyAsync(c->ws, snap, c->ws_bytes, hipMemcpyDeviceToDevice, c->stream));
     return 0;
   };
@@ -1357,6 +1427,7 @@ int macro_by_cycles(ader_ctx* c, double t_end, int nominal, F after, int* ran, d
   int r;
   *ran = 0;
   c->synced = false;
+  c->rep_fresh = false;
   set_free(c, nominal == 0);
   LCHK(c, aw::launch_target(d, t_end, c->stream));
   if ((r = read_scal(c, s))) return r;
@@ -1533,6 +1604,7 @@ int ader_adjoint_lts(ader_ctx* c, int32_t n_macro, int32_t keep_macro_steps, dou
   const int r =
       adjoint_lts_run(c, n_macro, keep_macro_steps, t_end, Qbar_dev, Xbar_dev, Qbar0_dev, Xbar0_dev, &done, pool, bufs);
   (void)hipStreamSynchronize(c->stream);
+  c->rep_fresh = false;
   for (char* p : bufs) (void)hipFree(p);
   pool.release();
   if (r) return r;
@@ -1714,6 +1786,7 @@ void ader_destroy(ader_ctx* c) {
   if (c->delta_buf) (void)hipFree(c->delta_buf);
   if (c->rec_buf) (void)hipFree(c->rec_buf);
   if (c->rec_delta_buf) (void)hipFree(c->rec_delta_buf);
+  if (c->rep) (void)hipHostFree(c->rep);
   drop_graphs(c);
   if (c->cap) (void)hipStreamDestroy(c->cap);
   for (int k = 0; k < ADER_K_COUNT; ++k)

@@ -83,7 +83,7 @@ struct Scal {
   unsigned long long n_node;    // node moves
   unsigned long long replay_overrides;   // replayed steps that differ from the level rule's
   int macro_index;  // macro steps ended since the state upload
-  int pad2;
+  int in_step;      // the macro step has open instances (else its kernels do nothing)
 };
 
 static_assert(offsetof(Scal, lists) % 8 == 0, "n_active and n_live must form one aligned 8-byte word");
@@ -311,7 +311,16 @@ int probe_contraction(const Tables* tab, int use_mfma, long n, int iters, const 
 
 // Kernel launchers (kernels.hip).  All launch on `stream`, return a
 // hipError_t as int.
-int launch_init_geometry(const Dev& d, void* stream);
+// State upload: counters and instance times reset (and the node positions
+// taken from xy_in, device [NV][2], unless null); then per element geometry,
+// averages from q_in ([4][NE]) and the check of both.
+int launch_upload_begin(const Dev& d, const double* xy_in, double t0, void* stream);
+int launch_upload_state(const Dev& d, const double* q_in, double gamma, void* stream);
+// Scal and the instances into host memory that the device can write (layout of
+// report_bytes: Scal, then Inst[K]).
+inline size_t report_inst_offset() { return (sizeof(Scal) + 63) & ~size_t(63); }
+inline size_t report_bytes(int K) { return report_inst_offset() + size_t(K) * sizeof(Inst); }
+int launch_report(const Dev& d, void* out, void* stream);
 // list: the set of list lengths (0 or 1) of the cycle, or -1 for every element.
 int launch_reconstruct(const Dev& d, const Params& p, int M, int list, int set_level,
                        void* stream);
@@ -330,10 +339,7 @@ int launch_patch(const Dev& d, const Params& p, int M, void* stream);
 int launch_update(const Dev& d, const Params& p, int list, void* stream);
 int launch_macro_end(const Dev& d, int only_if_done, void* stream);
 int launch_download_xy(const Dev& d, double* out, void* stream);
-int launch_upload_xy(const Dev& d, const double* in, void* stream);
 int launch_download_q(const Dev& d, double* out, void* stream);
-int launch_upload_q(const Dev& d, const double* in, void* stream);
 int launch_elem_times(const Dev& d, double* out, void* stream);
-int launch_check_state(const Dev& d, double gamma, void* stream);
 
 }  // namespace aw

@@ -1470,8 +1470,15 @@ __global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__
     }
     double G[4] = {0, 0, 0, 0}, Nn[3] = {0, 0, 0};
 #pragma unroll 1
-    for (int gq = 0; gq < nG; ++gq)
-      patch_row<M, FLUX>(d, tb, g, gq, C, trL, trR, G, Nn);
+    for (int gq = 0; gq < nG; ++gq) {
+      // row by row, as k_patch_split sums them: the same bits on any mesh size
+      double Gr[4] = {0, 0, 0, 0}, Nr[3] = {0, 0, 0};
+      patch_row<M, FLUX>(d, tb, g, gq, C, trL, trR, Gr, Nr);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) G[v] += Gr[v];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) Nn[k] += Nr[k];
+    }
         // inflow-positive memory variables: the flux leaves L and enters R
 #pragma unroll
     for (int v = 0; v < 4; ++v) sl[v] = mL[v] - G[v];
@@ -1728,13 +1735,14 @@ __device__ inline double macro_delta(const Dev& d, const Inst& in, int N, double
 // records.
 __global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, double dscale) {
   const int n = max(max(d.NE, d.NV), d.K);
+  const bool in_step = d.scal->n_open != 0;   // else the run is over: this macro step does nothing
   if (blockIdx.x == 0) {
     int unfinished = 0;
     for (int k = threadIdx.x; k < d.K; k += TPB) unfinished += d.inst[k].open ? d.inst[k].n_elems : 0;
     unfinished = block_sum(unfinished);
     if (threadIdx.x == 0) {
       d.scal->N = N;
-      d.scal->n_open = 0;             // counted at the macro-step end
+      d.scal->in_step = in_step;
       d.scal->lists[0] = {0, 0};
       d.scal->lists[1] = {0, 0};
       d.scal->n_unfinished = unfinished;
@@ -1743,7 +1751,7 @@ __global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, d
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     if (i < d.K) {
       const double delta = macro_delta(d, d.inst[i], N, fraction, dscale);
-      d.inst[i].delta = delta;
+      if (in_step) d.inst[i].delta = delta;
       if (d.inst[i].open) {
         const int m = d.scal->macro_index;
         if (d.replay_delta && m >= d.replay_delta_n) set_err(d, ERR_REPLAY);
@@ -1789,16 +1797,24 @@ __global__ void __launch_bounds__(TPB) k_macro_end(Dev d, int only_if_done) {
   if (only_if_done && d.scal->n_unfinished != 0) return;
   const int N = d.scal->N;
   const double t_end = d.scal->t_end;
-  if (blockIdx.x == 0 && threadIdx.x == 0) d.scal->macro_index += 1;
-  const int n = max(max(d.NE, d.NV), d.K);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    if (i < d.K) {
-      Inst* in = d.inst + i;
-      const double T = in->T + double(N) * in->delta;
+  if (blockIdx.x == 0) {
+    const bool in_step = d.scal->in_step != 0;
+    int open = 0;
+    for (int k = threadIdx.x; k < d.K; k += TPB) {
+      Inst* in = d.inst + k;
+      const double T = in_step ? in->T + double(N) * in->delta : in->T;
       in->T = T;
       in->open = short_of(T, t_end);
-      if (in->open) atomicAdd(&d.scal->n_open, 1);
+      open += in->open;
     }
+    open = block_sum(open);
+    if (threadIdx.x == 0) {
+      d.scal->n_open = open;
+      if (in_step) d.scal->macro_index += 1;
+    }
+  }
+  const int n = max(d.NE, d.NV);
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     if (i < d.NE) d.ts[i].tick = 0;
     if (i < d.NV) d.ntick[i] = 0;
   }
@@ -1823,46 +1839,71 @@ __global__ void __launch_bounds__(TPB) k_target(Dev d, double t_end) {
 // ---------------------------------------------------------------------------
 // Set-up and I/O
 // ---------------------------------------------------------------------------
-template <int M>
-__global__ void __launch_bounds__(TPB) k_init_geometry(Dev d) {
-  const int NE = d.NE, NV = d.NV, NF = d.NF;
-  const int n = max(max(NE, NV), NF);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    if (i < NE) {
-      double X[6];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int nd = d.tri[k * NE + i];
-        X[2 * k] = d.X[nd];
-        X[2 * k + 1] = d.X[NV + nd];
-      }
-      double* r = d.rec + size_t(i) * Sz<M>::RS;
-#pragma unroll
-      for (int c = 0; c < 6; ++c) r[XE + c] = X[c];
-      r[AO] = tri_area(X);
-      if (!(r[AO] > 0.0)) set_err(d, ERR_GEOM);
-      d.ts[i] = TickStep{0, 0};
-      d.act_stamp[i] = -1;
-#pragma unroll
-      for (int c = 0; c < 3 * MEM_W; ++c) d.mem[size_t(i) * 3 * MEM_W + c] = 0.0;
-      if (d.replay_pos) d.replay_pos[i] = 0;
+__global__ void __launch_bounds__(TPB) k_upload_begin(Dev d, const double* xy, double t0) {
+  if (blockIdx.x == 0) {
+    for (int k = threadIdx.x; k < d.K; k += TPB) {
+      Inst in = d.inst[k];
+      in.T = t0;
+      in.delta = 0.0;
+      in.min_dt_bits = ~0ull;
+      in.open = 0;
+      d.inst[k] = in;
     }
-    if (i < NV) {
-      d.ntick[i] = 0;
-      d.node_stamp[i] = -1;
+    if (threadIdx.x == 0) {
+      Scal s{};
+      s.N = 1;
+      *d.scal = s;
     }
+  }
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.NV; k += gridDim.x * blockDim.x) {
+    if (xy) {
+      d.X[k] = xy[2 * k];
+      d.X[d.NV + k] = xy[2 * k + 1];
+    }
+    d.ntick[k] = 0;
+    d.node_stamp[k] = -1;
   }
 }
 
 template <int M>
-__global__ void __launch_bounds__(TPB) k_check_state(Dev d, double g) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d.NE; i += gridDim.x * blockDim.x) {
-    const double* r = d.rec + size_t(i) * Sz<M>::RS;
+__global__ void __launch_bounds__(TPB) k_upload_state(Dev d, const double* q_in, double g) {
+  const int NE = d.NE, NV = d.NV;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < NE; i += gridDim.x * blockDim.x) {
+    double X[6];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int nd = d.tri[k * NE + i];
+      X[2 * k] = d.X[nd];
+      X[2 * k + 1] = d.X[NV + nd];
+    }
+    double* r = d.rec + size_t(i) * Sz<M>::RS;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) r[XE + c] = X[c];
+    const double A = tri_area(X);
+    r[AO] = A;
+    if (!(A > 0.0)) set_err(d, ERR_GEOM);
     double q[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) q[v] = r[QO + v];
+    for (int v = 0; v < 4; ++v) {
+      q[v] = q_in[size_t(v) * NE + i];
+      r[QO + v] = q[v];
+    }
     if (!(q[0] > 0.0) || !(pressure(q, g) > 0.0)) set_err(d, ERR_STATE);
+    d.ts[i] = TickStep{0, 0};
+    d.act_stamp[i] = -1;
+#pragma unroll
+    for (int c = 0; c < 3 * MEM_W; ++c) d.mem[size_t(i) * 3 * MEM_W + c] = 0.0;
+    if (d.replay_pos) d.replay_pos[i] = 0;
   }
+}
+
+// Scal and the instances, in 8-byte words, to memory of the host.
+__global__ void __launch_bounds__(TPB) k_report(Dev d, unsigned long long* out, int inst_at) {
+  static_assert(sizeof(Scal) % 8 == 0 && sizeof(Inst) % 8 == 0, "copied in 8-byte words");
+  const auto* s = reinterpret_cast<const unsigned long long*>(d.scal);
+  const auto* in = reinterpret_cast<const unsigned long long*>(d.inst);
+  for (int w = threadIdx.x; w < int(sizeof(Scal) / 8); w += TPB) out[w] = s[w];
+  for (int w = threadIdx.x; w < int(sizeof(Inst) / 8) * d.K; w += TPB) out[inst_at + w] = in[w];
 }
 
 template <int M>
@@ -1874,26 +1915,10 @@ __global__ void __launch_bounds__(TPB) k_download_q(Dev d, double* out) {
   }
 }
 
-template <int M>
-__global__ void __launch_bounds__(TPB) k_upload_q(Dev d, const double* in) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d.NE; i += gridDim.x * blockDim.x) {
-    double* r = d.rec + size_t(i) * Sz<M>::RS;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) r[QO + v] = in[size_t(v) * d.NE + i];
-  }
-}
-
 __global__ void __launch_bounds__(TPB) k_download_xy(Dev d, double* out) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.NV; k += gridDim.x * blockDim.x) {
     out[2 * k] = d.X[k];
     out[2 * k + 1] = d.X[d.NV + k];
-  }
-}
-
-__global__ void __launch_bounds__(TPB) k_upload_xy(Dev d, const double* in) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d.NV; k += gridDim.x * blockDim.x) {
-    d.X[k] = in[2 * k];
-    d.X[d.NV + k] = in[2 * k + 1];
   }
 }
 
@@ -1956,10 +1981,18 @@ void set_next_launch_events(void* start, void* stop) {
 }
 bool next_launch_events_pending() { return t_ev_start != nullptr; }
 
-int launch_init_geometry(const Dev& d, void* s) {
-  int n = d.NE > d.NV ? d.NE : d.NV;
-  if (d.NF > n) n = d.NF;
-  AW_DISPATCH(d.M, AW_LAUNCH(k_init_geometry<MM>, n, s, d));
+int launch_upload_begin(const Dev& d, const double* xy_in, double t0, void* s) {
+  AW_LAUNCH(k_upload_begin, d.NV, s, d, xy_in, t0);
+  return 0;
+}
+
+int launch_upload_state(const Dev& d, const double* q_in, double gamma, void* s) {
+  AW_DISPATCH(d.M, AW_LAUNCH(k_upload_state<MM>, d.NE, s, d, q_in, gamma));
+  return 0;
+}
+
+int launch_report(const Dev& d, void* out, void* s) {
+  AW_LAUNCH_G(k_report, 1, s, d, static_cast<unsigned long long*>(out), int(report_inst_offset() / 8));
   return 0;
 }
 
@@ -2077,8 +2110,7 @@ int launch_update(const Dev& d, const Params& p, int list, void* s) {
 }
 
 int launch_macro_end(const Dev& d, int only_if_done, void* s) {
-  long n = d.NE > d.NV ? d.NE : d.NV;
-  if (d.K > n) n = d.K;
+  const long n = std::max(d.NE, d.NV);
   AW_LAUNCH(k_macro_end, n, s, d, only_if_done);
   return 0;
 }
@@ -2088,28 +2120,13 @@ int launch_download_xy(const Dev& d, double* out, void* s) {
   return 0;
 }
 
-int launch_upload_xy(const Dev& d, const double* in, void* s) {
-  AW_LAUNCH(k_upload_xy, d.NV, s, d, in);
-  return 0;
-}
-
 int launch_download_q(const Dev& d, double* out, void* s) {
   AW_DISPATCH(d.M, AW_LAUNCH(k_download_q<MM>, d.NE, s, d, out));
   return 0;
 }
 
-int launch_upload_q(const Dev& d, const double* in, void* s) {
-  AW_DISPATCH(d.M, AW_LAUNCH(k_upload_q<MM>, d.NE, s, d, in));
-  return 0;
-}
-
 int launch_elem_times(const Dev& d, double* out, void* s) {
   AW_LAUNCH(k_elem_times, d.NE, s, d, out);
-  return 0;
-}
-
-int launch_check_state(const Dev& d, double gamma, void* s) {
-  AW_DISPATCH(d.M, AW_LAUNCH(k_check_state<MM>, d.NE, s, d, gamma));
   return 0;
 }
 
