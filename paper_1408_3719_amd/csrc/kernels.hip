@@ -1236,6 +1236,7 @@ __global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk, int list)
 // ---------------------------------------------------------------------------
 // Node solver and node motion
 // ---------------------------------------------------------------------------
+constexpr int RING_U = 8;
 template <int M>
 __global__ void __launch_bounds__(TPB) k_node(Dev d, const Tables* __restrict__ tb, Params P, int list) {
   const int cycle = d.scal->cycle;
@@ -1253,61 +1254,89 @@ __global__ void __launch_bounds__(TPB) k_node(Dev d, const Tables* __restrict__ 
     d.inst[k].min_dt_bits = ~0ull;
   for (int k = xcd_block() * blockDim.x + threadIdx.x; k < NV; k += gridDim.x * blockDim.x) {
     const int r0 = d.ring_ptr[k], r1 = d.ring_ptr[k + 1];
-    int newt = -1;
-    for (int r = r0; r < r1; ++r) {
-      const int j = d.ring_ent[r] >> 2;
-      if (d.act_stamp[j] == cycle) {
-        const TickStep tsj = d.ts[j];
-        newt = tsj.tick + tsj.step;
-        break;
-      }
-    }
     const int nk = d.ntick[k];
+    // The ring is taken RING_U entries at a time, their loads together (rings
+    // rarely have more): entries, then the elements' stamps and ticks, then their
+    // records, three waits instead of three per entry.
+    int ent[RING_U];
+    TickStep te[RING_U];
+    int newt = -1;
+    for (int r = r0; r < r1; r += RING_U) {
+      int st[RING_U];
+#pragma unroll
+      for (int u = 0; u < RING_U; ++u) ent[u] = d.ring_ent[min(r + u, r1 - 1)];
+#pragma unroll
+      for (int u = 0; u < RING_U; ++u) {
+        st[u] = d.act_stamp[ent[u] >> 2];
+        te[u] = d.ts[ent[u] >> 2];
+      }
+      // co-active elements that share a node have one future time
+#pragma unroll
+      for (int u = 0; u < RING_U; ++u)
+        if (st[u] == cycle) newt = te[u].tick + te[u].step;
+    }
     if (newt <= nk) continue;
+    const double xk = d.X[k], yk = d.X[NV + k], nx = d.wall_n[k], ny = d.wall_n[NV + k];
+    const int pin = d.wall_pin[k];
     double mu_sum = 0.0, Vx = 0.0, Vy = 0.0;
     bool ok = true;
-    for (int r = r0; r < r1; ++r) {
-      const int ent = d.ring_ent[r];
-      const int j = ent >> 2, lv = ent & 3;
-      const TickStep tsj = d.ts[j];
-      if (tsj.step <= 0) {
-        ok = false;
-        continue;
-      }
-      const double tau0 = tick_ratio(double(nk - tsj.tick), tsj.step);
-      const double tau1 = tick_ratio(double(newt - tsj.tick), tsj.step);
-      double L0[T], L1[T];
-      time_antideriv<M>(tau0, L0);
-      time_antideriv<M>(tau1, L1);
-      const double* rj = rec<M>(d, j);
-      double vx = 0.0, vy = 0.0;
+    for (int r = r0; r < r1; r += RING_U) {
+      if (r1 - r0 > RING_U) {   // else ent and te still hold the ring
 #pragma unroll
-      for (int q = 0; q < T; ++q) {
-        const double I = L1[q] - L0[q];
-        vx += I * rj[VV + (lv * T + q) * 2 + 0];
-        vy += I * rj[VV + (lv * T + q) * 2 + 1];
+        for (int u = 0; u < RING_U; ++u) ent[u] = d.ring_ent[min(r + u, r1 - 1)];
+#pragma unroll
+        for (int u = 0; u < RING_U; ++u) te[u] = d.ts[ent[u] >> 2];
       }
-      const double inv = 1.0 / (tau1 - tau0);
-      const double mu = rj[QO] * rj[AO];
-      Vx += mu * (vx * inv);
-      Vy += mu * (vy * inv);
-      mu_sum += mu;
+      double vv[RING_U][2 * T], q0[RING_U], ar[RING_U];
+#pragma unroll
+      for (int u = 0; u < RING_U; ++u) {
+        const double* rj = rec<M>(d, ent[u] >> 2);
+        const double* v = rj + VV + (ent[u] & 3) * T * 2;
+        q0[u] = rj[QO];
+        ar[u] = rj[AO];
+#pragma unroll
+        for (int c = 0; c < 2 * T; ++c) vv[u][c] = v[c];
+      }
+#pragma unroll
+      for (int u = 0; u < RING_U; ++u) {
+        if (r + u >= r1) continue;
+        if (te[u].step <= 0) {
+          ok = false;
+          continue;
+        }
+        const double tau0 = tick_ratio(double(nk - te[u].tick), te[u].step);
+        const double tau1 = tick_ratio(double(newt - te[u].tick), te[u].step);
+        double L0[T], L1[T];
+        time_antideriv<M>(tau0, L0);
+        time_antideriv<M>(tau1, L1);
+        double vx = 0.0, vy = 0.0;
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+          const double I = L1[q] - L0[q];
+          vx += I * vv[u][2 * q];
+          vy += I * vv[u][2 * q + 1];
+        }
+        const double inv = 1.0 / (tau1 - tau0);
+        const double mu = q0[u] * ar[u];
+        Vx += mu * (vx * inv);
+        Vy += mu * (vy * inv);
+        mu_sum += mu;
+      }
     }
     if (!ok) set_err(d, ERR_PRED);
     Vx /= mu_sum;
     Vy /= mu_sum;
-    if (d.wall_pin[k]) {
+    if (pin) {
       Vx = 0.0;
       Vy = 0.0;
     } else {
-      const double nx = d.wall_n[k], ny = d.wall_n[NV + k];
       const double vn = Vx * nx + Vy * ny;
       Vx -= vn * nx;
       Vy -= vn * ny;
     }
     const double dtk = double(newt - nk) * node_delta(d, k);
-    d.Xnew[k] = d.X[k] + dtk * Vx;
-    d.Xnew[NV + k] = d.X[NV + k] + dtk * Vy;
+    d.Xnew[k] = xk + dtk * Vx;
+    d.Xnew[NV + k] = yk + dtk * Vy;
     d.ntick_new[k] = newt;
     d.node_stamp[k] = cycle;
     ++nmoved;
@@ -1597,15 +1626,20 @@ __global__ void __launch_bounds__(TPB) k_update(Dev d, Params P, int list) {
     for (int c = 0; c < 3; ++c) hm[c] = (ms[4 + c] + ms[MEM_W + 4 + c]) + ms[2 * MEM_W + 4 + c];
 #pragma unroll
     for (int c = 0; c < 3 * MEM_W; ++c) ms[c] = 0.0;
+    // old and new node positions together with the stamps that choose between
+    // them, so that one wait serves them all
     double X[6];
-    int nd[3];
+    int nd[3], tnew[3];
     bool mv[3];
 #pragma unroll
+    for (int k = 0; k < 3; ++k) nd[k] = d.tri[k * NE + i];
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
-      nd[k] = d.tri[k * NE + i];
+      const double x0 = d.X[nd[k]], y0 = d.X[NV + nd[k]], x1 = d.Xnew[nd[k]], y1 = d.Xnew[NV + nd[k]];
+      tnew[k] = d.ntick_new[nd[k]];
       mv[k] = d.node_stamp[nd[k]] == cycle;
-      X[2 * k] = mv[k] ? d.Xnew[nd[k]] : d.X[nd[k]];
-      X[2 * k + 1] = mv[k] ? d.Xnew[NV + nd[k]] : d.X[NV + nd[k]];
+      X[2 * k] = mv[k] ? x1 : x0;
+      X[2 * k + 1] = mv[k] ? y1 : y0;
     }
     double* r = d.rec + size_t(i) * Sz<M>::RS;
     const double An = tri_area(X);
@@ -1634,7 +1668,7 @@ __global__ void __launch_bounds__(TPB) k_update(Dev d, Params P, int list) {
       if (mv[k]) {
         d.X[nd[k]] = X[2 * k];
         d.X[NV + nd[k]] = X[2 * k + 1];
-        d.ntick[nd[k]] = d.ntick_new[nd[k]];
+        d.ntick[nd[k]] = tnew[k];
       }
   }
   block_max_pos(&d.scal->max_gcl_bits, gmax);
