@@ -770,11 +770,19 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
 
 // ---------------------------------------------------------------------------
 // Space-time Galerkin predictor: nb lanes per element, lane m = spatial node m;
-// floor(64/nb) elements per wavefront (an element never straddles two), the
-// remaining lanes of a wavefront are spare
+// floor(64/nb) elements per wavefront (an element never straddles two); the
+// spare lanes of a wavefront repeat its first ones, same values to the same
+// places, so that they need no LDS of their own. LDS reads (288 cycles per
+// wavefront and slice at M=2) and the FP64 pipe (40 % busy) share the time at 2
+// workgroups of 4 wavefronts per CU; 3 need 168 registers, which spill, and
+// measured 73 instead of 64 us. Reciprocals by Newton instead of divisions (11
+// instructions, 30 per node) and the spare lanes' LDS given up: 97.5 -> 93.0 us
+// per cycle at 302k elements, M=2, LTS. 2 workgroups per CU are asked for
+// because M=3 otherwise takes 4 registers too many for them (39 -> 61 us at
+// 18.6k elements).
 // ---------------------------------------------------------------------------
 template <int M>
-__global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict__ tb, Params P,
+__global__ void __launch_bounds__(TPB, 2) k_predict(Dev d, const Tables* __restrict__ tb, Params P,
                                                  int list) {
   using S = Sz<M>;
   const bool use_list = list >= 0;
@@ -789,18 +797,19 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
   constexpr int NPT = 1 + 3 * nG;        // element mean + edge Gauss points
   constexpr int PPL = (NPT + G - 1) / G; // points per lane
   static_assert(TPB % 64 == 0, "whole wavefronts");
-  __shared__ double lds[(SLOTS + WPB) * LSTR];   // one extra slot per wavefront for its spare lanes
-  __shared__ double c0[16][TPB];         // per lane: fixed parts of slice t = 0
+  __shared__ double lds[SLOTS * LSTR];
+  __shared__ double c0[16][SLOTS * G];   // per node: fixed parts of slice t = 0
   const int NE = d.NE;
   const int nitems = use_list ? d.scal->lists[list].n_live : NE;
   const double g = P.gamma;
   unsigned long long npred = 0;    // predictors evaluated (counted on node 0)
   const int wv = threadIdx.x / 64, lw = threadIdx.x % 64;
   const bool spare = lw >= EPW * G;
-  const int slot = spare ? SLOTS + wv : wv * EPW + lw / G;
-  const int m = spare ? lw - EPW * G : lw % G;   // < G either way
+  const int lc = spare ? lw - EPW * G : lw;
+  const int slot = wv * EPW + lc / G;
+  const int cx = wv * EPW * G + lc;
+  const int m = lc % G;
   double* const my = lds + slot * LSTR;
-  const bool node = !spare;
   const int mm = m;
   // this lane's rows of the spatial derivative matrices
   double Dx[nb], De[nb];
@@ -819,15 +828,14 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
   for (int base = xcd_block((nitems + SLOTS - 1) / SLOTS) * SLOTS; base < nitems;
        base += gridDim.x * SLOTS) {
     const int idx = base + slot;
-    const int i = !spare && idx < nitems ? (use_list ? d.live_list[idx] : idx) : -1;
+    const int i = idx < nitems ? (use_list ? d.live_list[idx] : idx) : -1;
     const int st = i >= 0 ? d.ts[i].step : 0;
     const bool live = st > 0;           // uniform across the lanes of the element
-    const bool act = live && node;
-    if (live && m == 0) ++npred;
+    if (live && !spare && m == 0) ++npred;
     const double dt = live ? double(st) * elem_delta(d, i) : 1.0;
     const double idt = 1.0 / dt;
     double q[T][4], x[T][2];
-    if (act) {
+    if (live) {
       const double* r = rec<M>(d, i);
       const double px = r[XE + 0] + (r[XE + 2] - r[XE + 0]) * nxi + (r[XE + 4] - r[XE + 0]) * neta;
       const double py = r[XE + 1] + (r[XE + 3] - r[XE + 1]) * nxi + (r[XE + 5] - r[XE + 1]) * neta;
@@ -851,7 +859,7 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
     }
     // this node's fields of slice t into the element's exchange buffer
     auto put_fields = [&](int t) {
-      const double ir = 1.0 / q[t][0];
+      const double ir = rcp_newton(q[t][0]);
       const double u = q[t][1] * ir, v = q[t][2] * ir;
       const double p = (g - 1.0) * (q[t][3] - 0.5 * (q[t][1] * u + q[t][2] * v));
       const double h = q[t][3] + p;
@@ -880,7 +888,7 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
         yx += Dx[k] * vy;
         ye += De[k] * vy;
       }
-      const double idet = 1.0 / (xx * ye - xe * yx);
+      const double idet = rcp_newton(xx * ye - xe * yx);
       mt[0] = ye * idet;
       mt[1] = -xe * idet;
       mt[2] = -yx * idet;
@@ -944,7 +952,7 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
         double V[T][2];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-          const double ir = 1.0 / q[t][0];
+          const double ir = rcp_newton(q[t][0]);
           V[t][0] = q[t][1] * ir;
           V[t][1] = q[t][2] * ir;
         }
@@ -973,10 +981,10 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
         spatial_part(da, db, mt0, sp0);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          c0[v][threadIdx.x] = da[v];
-          c0[4 + v][threadIdx.x] = db[v];
-          c0[8 + v][threadIdx.x] = sp0[v];
-          c0[12 + v][threadIdx.x] = mt0[v];
+          c0[v][cx] = da[v];
+          c0[4 + v][cx] = db[v];
+          c0[8 + v][cx] = sp0[v];
+          c0[12 + v][cx] = mt0[v];
         }
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -1003,10 +1011,10 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
           double da[4], db[4], sp[4], mt[4], xi_t, eta_t;
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            da[v] = c0[v][threadIdx.x];
-            db[v] = c0[4 + v][threadIdx.x];
-            sp[v] = c0[8 + v][threadIdx.x];
-            mt[v] = c0[12 + v][threadIdx.x];
+            da[v] = c0[v][cx];
+            db[v] = c0[4 + v][cx];
+            sp[v] = c0[8 + v][cx];
+            mt[v] = c0[12 + v][cx];
           }
           time_metric(0, mt, xi_t, eta_t);
           accumulate(0, da, db, sp, xi_t, eta_t, qn);
@@ -1068,7 +1076,7 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
       }
       wave_sync();
     }
-    if (act) {
+    if (live) {
       double* rw = d.rec + size_t(i) * RS;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -1077,7 +1085,7 @@ __global__ void __launch_bounds__(TPB) k_predict(Dev d, const Tables* __restrict
         for (int t = 0; t < T; ++t) {
           double vx = 0.0, vy = 0.0;
           if (P.lagrangian) {
-            const double ir = 1.0 / q[t][0];
+            const double ir = rcp_newton(q[t][0]);
             vx = q[t][1] * ir;
             vy = q[t][2] * ir;
           }
