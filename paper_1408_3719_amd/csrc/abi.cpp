@@ -237,7 +237,8 @@ int check_err(ader_ctx* c, const aw::Scal& s) {
 // fluxes, update, reconstruction and time step, predictor. first: the cycles
 // before them since the macro-step start (the two sets of list lengths
 // alternate), or -1 when the sets have to be cleared first. last_level: every
-// element ends the macro step in these cycles, so none needs a new predictor.
+// element short of the macro step's end takes one step to it, so the update
+// criterion holds for all of them and none needs a new predictor.
 int issue_cycles(ader_ctx* c, int n, hipStream_t st, int first, bool last_level = false) {
   const aw::Dev& d = c->dev;
   const aw::Params& p = c->prm;
@@ -246,7 +247,7 @@ int issue_cycles(ader_ctx* c, int n, hipStream_t st, int first, bool last_level 
   if (first < 0 && n > 0) LCHK(c, aw::launch_cycle_begin(d, s));
   for (int k = 0; k < n; ++k) {
     const int list = (std::max(first, 0) + k) & 1;
-    LCHK(c, timed(c, ADER_K_SCHED, st, [&] { return aw::launch_sched(d, list, s); }));
+    LCHK(c, timed(c, ADER_K_SCHED, st, [&] { return aw::launch_sched(d, list, last_level, s); }));
     LCHK(c, timed(c, ADER_K_NODE, st, [&] { return aw::launch_node(d, p, M, list, s); }));
     LCHK(c, timed(c, ADER_K_PATCH, st, [&] { return aw::launch_patch(d, p, M, s); }));
     LCHK(c, timed(c, ADER_K_UPDATE, st, [&] { return aw::launch_update(d, p, list, s); }));

@@ -329,7 +329,7 @@ int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, void* 
 // Target time of the run, and which instances are short of it.
 int launch_target(const Dev& d, double t_end, void* stream);
 int launch_cycle_begin(const Dev& d, void* stream);
-int launch_sched(const Dev& d, int list, void* stream);
+int launch_sched(const Dev& d, int list, bool whole, void* stream);
 // Start and stop events (hipEvent_t) for the next grid launch of this host
 // thread: its timestamps are the kernel's own start and end.
 void set_next_launch_events(void* start, void* stop);
