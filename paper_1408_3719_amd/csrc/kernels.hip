@@ -1480,9 +1480,12 @@ __device__ inline void patch_row(const Dev& d, const Tables* __restrict__ tb, do
   }
 }
 
-// One lane per edge.
+// One lane per edge. Two workgroups per CU are asked for: the Osher fluxes and
+// M=3 otherwise take a few registers too many for them (75.6k elements, global
+// step: M=2 Osher 43.3 -> 35.9 us, M=3 Rusanov 47.2 -> 41.0, M=3 Osher 67.1 ->
+// 60.4; 10 to 38 registers go to scratch).
 template <int M, int FLUX>
-__global__ void __launch_bounds__(TPB) k_patch(Dev d, const Tables* __restrict__ tb, Params P) {
+__global__ void __launch_bounds__(TPB, 2) k_patch(Dev d, const Tables* __restrict__ tb, Params P) {
   const int cycle = d.scal->cycle;
   constexpr int T = M + 1, nG = M + 1, TS = Sz<M>::TS;
   const int NV = d.NV, NF = d.NF;
