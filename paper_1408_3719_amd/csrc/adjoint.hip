@@ -11,7 +11,8 @@
 // Given qbar_next = dL/dQ^{n+1} the kernels return qbar = dL/dQ^n, with dt
 // held fixed (the CFL step of eq. eqn.timestep is not differentiated):
 //   k_adj_recon<fwd>  reconstruction from the current averages (8 lanes per
-//                     element, lane s solves stencil s by Givens rotations)
+//                     element, lane s solves stencil s by Householder
+//                     reflections over blocks of rows)
 //   k_adj_pred_fwd    predictor sweeps, each iterate kept, edge traces and
 //                     cell means at the time nodes
 //   k_adj_patch       adjoint of the fluxes: per edge, the flux adjoint
@@ -31,7 +32,7 @@
 // Subgradients: the larger Rusanov signal speed and the bounding HLL speeds are
 // taken from the left state on ties, and |x| has derivative sign(x), 0 at 0.
 // The least-squares adjoint uses A R^-1 = Q of the QR factorisation: the
-// adjoint of the right-hand side is A R^-1 R^-T wbar, so the rotations need
+// adjoint of the right-hand side is A R^-1 R^-T wbar, so the reflections need
 // not be kept.
 #include <hip/hip_runtime.h>
 
@@ -280,8 +281,16 @@ __device__ inline void lts_place(const Tables* __restrict__ tb, const LtsView& s
 // VIRT (local time stepping): the elements of lw.act_list, their own data
 // from the state lw.s1, the stencil elements placed at the element's tick
 // (real or projected, lts_place).
+// The gathers of the rows bound it (7 loads per row, each lane its own line:
+// about half of the 70 us forward at 37.8k elements, M=2), so the forward pass
+// takes the rows a block at a time (ls_triangle: their loads are under way
+// together) and the reverse one row ahead. Two workgroups per CU are asked for up
+// to M=2, where the reverse pass of a moving mesh took 10 registers too many for
+// them. With the blocks: the moving step 720 -> 683 us, a local step's adjoint 14.88
+// -> 14.45 ms, the fixed one 365 -> 362 us, all at 37.8k elements; at M=3, 4.5k
+// elements 391 -> 368 us (moving).
 template <int M, bool REV, bool GEO = false, bool VIRT = false>
-__global__ void __launch_bounds__(TPB) k_adj_recon(Dev d, const Tables* __restrict__ tb, Params P,
+__global__ void __launch_bounds__(TPB, M <= 2 ? 2 : 1) k_adj_recon(Dev d, const Tables* __restrict__ tb, Params P,
                                                    AdjWork w, LtsWork lw) {
   using S = AZ<M>;
   constexpr int nb = S::nb, ne = S::ne, nu = S::nu, WS = S::WS;
@@ -319,15 +328,12 @@ __global__ void __launch_bounds__(TPB) k_adj_recon(Dev d, const Tables* __restri
     // kept data of this lane: slot k at lq[k * 8 * NE]
     double* lq = w.lsq + size_t(i) * 8 + sl;
     const size_t LS = size_t(8) * NE;
-    double R[nu][nu], ws[nu][4];
+    double R[nu][nu], ws[nu][4];   // R: upper triangle
     double om = 0.0, sig = 0.0;
 #pragma unroll
-    for (int a = 0; a < nu; ++a) {
-#pragma unroll
-      for (int b = 0; b < nu; ++b) R[a][b] = 0.0;
+    for (int a = 0; a < nu; ++a)
 #pragma unroll
       for (int v = 0; v < 4; ++v) ws[a][v] = 0.0;
-    }
     if (REV && valid) {
       int k = S::L_R;
 #pragma unroll
@@ -342,40 +348,13 @@ __global__ void __launch_bounds__(TPB) k_adj_recon(Dev d, const Tables* __restri
       sig = lq[S::L_SIG * LS];
     } else if (valid) {
       double z[nu][4];
-#pragma unroll
-      for (int a = 0; a < nu; ++a)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) z[a][v] = 0.0;
-#pragma unroll 1
-      for (int c = 1; c < ne; ++c) {
+      ls_triangle<M>(R, z, [&](int c, double (&a)[nu], double (&b)[4]) {
         double xv[6], qv[4];
         const double* rj = row(c, xv, qv);
-        double a[nu], b[4];
         ls_row<M>(rj, Xi, e1x, e1y, e2x, e2y, idet, a);
 #pragma unroll
         for (int v = 0; v < 4; ++v) b[v] = qv[v] - Qi[v];
-#pragma unroll
-        for (int k = 0; k < nu; ++k) {
-          const double rkk = R[k][k], ak = a[k];
-          const double h2 = rkk * rkk + ak * ak;
-          if (h2 == 0.0) continue;
-          const double rh = rsqrt(h2);
-          const double cs = rkk * rh, sn = ak * rh;
-          R[k][k] = h2 * rh;
-#pragma unroll
-          for (int c2 = k + 1; c2 < nu; ++c2) {
-            const double t = cs * R[k][c2] + sn * a[c2];
-            a[c2] = cs * a[c2] - sn * R[k][c2];
-            R[k][c2] = t;
-          }
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const double t = cs * z[k][v] + sn * b[v];
-            b[v] = cs * b[v] - sn * z[k][v];
-            z[k][v] = t;
-          }
-        }
-      }
+      });
 #pragma unroll
       for (int k = nu - 1; k >= 0; --k) {
 #pragma unroll
@@ -502,10 +481,35 @@ __global__ void __launch_bounds__(TPB) k_adj_recon(Dev d, const Tables* __restri
     // right-hand sides b_c = Q_j - Q_i: their adjoints are a_c . u
     double sumb[4] = {0.0, 0.0, 0.0, 0.0};
     double Xib[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    // the next row's element and the index after it are loaded a row ahead
+    double xn[6], qn[4];
+    int jn = 0;
+    if (!VIRT) {
+      const double* Xn = row(1, xn, qn);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) xn[k] = Xn[k];
+      jn = sidx[size_t(2) * NE];
+    }
 #pragma unroll 1
     for (int c = 1; c < ne; ++c) {
       double xv[6], qv[4];
-      const double* Xj = row(c, xv, qv);
+      const double* Xj = xv;
+      if (VIRT) {
+        Xj = row(c, xv, qv);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) xv[k] = xn[k];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) qv[v] = qn[v];
+        const double* Xn = gbase + size_t(jn) * gs;   // past the last row: that row again
+#pragma unroll
+        for (int k = 0; k < 6; ++k) xn[k] = Xn[k];
+        if (GEO) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) qn[v] = w.q[size_t(v) * NE + jn];
+        }
+        if (c + 2 < ne) jn = sidx[size_t(c + 2) * NE];
+      }
       double a[nu], bb[4];
       ls_row<M>(Xj, Xi, e1x, e1y, e2x, e2y, idet, a);
 #pragma unroll
@@ -1425,7 +1429,7 @@ __global__ void __launch_bounds__(TPB) k_lag_node_rev(Dev d, const Tables* __res
 // are the element's own, added to the reconstruction's and the vertices'
 // adjoints and then cleared (the predictor's outputs are overwritten here).
 template <int M, bool LTS = false>
-__global__ void __launch_bounds__(TPB) k_lag_pred_rev(Dev d, const Tables* __restrict__ tb, Params P,
+__global__ void __launch_bounds__(TPB, M <= 2 ? 2 : 1) k_lag_pred_rev(Dev d, const Tables* __restrict__ tb, Params P,
                                                       LagWork w, double dt_all, LtsWork lz) {
   using S = AZ<M>;
   using L = LP<M>;
