@@ -252,12 +252,12 @@ int ader_get_schedule_record(ader_ctx* ctx, int32_t* step_ptr, int32_t* steps, i
                              int32_t deltas_cap, int64_t* n_steps, int32_t* n_deltas);
 
 /* Launch mode of ader_step_gts / ader_step_lts.  on != 0 (the default): each
- * macro step (levels and predictors, its 2^(L-1) cycles, the unfinished count
- * and the macro-step end) is one HIP graph, captured on a private stream of
+ * macro step (levels and predictors, its 2^(L-1) cycles and the macro-step
+ * end) is one HIP graph, captured on a private stream of
  * the context at the first step with a given number of levels and replayed on
  * the context's stream (the target time is read from device memory, so one
- * graph serves every target); one host synchronisation per macro step, more
- * only when extra cycles are needed (two cycles per captured batch). on == 0:
+ * graph serves every target); one host synchronisation per macro step (up to
+ * eight global steps are queued between two), more only when extra cycles are needed (two cycles per captured batch). on == 0:
  * the same kernels are launched one by one.  Results are identical.  While
  * profiling is on, kernels are always launched one by one. */
 int ader_set_graphs(ader_ctx* ctx, int32_t on);
@@ -369,7 +369,9 @@ int ader_adjoint_lagrangian_step(ader_ctx* ctx, double dt, const double* Q_dev, 
  * as ader_step_lts would leave it.
  *   Qbar_dev, Qbar0_dev: device [4][n_elems] SoA; Xbar_dev, Xbar0_dev:
  *   device [n_nodes][2]; no output may overlap an input.
- * Memory (allocated by the library and freed before returning): for the last
+ * Memory (allocated by the library; what fits in 1/16 of the device's memory
+ * and 1/8 of its free memory stays with the context for the next such call,
+ * until ader_destroy, the rest is freed before returning): for the last
  * keep_macro_steps macro steps (-1: as many as 60% of the free device memory
  * holds, counting 2^(L-1) + 3 states each) the forward keeps the state the
  * reverse sweep reads (ticks, element records, traces, reconstructions, node
@@ -444,7 +446,7 @@ int ader_debug_macro_begin(ader_ctx* ctx, double t_end, int32_t levels);
 
 /* Per-kernel timing for benchmarks: a stage of one kernel launch is timed by
  * start and stop events attached to that launch (the kernel's own execution);
- * a stage of several launches (macro-step boundary, status, adjoint) by HIP
+ * a stage of several launches (macro-step boundary, adjoint) by HIP
  * events recorded before and after it on the context's stream.  ader_set_profiling(ctx, 1) clears the
  * totals and starts recording, 0 stops.  ader_kernel_times synchronises and
  * writes, for each kernel id k < n (ADER_K_*), the summed milliseconds and
@@ -457,7 +459,7 @@ enum {
   ADER_K_RECON,       /* virtual projection, WENO, CFL step and level           */
   ADER_K_PREDICT,     /* space-time predictor                                   */
   ADER_K_MACRO,       /* macro-step boundary: min CFL step, levels              */
-  ADER_K_STATUS,      /* unfinished-element count                               */
+  ADER_K_STATUS,      /* no launches of its own (the stages keep the counts)     */
   ADER_K_ADJOINT,     /* ader_adjoint_gts_step (all its kernels)                */
   ADER_K_COUNT
 };

@@ -34,14 +34,16 @@ struct ader_ctx {
   hipStream_t cap = nullptr;
   hipGraphExec_t gexec = nullptr;
   int g_nominal = 0;
-  hipGraphExec_t gcyc = nullptr;    // FREE_BATCH cycles and the status count
-  hipGraphExec_t gextra = nullptr;  // EXTRA_BATCH cycles and the status count
+  hipGraphExec_t gcyc = nullptr;    // FREE_BATCH cycles
+  hipGraphExec_t gextra = nullptr;  // EXTRA_BATCH cycles
   int64_t extra_cycles = 0, long_macro_steps = 0;   // beyond 2^(L-1) cycles
   // schedule replay tables (device memory owned by the context)
   int* replay_buf = nullptr;
   double* delta_buf = nullptr;     // tick-length replay
   int* rec_buf = nullptr;          // schedule record: steps, then positions
   double* rec_delta_buf = nullptr; // schedule record: tick lengths
+  // device blocks the last LTS adjoint left for the next one (Blocks)
+  std::vector<std::pair<char*, size_t>> adj_blocks;
   // status report of the device (Scal, then the instances) in pinned host memory;
   // fresh while nothing has been queued that changes them
   char* rep = nullptr;
@@ -1393,27 +1395,77 @@ aw::LtsView view_at(const ader_ctx* c, const char* saved) {
   return v;
 }
 
-// Device memory handed out in order from large chunks (freed together).
-struct Pool {
-  std::vector<char*> chunks;
-  size_t chunk = 0, used = 0;
-  int take(ader_ctx* c, size_t bytes, char** out) {
-    bytes = al256(bytes);
-    if (chunks.empty() || used + bytes > chunk) {
-      const size_t n = bytes > chunk ? bytes : chunk;
+void free_adj_blocks(ader_ctx* c) {
+  for (const auto& b : c->adj_blocks) (void)hipFree(b.first);
+  c->adj_blocks.clear();
+}
+
+// Device memory of one LTS adjoint call. Blocks come from those the context
+// kept from its last call when one of about the size is there, else from
+// hipMalloc; small pieces are handed out in order from a chunk. give_back()
+// leaves the blocks with the context, as many as fit in 1/16 of the device's
+// memory and 1/8 of what is free of it, and frees the others. Allocating and
+// freeing the 1.9 GB of a call (4 macro steps at 37.8k elements, M=2) each time
+// is cheap only until a process has passed the whole memory once: from then on
+// the driver clears the pages before it hands them out again, and the call took
+// 117 ms (some of them above 1 s) instead of 14.4.
+struct Blocks {
+  ader_ctx* c;
+  std::vector<std::pair<char*, size_t>> used;
+  char* at = nullptr;   // the chunk in use
+  size_t chunk = 0, left = 0;
+
+  int block(size_t bytes, char** out) {
+    auto& k = c->adj_blocks;
+    size_t best = k.size();
+    for (size_t i = 0; i < k.size(); ++i)
+      if (k[i].second >= bytes && k[i].second <= 2 * bytes && (best == k.size() || k[i].second < k[best].second))
+        best = i;
+    if (best < k.size()) {
+      used.push_back(k[best]);
+      k.erase(k.begin() + best);
+    } else {
       char* p = nullptr;
-      HIPCHK(c, hipMalloc((void**)&p, n));
-      chunks.push_back(p);
-      chunk = n > chunk ? n : chunk;
-      used = 0;
+      hipError_t e = hipMalloc((void**)&p, bytes);
+      if (e == hipErrorOutOfMemory && !k.empty()) {
+        (void)hipGetLastError();
+        free_adj_blocks(c);
+        e = hipMalloc((void**)&p, bytes);
+      }
+      HIPCHK(c, e);
+      used.push_back({p, bytes});
     }
-    *out = chunks.back() + used;
-    used += bytes;
+    *out = used.back().first;
     return 0;
   }
-  void release() {
-    for (char* p : chunks) (void)hipFree(p);
-    chunks.clear();
+  int take(size_t bytes, char** out) {
+    bytes = al256(bytes);
+    if (bytes > left) {
+      const size_t n = std::max(bytes, chunk);
+      int r;
+      if ((r = block(n, &at))) return r;
+      left = n;
+    }
+    *out = at;
+    at += bytes;
+    left -= bytes;
+    return 0;
+  }
+  // after the context's stream has run dry; keep = false: free everything
+  void give_back(bool keep) {
+    size_t free_b = 0, total_b = 0, held = 0;
+    free_adj_blocks(c);   // not needed by this call
+    if (!keep || hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = total_b = 0;
+    const size_t limit = std::min(total_b / 16, free_b / 8);
+    for (const auto& u : used) {
+      if (held + u.second <= limit) {
+        held += u.second;
+        c->adj_blocks.push_back(u);
+      } else {
+        (void)hipFree(u.first);
+      }
+    }
+    used.clear();
   }
 };
 
@@ -1479,15 +1531,11 @@ int macro_by_cycles(ader_ctx* c, double t_end, int nominal, F after, int* ran, d
 // start's predictors; finally the pre-processing reconstruction. The context
 // ends at the forward's end state.
 int adjoint_lts_run(ader_ctx* c, int n_macro, int keep_req, double t_end, const double* Qbar, const double* Xbar,
-                    double* Qbar0, double* Xbar0, int* n_done, Pool& pool, std::vector<char*>& bufs) {
+                    double* Qbar0, double* Xbar0, int* n_done, Blocks& mem) {
   const aw::Dev& d = c->dev;
   const int M = c->cfg.M, L = c->cfg.lts_levels, nominal = L > 0 ? 1 << (L - 1) : 0;
   const size_t sb = state_bytes(c), vb = view_bytes(c);
-  auto take = [&](char** out, size_t bytes) -> int {
-    HIPCHK(c, hipMalloc((void**)out, bytes));
-    bufs.push_back(*out);
-    return 0;
-  };
+  auto take = [&](char** out, size_t bytes) -> int { return mem.block(bytes, out); };
   int r;
   char* wb = nullptr;
   const size_t wbytes = aw::lts_work_bytes(M, d.NE, d.NV, d.NF, c->prm.npic);
@@ -1499,10 +1547,12 @@ int adjoint_lts_run(ader_ctx* c, int n_macro, int keep_req, double t_end, const 
   if ((r = view_save(c, v0))) return r;
   size_t free_b = 0, total_b = 0;
   HIPCHK(c, hipMemGetInfo(&free_b, &total_b));
+  for (const auto& k : c->adj_blocks) free_b += k.second;   // free to this call
   const size_t per_macro = size_t(nominal > 0 ? nominal + 3 : 4 * FREE_BATCH) * vb;
   const long fits = long(std::min<size_t>(size_t(n_macro), size_t(0.6 * double(free_b)) / per_macro));
   const long kept = keep_req < 0 ? fits : std::min<long>(keep_req, n_macro);
-  pool.chunk = std::max<size_t>(vb, size_t(64) * vb);
+  // 64 states at a time, or all of a short run's
+  mem.chunk = vb * size_t(nominal > 0 ? std::clamp<long>(kept * (nominal + 1), 1, 64) : 64);
   std::vector<std::vector<char*>> views(n_macro);   // kept macro steps: start, then each cycle
   std::vector<char*> start(n_macro, nullptr);       // replayed macro steps: full state at the start
   std::vector<double> delta(n_macro, 0.0);
@@ -1512,7 +1562,7 @@ int adjoint_lts_run(ader_ctx* c, int n_macro, int keep_req, double t_end, const 
     if (m >= n_macro - kept) {
       auto keep = [&](int k) -> int {
         char* p = nullptr;
-        int e = pool.take(c, vb, &p);
+        int e = mem.take(vb, &p);
         if (e) return e;
         views[m].push_back(p);
         (void)k;
@@ -1599,15 +1649,13 @@ int ader_adjoint_lts(ader_ctx* c, int32_t n_macro, int32_t keep_macro_steps, dou
   if (c->prm.flux != ADER_FLUX_RUSANOV && c->prm.flux != ADER_FLUX_HLL)
     return fail(c, ADER_E_ARG, "the LTS adjoint covers the Rusanov and HLL fluxes");
   if (!std::isfinite(t_end)) return fail(c, ADER_E_ARG, "t_end is not finite");
-  std::vector<char*> bufs;
-  Pool pool;
+  Blocks mem{c};
   int done = 0;
   const int r =
-      adjoint_lts_run(c, n_macro, keep_macro_steps, t_end, Qbar_dev, Xbar_dev, Qbar0_dev, Xbar0_dev, &done, pool, bufs);
+      adjoint_lts_run(c, n_macro, keep_macro_steps, t_end, Qbar_dev, Xbar_dev, Qbar0_dev, Xbar0_dev, &done, mem);
   (void)hipStreamSynchronize(c->stream);
   c->rep_fresh = false;
-  for (char* p : bufs) (void)hipFree(p);
-  pool.release();
+  mem.give_back(r == 0);
   if (r) return r;
   *n_done = done;
   return ADER_OK;
@@ -1787,6 +1835,7 @@ void ader_destroy(ader_ctx* c) {
   if (c->delta_buf) (void)hipFree(c->delta_buf);
   if (c->rec_buf) (void)hipFree(c->rec_buf);
   if (c->rec_delta_buf) (void)hipFree(c->rec_delta_buf);
+  free_adj_blocks(c);
   if (c->rep) (void)hipHostFree(c->rep);
   drop_graphs(c);
   if (c->cap) (void)hipStreamDestroy(c->cap);

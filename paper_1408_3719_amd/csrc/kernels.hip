@@ -30,8 +30,11 @@
 //                  lane m owns spatial node m for all time nodes; spatial
 //                  derivatives read the other nodes of the same time slice
 //                  from LDS, ordered within the wavefront.
-//   k_sched:       8 lanes per element over its scheduling stencil.
-//   others:        one lane per node, edge or element.
+//   k_sched:       8 lanes per element over its scheduling stencil (one in a
+//                  macro step of one level).
+//   k_patch:       one lane per edge, on small meshes one per Gauss row
+//                  (k_patch_split).
+//   others:        one lane per node or element.
 // Blocks are renumbered so that each XCD works on a contiguous index range.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -458,7 +461,7 @@ __device__ inline double group8_sum(double v) {
 // (real data, or projected to the tick), and the rows read vertices and average
 // from LDS. With the block least squares of basis.h, per launch against rows
 // fetched by their lanes and Givens rotations: explosion of 302k triangles, M=2,
-// 4 levels 264 -> 166 us; vortex of 75k, M=2, 3 levels 93 -> 69 us; vortex of
+// 4 levels 264 -> 163 us; vortex of 75k, M=2, 3 levels 93 -> 69 us; vortex of
 // 19k, M=3 107 -> 98 us; 150k triangles, M=1, global steps 120 -> 69 us; 1,064
 // triangles, M=1 13.3 -> 7.5 us. Now bound by FP64 issue in the least squares
 // (10k of 34k cycles of a workgroup) and the latency of the phases before it
@@ -1256,6 +1259,10 @@ __global__ void __launch_bounds__(SCHED_TPB) k_sched(Dev d, int chunk, int list,
 // ---------------------------------------------------------------------------
 // Node solver and node motion
 // ---------------------------------------------------------------------------
+// Bound by the chain of dependent loads of a ring (~1 us each: entries, then
+// stamps and ticks, then records) and, on small meshes, by the launch: entry by
+// entry 32.6 us per cycle at 302k elements and 14.3 on the 4.7k vortex, RING_U at
+// a time 29.3 and 11.0.
 constexpr int RING_U = 8;
 template <int M>
 __global__ void __launch_bounds__(TPB) k_node(Dev d, const Tables* __restrict__ tb, Params P, int list) {
@@ -1631,6 +1638,9 @@ __global__ void __launch_bounds__(TPB) k_patch_split(Dev d, const Tables* __rest
 // ---------------------------------------------------------------------------
 // Memory variables and conservative update
 // ---------------------------------------------------------------------------
+// Bound by the chain list entry -> nodes -> positions and by the 192 bytes of
+// slots an element reads and clears; old and new positions are loaded with the
+// stamps that choose between them: 30.5 -> 29.6 us per cycle at 302k elements.
 template <int M>
 __global__ void __launch_bounds__(TPB) k_update(Dev d, Params P, int list) {
   const int cycle = d.scal->cycle;
