@@ -85,15 +85,19 @@ def recon_flops(M: int) -> int:
     nb = (M + 1) * (M + 2) // 2
     nu = nb - 1
     ne = 2 * nb
-    # quadrature points of the rule exact to degree M and the flops that place
-    # each (centroid 6, edge midpoint 4, vertex 0)
-    point_cost = {1: [6], 2: [4, 4, 4], 3: [0, 0, 0, 4, 4, 4, 6]}[M]
     ref = 3 * 8                                   # vertices into the element's frame
-    means = sum(c + 2 * nb + 2 * nb for c in point_cost)   # point, monomials, weighted sums
+    means = {1: 6, 2: 30, 3: 88}[M]               # monomial means in closed form
     arow = nu + 4                                 # shift by the reference means + right-hand side
-    givens = nu * (8 + 24) + 6 * nu * (nu - 1) // 2
-    row = ref + means + arow + givens
-    stencil = (ne - 1) * row + 4 * nu * (nu + 1) + 4 * (2 * nu * nu + 2 * nu) + 20 + 8 * nu
+    row = ref + means + arow
+    # Householder triangle: a first block of rows, the others folded in
+    first, nxt = {1: (5, 0), 2: (6, 3), 3: (10, 5)}[M]
+    qr = sum(2 * (first - k) + 12 + (nu - k - 1 + 4) * 4 * (first - k) for k in range(nu))
+    rest = ne - 1 - first
+    while rest > 0:
+        p = min(nxt, rest)
+        qr += sum(2 * (p + 1) + 12 + (nu - k - 1 + 4) * 4 * (p + 1) for k in range(nu))
+        rest -= p
+    stencil = (ne - 1) * row + qr + 4 * nu * (nu + 1) + 4 * (2 * nu * nu + 2 * nu) + 20 + 8 * nu
     out = nb * 4 * 2 * nu                         # nodal values from the weighted coefficients
     cfl = 4 * 40
     return 7 * stencil + out + cfl
