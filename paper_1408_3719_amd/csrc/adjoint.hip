@@ -280,10 +280,12 @@ __device__ inline void lts_place(const Tables* __restrict__ tb, const LtsView& s
 // VIRT (local time stepping): the elements of lw.act_list, their own data
 // from the state lw.s1, the stencil elements placed at the element's tick
 // (real or projected, lts_place).
-// The gathers of the rows bound it (7 loads per row, each lane its own line:
-// about half of the 70 us forward at 37.8k elements, M=2), so the forward pass
-// takes the rows a block at a time (ls_triangle: their loads are under way
-// together) and the reverse one row ahead. Two workgroups per CU are asked for up
+// Bound by latency at the two wavefronts per SIMD its registers allow (a row is
+// index, element, arithmetic one after the other), not by the number of its
+// gathers: vertices and averages in one record, 5 loads per row instead of 7,
+// took the same time. So the forward pass takes the rows a block at a time
+// (ls_triangle: their loads are under way together) and the reverse one row
+// ahead. Two workgroups per CU are asked for up
 // to M=2, where the reverse pass of a moving mesh took 10 registers too many for
 // them. With the blocks: the moving step 720 -> 683 us, a local step's adjoint 14.88
 // -> 14.45 ms, the fixed one 365 -> 362 us, all at 37.8k elements; at M=3, 4.5k
