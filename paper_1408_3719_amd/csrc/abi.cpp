@@ -485,10 +485,10 @@ int run_free(ader_ctx* c, double t_target, int max_macro) {
   return 0;
 }
 
-// The instances as of the last read_scal.
-int read_insts(ader_ctx* c, std::vector<aw::Inst>& in) {
-  in.assign(rep_inst(c), rep_inst(c) + c->dev.K);
-  return 0;
+// The instances as of the last read_scal: a caller that has not just made one
+// must look at rep_fresh first.
+std::vector<aw::Inst> report_insts(const ader_ctx* c) {
+  return std::vector<aw::Inst>(rep_inst(c), rep_inst(c) + c->dev.K);
 }
 
 // t: the earliest instance time (the common time of all elements when there
@@ -902,9 +902,7 @@ int ader_upload_state_xy(ader_ctx* c, const double* Q_dev, const double* node_xy
 // Statistics at the end of a run, whose last status read is still fresh.
 static int run_stats(ader_ctx* c, ader_stats* st) {
   if (!c->rep_fresh) return ader_get_stats(c, st);
-  std::vector<aw::Inst> in;
-  read_insts(c, in);
-  fill_stats(c, rep_scal(c), in, st);
+  fill_stats(c, rep_scal(c), report_insts(c), st);
   return ADER_OK;
 }
 
@@ -938,10 +936,9 @@ int ader_get_stats(ader_ctx* c, ader_stats* st) {
   if (!c || !st) return ADER_E_ARG;
   if (!c->bound) return fail(c, ADER_E_ORDER, "no workspace bound");
   aw::Scal s;
-  std::vector<aw::Inst> in;
-  int r = read_scal(c, s);
-  if (r || (r = read_insts(c, in))) return r;
-  fill_stats(c, s, in, st);
+  const int r = read_scal(c, s);
+  if (r) return r;
+  fill_stats(c, s, report_insts(c), st);
   return ADER_OK;
 }
 
@@ -973,9 +970,9 @@ int ader_debug_dump(ader_ctx* c, int32_t what, void* host, size_t bytes) {
   if (!c->bound) return fail(c, ADER_E_ORDER, "no workspace bound");
   if (what == ADER_DBG_SCAL) {
     aw::Scal s;
-    std::vector<aw::Inst> in;
-    int r = read_scal(c, s);
-    if (r || (r = read_insts(c, in))) return r;
+    const int r = read_scal(c, s);
+    if (r) return r;
+    const std::vector<aw::Inst> in = report_insts(c);
     double v[4] = {in[0].T, in[0].delta, double(s.N), s.t_end};
     std::memcpy(host, v, sizeof(v));
     return ADER_OK;
@@ -1010,9 +1007,9 @@ int ader_debug_inject(ader_ctx* c, int32_t what, const void* host, size_t bytes)
   c->rep_fresh = false;
   if (what == ADER_DBG_SCAL) {
     aw::Scal s;
-    std::vector<aw::Inst> in;
     int r = read_scal(c, s);
-    if (r || (r = read_insts(c, in))) return r;
+    if (r) return r;
+    std::vector<aw::Inst> in = report_insts(c);
     double v[4];
     std::memcpy(v, host, sizeof(v));
     in[0].T = v[0];
@@ -1074,10 +1071,10 @@ int ader_set_profiling(ader_ctx* c, int32_t on) {
 int ader_instance_times(ader_ctx* c, int32_t n, double* T_host) {
   if (!c || n < 0 || (n > 0 && !T_host)) return ADER_E_ARG;
   if (!c->bound) return fail(c, ADER_E_ORDER, "no workspace bound");
-  std::vector<aw::Inst> in;
-  int r = read_insts(c, in);
+  aw::Scal s;
+  const int r = read_scal(c, s);
   if (r) return r;
-  for (int k = 0; k < n && k < int(in.size()); ++k) T_host[k] = in[k].T;
+  for (int k = 0; k < n && k < c->dev.K; ++k) T_host[k] = rep_inst(c)[k].T;
   return ADER_OK;
 }
 
