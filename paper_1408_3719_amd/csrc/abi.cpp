@@ -343,7 +343,8 @@ void set_free(ader_ctx* c, bool free_steps) {
 
 // Status at the start of a run, the target time being t_target: as of the last
 // report when that is still fresh (the same test for open instances as the
-// device's), else read.
+// device's) and there is a step to take, else read, so that a run without one
+// still returns with the stream run dry.
 int run_start(ader_ctx* c, double t_target, aw::Scal& s) {
   LCHK(c, aw::launch_target(c->dev, t_target, c->stream));
   if (!c->rep_fresh) return read_scal(c, s);
@@ -351,7 +352,7 @@ int run_start(ader_ctx* c, double t_target, aw::Scal& s) {
   s.n_open = 0;
   for (int k = 0; k < c->dev.K; ++k)
     s.n_open += !(t_target - rep_inst(c)[k].T <= 1e-12 * std::fmax(1.0, std::fabs(t_target)));
-  return 0;
+  return s.n_open == 0 ? read_scal(c, s) : 0;
 }
 
 // Global steps queued between two status reads. An idle wait and a report cost

@@ -35,3 +35,23 @@ def test_instance_times_after_an_injected_time():
     v[0] = 0.625
     s.inject("SCAL", v)
     assert s.instance_times()[0] == 0.625
+
+
+@pytest.mark.parametrize("levels", [1, 3, 0])
+def test_a_run_without_a_step_still_synchronises(levels):
+    """The caller's work queued before the call is done when it returns."""
+    import torch
+
+    s, _, _ = _solver(levels=levels)
+    step = s.step_gts if levels == 1 else s.step_lts
+    t = step(0.05)["t"]
+    a = torch.ones(4096, 4096, dtype=torch.float64, device=s.device)
+    for _ in range(3):
+        a @ a                     # the library's first calls
+    torch.cuda.synchronize()
+    for _ in range(40):           # ~80 ms
+        b = a @ a
+    assert not s.stream.query()
+    step(t)
+    assert s.stream.query()
+    assert float(b[0, 0]) == 4096.0
