@@ -1888,12 +1888,14 @@ __global__ void __launch_bounds__(TPB) k_macro_end(Dev d, int only_if_done) {
 }
 
 // The target time of a run, and which instances are short of it, and how many
-// (one workgroup).
+// (one workgroup). Their smallest CFL steps are taken afresh: a macro step begun
+// without a cycle since leaves its own behind.
 __global__ void __launch_bounds__(TPB) k_target(Dev d, double t_end) {
   int c = 0;
   for (int k = threadIdx.x; k < d.K; k += blockDim.x) {
     const int open = short_of(d.inst[k].T, t_end);
     d.inst[k].open = open;
+    d.inst[k].min_dt_bits = ~0ull;
     c += open;
   }
   c = block_sum(c);

@@ -55,3 +55,18 @@ def test_a_run_without_a_step_still_synchronises(levels):
     step(t)
     assert s.stream.query()
     assert float(b[0, 0]) == 4096.0
+
+
+@pytest.mark.parametrize("levels", [1, 3])
+def test_a_macro_step_begun_again_takes_the_steps_as_they_are(levels):
+    """The tick length follows the CFL steps at the begin, larger ones too."""
+    s, _, _ = _solver(levels=levels)
+    s.debug_macro_begin(1e9, levels)
+    first = s.dump("SCAL")[1]
+    s.inject("DTCFL", 4.0 * s.dump("DTCFL"))
+    s.debug_macro_begin(1e9, levels)
+    assert s.dump("SCAL")[1] == 4.0 * first
+    a, _, _ = _solver(levels=levels)
+    a.inject("DTCFL", 4.0 * a.dump("DTCFL"))
+    a.debug_macro_begin(1e9, levels)
+    assert np.array_equal(a.dump("STEP"), s.dump("STEP"))
