@@ -261,11 +261,12 @@ int issue_cycles(ader_ctx* c, int n, hipStream_t st, int first, bool last_level 
 
 // Tick lengths and levels of the open instances (flagged by
 // launch_target for the target time or by the macro step before), predictors. nominal = 2^(L-1)
-// for L dyadic levels, 0 for free steps.
-int issue_macro_begin(ader_ctx* c, int nominal, hipStream_t st) {
+// for L dyadic levels, 0 for free steps. queued: no status read before it, so
+// that it may lie past the end of the run.
+int issue_macro_begin(ader_ctx* c, int nominal, hipStream_t st, bool queued = false) {
   const double frac = nominal <= 1 ? 1.0 : c->cfg.lts_step_fraction > 0.0 ? c->cfg.lts_step_fraction : 0.95;
   LCHK(c, timed(c, ADER_K_MACRO, st,
-                [&] { return aw::launch_macro_begin(c->dev, aw::MACRO_TICKS, nominal, frac, st); }));
+                [&] { return aw::launch_macro_begin(c->dev, aw::MACRO_TICKS, nominal, frac, queued, st); }));
   LCHK(c, timed(c, ADER_K_PREDICT, st, [&] { return aw::launch_predict(c->dev, c->prm, c->cfg.M, -1, st); }));
   return 0;
 }
@@ -280,7 +281,7 @@ int issue_macro_begin(ader_ctx* c, int nominal, hipStream_t st) {
 // from the device (launch_target), so one captured graph serves every target.
 int issue_macro(ader_ctx* c, int nominal, hipStream_t st) {
   int r;
-  if ((r = issue_macro_begin(c, nominal, st))) return r;
+  if ((r = issue_macro_begin(c, nominal, st, true))) return r;
   if ((r = issue_cycles(c, nominal, st, 0, nominal == 1 && !c->dev.replay_steps && !c->dev.replay_delta))) return r;
   LCHK(c, aw::launch_macro_end(c->dev, 1, st));
   return 0;

@@ -325,7 +325,8 @@ int launch_report(const Dev& d, void* out, void* stream);
 int launch_reconstruct(const Dev& d, const Params& p, int M, int list, int set_level,
                        void* stream);
 int launch_predict(const Dev& d, const Params& p, int M, int list, void* stream);
-int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, void* stream);
+// queued: the macro step may be one past the end of the run.
+int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, bool queued, void* stream);
 // Target time of the run, and which instances are short of it.
 int launch_target(const Dev& d, double t_end, void* stream);
 int launch_cycle_begin(const Dev& d, void* stream);

@@ -1799,10 +1799,11 @@ __device__ inline double macro_delta(const Dev& d, const Inst& in, int N, double
 // Tick lengths and levels at the macro-step start; elements of closed instances
 // sit at tick N with no step, i.e. finished. Every thread works out its
 // instance's tick length itself; the first K also keep it, with its checks and
-// records.
-__global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, double dscale) {
+// records. queued: the macro step may lie past the end of the run; it then does
+// nothing and the tick lengths stay those of the last one taken.
+__global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, double dscale, int queued) {
   const int n = max(max(d.NE, d.NV), d.K);
-  const bool in_step = d.scal->n_open != 0;   // else the run is over: this macro step does nothing
+  const bool in_step = d.scal->n_open != 0;
   if (blockIdx.x == 0) {
     int unfinished = 0;
     for (int k = threadIdx.x; k < d.K; k += TPB) unfinished += d.inst[k].open ? d.inst[k].n_elems : 0;
@@ -1818,7 +1819,7 @@ __global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, d
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     if (i < d.K) {
       const double delta = macro_delta(d, d.inst[i], N, fraction, dscale);
-      if (in_step) d.inst[i].delta = delta;
+      if (in_step || !queued) d.inst[i].delta = delta;
       if (d.inst[i].open) {
         const int m = d.scal->macro_index;
         if (d.replay_delta && m >= d.replay_delta_n) set_err(d, ERR_REPLAY);
@@ -2103,10 +2104,10 @@ int launch_target(const Dev& d, double t_end, void* s) {
   return 0;
 }
 
-int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, void* s) {
+int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, bool queued, void* s) {
   AW_LAUNCH(k_min_dt, (long(d.NE) + MIN_U - 1) / MIN_U, s, d);
   const long n = std::max(long(std::max(d.NE, d.NV)), long(d.K));
-  AW_LAUNCH(k_levels, n, s, d, N, fraction, double(nominal) / double(N));
+  AW_LAUNCH(k_levels, n, s, d, N, fraction, double(nominal) / double(N), int(queued));
   return 0;
 }
 

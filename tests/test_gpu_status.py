@@ -70,3 +70,14 @@ def test_a_macro_step_begun_again_takes_the_steps_as_they_are(levels):
     a.inject("DTCFL", 4.0 * a.dump("DTCFL"))
     a.debug_macro_begin(1e9, levels)
     assert np.array_equal(a.dump("STEP"), s.dump("STEP"))
+
+
+@pytest.mark.parametrize("levels", [1, 3])
+def test_a_macro_step_begun_at_its_target_stands_still(levels):
+    """No instance is open: every element stays at the time reached."""
+    s, _, _ = _solver(levels=levels)
+    step = s.step_gts if levels == 1 else s.step_lts
+    t = step(0.05)["t"]
+    s.debug_macro_begin(t, levels)
+    assert s.dump("SCAL")[1] == 0.0
+    assert (s.download()[2] == t).all()
