@@ -262,7 +262,7 @@ int issue_cycles(ader_ctx* c, int n, hipStream_t st, int first, bool last_level 
 // Tick lengths and levels of the open instances (flagged by
 // launch_target for the target time or by the macro step before), predictors. nominal = 2^(L-1)
 // for L dyadic levels, 0 for free steps. queued: no status read before it, so
-// that it may lie past the end of the run.
+// that it may lie past the end of the run or behind a step that failed.
 int issue_macro_begin(ader_ctx* c, int nominal, hipStream_t st, bool queued = false) {
   const double frac = nominal <= 1 ? 1.0 : c->cfg.lts_step_fraction > 0.0 ? c->cfg.lts_step_fraction : 0.95;
   LCHK(c, timed(c, ADER_K_MACRO, st,
@@ -358,7 +358,7 @@ int run_start(ader_ctx* c, double t_target, aw::Scal& s) {
 
 // Global steps queued between two status reads. An idle wait and a report cost
 // ~20 us, a step of a small mesh ~50 us of kernels; a step queued past the
-// target does nothing, but takes its launches.
+// target or behind an error does nothing, but takes its launches.
 constexpr int GTS_BATCH = 8;
 
 // Global steps to queue before the next status read: as many as the last tick
@@ -410,9 +410,14 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
       return r;
     }
     if ((r = read_scal(c, s))) return r;
-    const int ended = s.macro_index - index;   // of the queued steps, those that had an open instance
-    c->cycles += nominal * (batched ? ended : 1);
-    if ((r = check_err(c, s))) return r;
+    // of the queued steps, those that had an open instance and no error before
+    // them; the one that failed may not have ended
+    const int ended = s.macro_index - index, stuck = s.n_unfinished != 0;
+    c->cycles += batched ? ended + stuck : nominal;
+    if ((r = check_err(c, s))) {
+      if (batched) c->macro_steps += ended + stuck - 1;
+      return r;
+    }
     if (s.n_unfinished != 0) {
       long long last = (long long)s.updates;
       for (;;) {

@@ -74,7 +74,7 @@ struct Scal {
                     // start, less those that reach it in each cycle)
   int err;          // sticky error bits (ERR_*)
   int cycle;        // stamp of the current cycle (advanced by the cycle's reconstruction)
-  int pad;
+  int failed;       // an error was raised before the current macro step
   unsigned long long max_gcl_bits;  // max relative GCL residual
   unsigned long long updates;
   unsigned long long overshoots;
@@ -83,7 +83,8 @@ struct Scal {
   unsigned long long n_node;    // node moves
   unsigned long long replay_overrides;   // replayed steps that differ from the level rule's
   int macro_index;  // macro steps ended since the state upload
-  int in_step;      // the macro step has open instances (else its kernels do nothing)
+  int in_step;      // the macro step has open instances and no error came before it
+                    // (else its kernels do nothing)
 };
 
 static_assert(offsetof(Scal, lists) % 8 == 0, "n_active and n_live must form one aligned 8-byte word");
@@ -325,7 +326,7 @@ int launch_report(const Dev& d, void* out, void* stream);
 int launch_reconstruct(const Dev& d, const Params& p, int M, int list, int set_level,
                        void* stream);
 int launch_predict(const Dev& d, const Params& p, int M, int list, void* stream);
-// queued: the macro step may be one past the end of the run.
+// queued: the macro step may be one past the end of the run or behind an error.
 int launch_macro_begin(const Dev& d, int N, int nominal, double fraction, bool queued, void* stream);
 // Target time of the run, and which instances are short of it.
 int launch_target(const Dev& d, double t_end, void* stream);

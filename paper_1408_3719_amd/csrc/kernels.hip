@@ -1716,8 +1716,10 @@ __global__ void __launch_bounds__(TPB) k_update(Dev d, Params P, int list) {
 // workgroup takes MIN_U such rows per wavefront and merges its wavefronts'
 // minima first, so a single instance takes one atomic per workgroup (atomics
 // on one address serialise).
+// The errors so far are noted for k_levels, whose own blocks may raise more.
 constexpr int MIN_U = 4;
 __global__ void __launch_bounds__(TPB) k_min_dt(Dev d) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) d.scal->failed = d.scal->err != 0;
   constexpr int WPB = TPB / 64;
   __shared__ int wk[WPB];
   __shared__ double wm[WPB];
@@ -1799,11 +1801,12 @@ __device__ inline double macro_delta(const Dev& d, const Inst& in, int N, double
 // Tick lengths and levels at the macro-step start; elements of closed instances
 // sit at tick N with no step, i.e. finished. Every thread works out its
 // instance's tick length itself; the first K also keep it, with its checks and
-// records. queued: the macro step may lie past the end of the run; it then does
-// nothing and the tick lengths stay those of the last one taken.
+// records. queued: the macro step may lie past the end of the run, or behind one
+// that failed; it then does nothing, and the tick lengths and the count of
+// unfinished elements stay those of the last one taken.
 __global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, double dscale, int queued) {
   const int n = max(max(d.NE, d.NV), d.K);
-  const bool in_step = d.scal->n_open != 0;
+  const bool failed = queued && d.scal->failed, in_step = d.scal->n_open != 0 && !failed;
   if (blockIdx.x == 0) {
     int unfinished = 0;
     for (int k = threadIdx.x; k < d.K; k += TPB) unfinished += d.inst[k].open ? d.inst[k].n_elems : 0;
@@ -1813,14 +1816,14 @@ __global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, d
       d.scal->in_step = in_step;
       d.scal->lists[0] = {0, 0};
       d.scal->lists[1] = {0, 0};
-      d.scal->n_unfinished = unfinished;
+      if (!failed) d.scal->n_unfinished = unfinished;
     }
   }
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     if (i < d.K) {
       const double delta = macro_delta(d, d.inst[i], N, fraction, dscale);
       if (in_step || !queued) d.inst[i].delta = delta;
-      if (d.inst[i].open) {
+      if (d.inst[i].open && in_step) {
         const int m = d.scal->macro_index;
         if (d.replay_delta && m >= d.replay_delta_n) set_err(d, ERR_REPLAY);
         if (d.rec_delta) {
@@ -1833,7 +1836,7 @@ __global__ void __launch_bounds__(TPB) k_levels(Dev d, int N, double fraction, d
       }
     }
     if (i < d.NE) {
-      const double delta = macro_delta(d, d.inst[d.K == 1 ? 0 : d.e_inst[i]], N, fraction, dscale);
+      const double delta = failed ? 0.0 : macro_delta(d, d.inst[d.K == 1 ? 0 : d.e_inst[i]], N, fraction, dscale);
       TickStep me;
       if (delta > 0.0) {
         int over;

@@ -3,7 +3,7 @@ device at the call, whatever ran since the last report."""
 import numpy as np
 import pytest
 
-from workloads import vortex_case
+from workloads import concat_instances, sod_case, vortex_case
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +81,40 @@ def test_a_macro_step_begun_at_its_target_stands_still(levels):
     s.debug_macro_begin(t, levels)
     assert s.dump("SCAL")[1] == 0.0
     assert (s.download()[2] == t).all()
+
+
+def _failing(batch):
+    """A tube too coarse for the unlimited scheme, alone or between two vortices."""
+    from paper_1408_3719_amd import Config, Solver
+
+    mesh, Q = sod_case(600, seed=1408)
+    if not batch:
+        return Solver(mesh.nodes, mesh.tris, mesh.bedges, Q, Config(M=1))
+    nodes, tris, bedges, Q, first = concat_instances([vortex_case(300, seed=1), (mesh, Q), vortex_case(400, seed=2)])
+    return Solver(nodes, tris, bedges, Q, Config(M=1), instance_first=first)
+
+
+def _after(s):
+    """State, steps, times and statistics, whatever they hold."""
+    st = s.stats()
+    return [*s.download(), s.instance_times(), s.dump("TICK"), s.dump("STEP"), s.dump("NTICK"), s.dump("WNOD"),
+            s.dump("DTCFL"), s.dump("SCAL"), np.array([float(st[k]) for k in st])]
+
+
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("before", [0, 3, 6])
+def test_a_failed_run_stops_at_the_step_that_failed(batch, before):
+    """Steps queued behind it leave everything as eager launches do, which
+    stop there; `before` single steps move it inside the queue."""
+    from paper_1408_3719_amd import AderError
+
+    a, b = _failing(batch), _failing(batch)
+    b.set_graphs(False)
+    for s in (a, b):
+        for _ in range(before):
+            s.step_gts(1e9, 1)
+        with pytest.raises(AderError):
+            s.step_gts(2.0)
+    assert a.stats()["macro_steps"] == b.stats()["macro_steps"] > before
+    for x, y in zip(_after(a), _after(b)):
+        assert np.array_equal(x, y, equal_nan=True)
