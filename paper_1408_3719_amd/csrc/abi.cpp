@@ -49,7 +49,7 @@ struct ader_ctx {
   char* rep = nullptr;
   int rep_K = 0;
   bool rep_fresh = false;
-  double prev_delta = 0.0;   // tick length of instance 0 at the report before
+  aw::StepEstimate est;      // of the global steps since the state upload
   // the library's fixed adjoint scratch on this context's GPU (ader_bind_workspace)
   void* static_work = nullptr;
   size_t static_bytes = 0;
@@ -213,7 +213,6 @@ const aw::Inst* rep_inst(const ader_ctx* c) {
 // The device's status, written to pinned memory by a kernel of its own (a copy
 // into pageable memory costs a staging copy more).
 int read_scal(ader_ctx* c, aw::Scal& s) {
-  c->prev_delta = rep_inst(c)[0].delta;
   LCHK(c, aw::launch_report(c->dev, c->rep, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->prof) flush_events(c);
@@ -352,7 +351,7 @@ int run_start(ader_ctx* c, double t_target, aw::Scal& s) {
   s = rep_scal(c);
   s.n_open = 0;
   for (int k = 0; k < c->dev.K; ++k)
-    s.n_open += !(t_target - rep_inst(c)[k].T <= 1e-12 * std::fmax(1.0, std::fabs(t_target)));
+    s.n_open += aw::short_of_target(rep_inst(c)[k].T, t_target);
   return s.n_open == 0 ? read_scal(c, s) : 0;
 }
 
@@ -360,21 +359,6 @@ int run_start(ader_ctx* c, double t_target, aw::Scal& s) {
 // ~20 us, a step of a small mesh ~50 us of kernels; a step queued past the
 // target or behind an error does nothing, but takes its launches.
 constexpr int GTS_BATCH = 8;
-
-// Global steps to queue before the next status read: as many as the last tick
-// length needs to reach the target, at most GTS_BATCH.
-int gts_batch(const ader_ctx* c, double t_target) {
-  const double steps_per = double(aw::MACRO_TICKS);
-  double need = 0.0;
-  for (int k = 0; k < c->dev.K; ++k) {
-    const aw::Inst& in = rep_inst(c)[k];
-    if (!in.open && k > 0) continue;
-    const double delta = k == 0 ? std::fmax(in.delta, c->prev_delta) : in.delta;
-    if (!(delta > 0.0)) return 1;
-    need = std::fmax(need, (t_target - in.T) / (steps_per * delta));
-  }
-  return need >= double(GTS_BATCH) ? GTS_BATCH : std::max(1, int(std::ceil(need)));
-}
 
 // Macro steps of L dyadic levels until t_target; returns 0 or an error code.
 // One host synchronisation per macro step of 2^(L-1) cycles; when some element
@@ -398,7 +382,7 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
     if (s.n_open == 0) break;      // every instance has reached t_target
     int queued = 1;
     if (batched) {
-      queued = gts_batch(c, t_target);
+      queued = c->est.steps(rep_inst(c), t_target, GTS_BATCH);
       if (max_macro > 0) queued = std::min(queued, max_macro - k);
     }
     const int index = s.macro_index;
@@ -410,6 +394,7 @@ int run_macro(ader_ctx* c, double t_target, int max_macro, int levels) {
       return r;
     }
     if ((r = read_scal(c, s))) return r;
+    if (nominal == 1) c->est.note(rep_inst(c));
     // of the queued steps, those that had an open instance and no error before
     // them; the one that failed may not have ended
     const int ended = s.macro_index - index, stuck = s.n_unfinished != 0;
@@ -840,6 +825,7 @@ int ader_bind_workspace(ader_ctx* c, void* dev_ptr, size_t bytes) {
   }
   std::memset(c->rep, 0, aw::report_bytes(d.K));
   c->rep_fresh = false;
+  c->est.reset(d.K);
   if ((r = h2d(c, d.inst, in0.data(), in0.size() * sizeof(aw::Inst)))) return r;
   if ((r = h2d(c, d.tri, tri.data(), tri.size() * sizeof(int)))) return r;
   if ((r = h2d(c, d.elem_edges, ee.data(), ee.size() * sizeof(int)))) return r;
@@ -889,6 +875,7 @@ int ader_upload_state_xy(ader_ctx* c, const double* Q_dev, const double* node_xy
     xy = to_soa(t.xy, t.NV, 2);
     if ((r = h2d(c, d.X, xy.data(), xy.size() * sizeof(double)))) return r;
   }
+  c->est.reset(d.K);
   c->cycles = 0;
   c->macro_steps = 0;
   c->extra_cycles = 0;

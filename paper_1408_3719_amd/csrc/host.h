@@ -1,5 +1,7 @@
 // Host-side pieces of the aderweno library: tables and topology.
 #pragma once
+#include <algorithm>
+#include <cmath>
 #include <string>
 #include <vector>
 
@@ -32,5 +34,36 @@ struct Topology {
 // Throws std::runtime_error with a message on an invalid mesh.
 void build_topology(int M, int n_nodes, const double* xy, int n_elems, const int* tri,
                     int n_bedges, const int* bedge, Topology& t);
+
+// Is an instance at time T short of the target time (the test that the device
+// applies too)?
+inline bool short_of_target(double T, double t_target) {
+  return !(t_target - T <= 1e-12 * std::fmax(1.0, std::fabs(t_target)));
+}
+
+// Global steps to queue before the next status read, estimated from the steps
+// that the run has taken since the state upload. Results do not depend on it.
+struct StepEstimate {
+  // per instance the tick length of its last step that did not end at the
+  // target (that one may be cut short), 0: none yet
+  std::vector<double> delta;
+  void reset(int K) { delta.assign(size_t(K), 0.0); }
+  // the instances after the queued steps
+  void note(const Inst* in) {
+    for (size_t k = 0; k < delta.size(); ++k)
+      if (in[k].open && in[k].delta > 0.0) delta[k] = in[k].delta;
+  }
+  // as many as the instance furthest behind needs, at most `limit`; one while an
+  // instance short of the target has no step to go by. The others do not count.
+  int steps(const Inst* in, double t_target, int limit) const {
+    double need = 0.0;
+    for (size_t k = 0; k < delta.size(); ++k) {
+      if (!short_of_target(in[k].T, t_target)) continue;
+      if (!(delta[k] > 0.0)) return 1;
+      need = std::fmax(need, (t_target - in[k].T) / (double(MACRO_TICKS) * delta[k]));
+    }
+    return need >= double(limit) ? limit : std::max(1, int(std::ceil(need)));
+  }
+};
 
 }  // namespace aw
