@@ -49,7 +49,7 @@ struct ader_ctx {
   char* rep = nullptr;
   int rep_K = 0;
   bool rep_fresh = false;
-  aw::StepEstimate est;      // of the global steps since the state upload
+  aw::StepEstimate est;      // of the global steps to queue
   // the library's fixed adjoint scratch on this context's GPU (ader_bind_workspace)
   void* static_work = nullptr;
   size_t static_bytes = 0;
@@ -875,7 +875,6 @@ int ader_upload_state_xy(ader_ctx* c, const double* Q_dev, const double* node_xy
     xy = to_soa(t.xy, t.NV, 2);
     if ((r = h2d(c, d.X, xy.data(), xy.size() * sizeof(double)))) return r;
   }
-  c->est.reset(d.K);
   c->cycles = 0;
   c->macro_steps = 0;
   c->extra_cycles = 0;

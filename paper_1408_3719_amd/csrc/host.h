@@ -42,7 +42,10 @@ inline bool short_of_target(double T, double t_target) {
 }
 
 // Global steps to queue before the next status read, estimated from the steps
-// that the run has taken since the state upload. Results do not depend on it.
+// taken so far. Results do not depend on it: a step too many does nothing, one
+// too few costs a status read. A new state's first steps are guessed from those of
+// the state before, since a caller who uploads again mostly uploads a like state
+// (1,064 triangles, M=1, 20 steps per upload: 1,245 us, 1,270 with a fresh start).
 struct StepEstimate {
   // per instance the tick length of its last step that did not end at the
   // target (that one may be cut short), 0: none yet

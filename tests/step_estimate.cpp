@@ -39,7 +39,7 @@ int main() {
   std::printf("next_target %d\n", e.steps(in, 2.0, 8));
   std::printf("first_instance_again %d\n", e.steps(in, 1.5, 8));
   e.reset(2);
-  std::printf("after_an_upload %d\n", e.steps(in, 2.0, 8));
+  std::printf("bound_anew %d\n", e.steps(in, 2.0, 8));
   in[0] = at(2.0, 0.0, false);
   in[1] = at(2.0, 0.0, false);
   std::printf("nothing_to_do %d\n", e.steps(in, 2.0, 8));

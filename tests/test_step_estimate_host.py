@@ -1,6 +1,6 @@
 """How many global steps are queued between two status reads
 (tests/step_estimate.cpp, built with g++; no GPU): as many as the instance
-furthest behind needs by the steps of this state, whichever instance that is."""
+furthest behind needs by the steps taken so far, whichever instance that is."""
 import os
 import shutil
 import subprocess
@@ -23,4 +23,4 @@ def test_steps_queued_in_named_situations(tmp_path):
     got = {name: int(n) for name, n in (ln.split() for ln in out.strip().splitlines())}
     assert got == {"no_step_yet": 1, "furthest_behind": 7, "limited": 8, "inside_one_step": 2,
                    "first_instance_done": 4, "next_target": 8, "first_instance_again": 4,
-                   "after_an_upload": 1, "nothing_to_do": 1}
+                   "bound_anew": 1, "nothing_to_do": 1}
