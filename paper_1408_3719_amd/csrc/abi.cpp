@@ -799,6 +799,7 @@ int ader_bind_workspace(ader_ctx* c, void* dev_ptr, size_t bytes) {
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
       c->dev.n_cu = ncu;
   }
+  c->dev.staged = aw::named_elements(c->topo, aw::recon_share(c->topo.NE, c->dev.n_cu)) <= aw::STAGED_NAMES;
   const aw::Topology& t = c->topo;
   aw::Dev& d = c->dev;
   const size_t NE = t.NE, NV = t.NV, NF = t.NF;

@@ -135,6 +135,7 @@ struct Dev {
   // workgroups per CU of the node and patch launches, which sweep every node
   // and edge (0: one grid over all of them; else a persistent grid striding them)
   int sweep_wg_per_cu;
+  int staged;       // reconstruction with the stencil elements of a workgroup placed once, in LDS
   int free_steps;   // 1: free local steps (one macro step of FREE_TICKS to the target)
   Scal* scal;
   Inst* inst;                        // [K]
@@ -309,6 +310,29 @@ int launch_lts_out(const Dev& d, const LtsWork& w, double* Qbar, double* Xbar, v
 // tables, F and out [n][10][6]; blocks <= 0: one block per 40 elements.
 int probe_contraction(const Tables* tab, int use_mfma, long n, int iters, const double* F, double* out,
                       void* stream, int blocks);
+
+// Elements per workgroup of a reconstruction over n elements, a multiple of 4:
+// all 32 lane groups when the launch fills the chip twice over, else fewer, so
+// that a short list still spreads over every CU.
+constexpr int recon_share(int n, int n_cu) {
+  const int spread = 2 * (n_cu > 0 ? n_cu : 256);
+  const int per = ((n + spread - 1) / spread + 3) & ~3;
+  return per < 4 ? 4 : (per > 32 ? 32 : per);
+}
+// Most elements that a workgroup's share may name, on average over the mesh, for
+// the staged reconstruction; with more, every lane places its own rows. A whole
+// step with either (us; names: 32 elements unless noted), vortex or explosion,
+// elements numbered along a curve, in rows of the mesh, in runs of n from the
+// curve in random order, at random:
+//   M=1 150k, global: curve (146) 215 staged, 276 direct; runs of 8 (302) 256, 291;
+//     rows (319) 305, 284; random (953) 589, 369
+//   M=2 80k, 3 levels: curve (222) 763, 839; runs of 32 (251) 818, 844; of 16 (397)
+//     848, 849; rows (513) 908, 854; random (2,065) 2,137, 1,044
+//   M=2 400k, 4 levels: curve (226) 2,385, 2,685; runs of 16 (343) 2,978, 2,898;
+//     random (2,102) 6,540, 3,907
+//   M=3 7k, 3 levels, 16 elements: curve (237) 581, 613; 13.5k, 28 elements: curve
+//     (294) 726, 714; 20k: curve (306) 834, 761, random (3,267) 2,502, 823
+constexpr int STAGED_NAMES = 300;
 
 // Kernel launchers (kernels.hip).  All launch on `stream`, return a
 // hipError_t as int.

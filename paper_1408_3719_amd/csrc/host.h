@@ -35,6 +35,10 @@ struct Topology {
 void build_topology(int M, int n_nodes, const double* xy, int n_elems, const int* tri,
                     int n_bedges, const int* bedge, Topology& t);
 
+// Mean number of different elements that the stencils and face neighbours of
+// `group` consecutive elements name, over at most 64 such groups spread over the mesh.
+double named_elements(const Topology& t, int group);
+
 // Is an instance at time T short of the target time (the test that the device
 // applies too)?
 inline bool short_of_target(double T, double t_target) {

@@ -23,7 +23,8 @@
 // (independent meshes) keep their own time and tick length (Inst).
 //
 // Lane mappings (64-wide wavefronts):
-//   k_reconstruct: 8 lanes per element, lane s solves stencil s (s < 7); the
+//   k_reconstruct: 8 lanes per element, lane s solves stencil s (s < 7); where
+//                  the numbering lets consecutive elements share them, the
 //                  stencil elements of a workgroup are placed once, in LDS; the
 //                  CFL step and the WENO sum go over the 8 lanes.
 //   k_predict:     nb lanes per element, floor(64/nb) elements per wavefront,
@@ -466,6 +467,11 @@ __device__ inline double group8_sum(double v) {
 // triangles, M=1 13.3 -> 7.5 us. Now bound by FP64 issue in the least squares
 // (10k of 34k cycles of a workgroup) and the latency of the phases before it
 // (index loads, hash table, placing: 17k) at two workgroups per CU.
+// All this rests on consecutive elements naming the same ones. On a mesh
+// numbered in another way a round of 32 does not fit, and what is hashed, thrown
+// away and placed for a few lanes costs more than the staging saves: there every
+// lane places its own rows (STAGED = false), the same arithmetic on the same data
+// in the same order. STAGED_NAMES (common.h) has the line between the two.
 template <int M>
 struct Stage {
   static constexpr int CAP = M == 1 ? 448 : 640;   // placed elements a round holds (80 bytes each)
@@ -478,84 +484,81 @@ struct Stage {
 
 constexpr unsigned long long NO_KEY = ~0ull;
 
-template <int M>
+template <int M, bool STAGED>
 __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruct(Dev d, const Tables* __restrict__ tb, Params P,
                                                      int list, int set_level) {
   using S = Sz<M>;
   using G = Stage<M>;
   const bool use_list = list >= 0;
   constexpr int nb = S::nb, ne = S::ne, nu = S::nu, WS = S::WS, NR = ne - 1;
-  __shared__ unsigned long long key[G::TAB];      // tick << 32 | element
-  __shared__ unsigned short slot_of[G::TAB], entry[G::CAP];
-  __shared__ double2 placed[G::CAP * 5];          // x0 y0 x1 y1 x2 y2 Q0..Q3
+  constexpr int TAB = STAGED ? G::TAB : 1, CAP = STAGED ? G::CAP : 1;
+  __shared__ unsigned long long key[TAB];      // tick << 32 | element
+  __shared__ unsigned short slot_of[TAB], entry[CAP];
+  __shared__ double2 placed[CAP * 5];          // x0 y0 x1 y1 x2 y2 Q0..Q3
   __shared__ int count;
   const int NE = d.NE;
   const int nitems = use_list ? d.scal->lists[list].n_active : NE;
   // the cycle's stamp has served its last reader (the update)
   if (use_list && blockIdx.x == 0 && threadIdx.x == 0) d.scal->cycle += 1;
   const int tid = threadIdx.x, sl = tid & 7, grp = tid >> 3;
-  // elements per workgroup: all 32 lane groups when the launch fills the chip
-  // twice over, else fewer, so that a short list still spreads over every CU
-  const int spread = 2 * (d.n_cu > 0 ? d.n_cu : 256);
-  int per = ((nitems + spread - 1) / spread + 3) & ~3;
-  per = per < 4 ? 4 : (per > TPB / 8 ? TPB / 8 : per);
+  const int per = recon_share(nitems, d.n_cu);
   const int nwork = (nitems + per - 1) / per;
   for (int wg = xcd_block(nwork); wg < nwork; wg += gridDim.x) {
     const int first = wg * per, last = min(nitems, first + per);
     int round = per;
     for (int base = first; base < last;) {
-      for (int t = tid; t < G::TAB; t += TPB) key[t] = NO_KEY;
-      if (tid == 0) count = 0;
-      __syncthreads();
       const int idx = base + grp;
       const bool mine = grp < round && idx < last;
       int i = 0, nt = 0;
-      bool valid = false;
-      int at[NR];      // table entry of each row (lane 7: of the face neighbours)
-      {
-        int j[NR];
+      bool valid = false, ok = true;
+      int at[NR];      // element of each row (lane 7: the face neighbours), when staged its slot
 #pragma unroll
-        for (int c = 0; c < NR; ++c) j[c] = -1;
-        if (mine) {
-          i = use_list ? d.act_list[idx] : idx;
-          nt = d.ts[i].tick;
-          if (sl < NSTEN) {
-            const int* sidx = d.sten + size_t(sl * ne) * NE + i;   // row c at sidx[c * NE]
+      for (int c = 0; c < NR; ++c) at[c] = -1;
+      if (mine) {
+        i = use_list ? d.act_list[idx] : idx;
+        nt = d.ts[i].tick;
+        if (sl < NSTEN) {
+          const int* sidx = d.sten + size_t(sl * ne) * NE + i;   // row c at sidx[c * NE]
 #pragma unroll
-            for (int c = 0; c < NR; ++c) j[c] = sidx[(c + 1) * NE];   // -1 in a dropped sector
-          } else {
+          for (int c = 0; c < NR; ++c) at[c] = sidx[(c + 1) * NE];   // -1 in a dropped sector
+        } else {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) j[k] = d.neigh[k * NE + i];
-          }
+          for (int k = 0; k < 3; ++k) at[k] = d.neigh[k * NE + i];
         }
-        valid = sl < NSTEN && j[0] >= 0;
+      }
+      valid = sl < NSTEN && at[0] >= 0;
+      if constexpr (STAGED) {
+        for (int t = tid; t < TAB; t += TPB) key[t] = NO_KEY;
+        if (tid == 0) count = 0;
+        __syncthreads();
         const unsigned long long hi = (unsigned long long)(unsigned)nt << 32;
         // The probes of all rows go out together (one LDS round trip for all of
         // them), again and again until every row has found or made its entry;
         // new entries take slots in the list. Ends: a table without a free entry
         // holds TAB > CAP of them, each counted by its maker without waiting for
         // a thread that still probes.
+        int pos[NR];   // table entry
         unsigned pend = 0;
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
-          at[c] = int(((unsigned)j[c] * 2654435761u ^ (unsigned)nt * 40503u) >> 16) & (G::TAB - 1);
-          if (j[c] >= 0) pend |= 1u << c;
+          pos[c] = int(((unsigned)at[c] * 2654435761u ^ (unsigned)nt * 40503u) >> 16) & (TAB - 1);
+          if (at[c] >= 0) pend |= 1u << c;
         }
         while (pend) {
           unsigned long long old[NR];
 #pragma unroll
           for (int c = 0; c < NR; ++c) {
-            old[c] = hi | (unsigned)j[c];
-            if (pend >> c & 1) old[c] = atomicCAS(&key[at[c]], NO_KEY, old[c]);
+            old[c] = hi | (unsigned)at[c];
+            if (pend >> c & 1) old[c] = atomicCAS(&key[pos[c]], NO_KEY, old[c]);
           }
           unsigned won = 0, next = 0;
 #pragma unroll
           for (int c = 0; c < NR; ++c) {
             if (old[c] == NO_KEY)
               won |= 1u << c;
-            else if (old[c] != (hi | (unsigned)j[c])) {
+            else if (old[c] != (hi | (unsigned)at[c])) {
               next |= 1u << c;
-              at[c] = (at[c] + 1) & (G::TAB - 1);
+              pos[c] = (pos[c] + 1) & (TAB - 1);
             }
           }
           pend = next;
@@ -564,53 +567,57 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
 #pragma unroll
             for (int c = 0; c < NR; ++c)
               if (won >> c & 1) {
-                if (slot < G::CAP) {
-                  entry[slot] = (unsigned short)at[c];
-                  slot_of[at[c]] = (unsigned short)slot;
+                if (slot < CAP) {
+                  entry[slot] = (unsigned short)pos[c];
+                  slot_of[pos[c]] = (unsigned short)slot;
                 }
                 ++slot;
               }
           }
-          if (pend && __atomic_load_n(&count, __ATOMIC_RELAXED) > G::CAP) pend = 0;
+          if (pend && __atomic_load_n(&count, __ATOMIC_RELAXED) > CAP) pend = 0;
         }
-      }
-      __syncthreads();
-      const int n = count;
-      if (n > G::CAP) {   // elements far apart (few rows in common): smaller rounds
         __syncthreads();
-        round = max(round / 2, G::SUB);
-        continue;
-      }
-      bool ok = true;
-      for (int s = tid; s < n; s += TPB) {
-        const unsigned long long k = key[entry[s]];
-        const int j = int(k & 0xffffffffull);
-        double X[6], Q[4];
-        ok &= project<M>(d, tb, j, int(k >> 32), elem_delta(d, j), X, Q);
-        double2* o = placed + s * 5;
+        const int n = count;
+        if (n > CAP) {   // elements far apart (few rows in common): smaller rounds
+          __syncthreads();
+          round = max(round / 2, G::SUB);
+          continue;
+        }
+        for (int s = tid; s < n; s += TPB) {
+          const unsigned long long k = key[entry[s]];
+          const int j = int(k & 0xffffffffull);
+          double X[6], Q[4];
+          ok &= project<M>(d, tb, j, int(k >> 32), elem_delta(d, j), X, Q);
+          double2* o = placed + s * 5;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) o[c] = make_double2(X[2 * c], X[2 * c + 1]);
-        o[3] = make_double2(Q[0], Q[1]);
-        o[4] = make_double2(Q[2], Q[3]);
-      }
-      if (!ok) set_err(d, ERR_PRED);
+          for (int c = 0; c < 3; ++c) o[c] = make_double2(X[2 * c], X[2 * c + 1]);
+          o[3] = make_double2(Q[0], Q[1]);
+          o[4] = make_double2(Q[2], Q[3]);
+        }
 #pragma unroll
-      for (int c = 0; c < NR; ++c) at[c] = slot_of[at[c]];
-      __syncthreads();
+        for (int c = 0; c < NR; ++c) at[c] = slot_of[pos[c]];
+        __syncthreads();
+      }
       if (mine) {
-        auto stencil_element = [&](int slot, double X[6], double Q[4]) {
-          const double2* o = placed + slot * 5;
+        const double delta = elem_delta(d, i);
+        // vertices and average of a stencil element: at a slot, or element j placed now
+        auto stencil_element = [&](int j, double X[6], double Q[4]) {
+          if constexpr (STAGED) {
+            const double2* o = placed + j * 5;
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const double2 v = o[c];
-            X[2 * c] = v.x;
-            X[2 * c + 1] = v.y;
+            for (int c = 0; c < 3; ++c) {
+              const double2 v = o[c];
+              X[2 * c] = v.x;
+              X[2 * c + 1] = v.y;
+            }
+            const double2 q0 = o[3], q1 = o[4];
+            Q[0] = q0.x;
+            Q[1] = q0.y;
+            Q[2] = q1.x;
+            Q[3] = q1.y;
+          } else {
+            ok &= project<M>(d, tb, j, nt, delta, X, Q);
           }
-          const double2 q0 = o[3], q1 = o[4];
-          Q[0] = q0.x;
-          Q[1] = q0.y;
-          Q[2] = q1.x;
-          Q[3] = q1.y;
         };
         const double* ri = rec<M>(d, i);
         double Xi[6], Qi[4];
@@ -758,14 +765,15 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
               d.ts[i].step = 0;
             } else {
               int over;
-              const int own = level_step(dt, elem_delta(d, i), N, nt, d.free_steps, &over);
-              d.ts[i].step = take_step(d, i, own, nt, N, dt, elem_delta(d, i), &over);
+              const int own = level_step(dt, delta, N, nt, d.free_steps, &over);
+              d.ts[i].step = take_step(d, i, own, nt, N, dt, delta, &over);
               if (over) atomicAdd(&d.scal->overshoots, 1ull);
             }
           }
         }
       }
-      __syncthreads();   // the next round clears the table
+      if (!ok) set_err(d, ERR_PRED);
+      if constexpr (STAGED) __syncthreads();   // the next round clears the table
       base += round;
     }
   }
@@ -2089,7 +2097,12 @@ int launch_reconstruct(const Dev& d, const Params& p, int M, int list, int set_l
   const long full = (8L * d.NE + TPB - 1) / TPB, spread = 2L * (d.n_cu > 0 ? d.n_cu : 256);
   const long small = (long(d.NE) + 3) / 4;
   const int g = list_grid(d, std::max(full, std::min(small, spread)), list >= 0);
-  AW_DISPATCH(M, AW_LAUNCH_G(k_reconstruct<MM>, g, s, d, d.tab, p, list, set_level));
+  AW_DISPATCH(M, {
+    if (d.staged)
+      AW_LAUNCH_G((k_reconstruct<MM, true>), g, s, d, d.tab, p, list, set_level);
+    else
+      AW_LAUNCH_G((k_reconstruct<MM, false>), g, s, d, d.tab, p, list, set_level);
+  });
   return 0;
 }
 

@@ -318,4 +318,22 @@ void build_topology(int M, int NV, const double* xy, int NE, const int* tri_in, 
       }
 }
 
+double named_elements(const Topology& t, int group) {
+  const int groups = (t.NE + group - 1) / group, step = std::max(1, groups / 64);
+  std::vector<int> mark(t.NE, -1);
+  long named = 0, taken = 0;
+  for (int g = 0; g < groups; g += step, ++taken)
+    for (int i = g * group; i < std::min(t.NE, (g + 1) * group); ++i) {
+      auto name = [&](int j) {
+        if (j < 0 || mark[j] == g) return;
+        mark[j] = g;
+        ++named;
+      };
+      for (int s = 0; s < NSTEN; ++s)
+        for (int c = 1; c < t.ne; ++c) name(t.sten[(size_t(i) * NSTEN + s) * t.ne + c]);
+      for (int k = 0; k < 3; ++k) name(t.neigh[3 * i + k]);
+    }
+  return double(named) / double(std::max(1L, taken));
+}
+
 }  // namespace aw
