@@ -369,9 +369,11 @@ int ader_adjoint_lagrangian_step(ader_ctx* ctx, double dt, const double* Q_dev, 
  * as ader_step_lts would leave it.
  *   Qbar_dev, Qbar0_dev: device [4][n_elems] SoA; Xbar_dev, Xbar0_dev:
  *   device [n_nodes][2]; no output may overlap an input.
- * Memory (allocated by the library; what fits in 1/16 of the device's memory
- * and 1/8 of its free memory stays with the context for the next such call,
- * until ader_destroy, the rest is freed before returning): for the last
+ * Memory (allocated by the library; what fits in 1/8 of the device's free
+ * memory and, with what other contexts of the process keep, in 1/16 of its
+ * whole memory stays with the context for the next such call, until
+ * ader_release_memory or ader_destroy, or until memory runs short in a call on
+ * this context; the rest is freed before returning): for the last
  * keep_macro_steps macro steps (-1: as many as 60% of the free device memory
  * holds, counting 2^(L-1) + 3 states each) the forward keeps the state the
  * reverse sweep reads (ticks, element records, traces, reconstructions, node
@@ -384,6 +386,10 @@ int ader_adjoint_lagrangian_step(ader_ctx* ctx, double dt, const double* Q_dev, 
  * forward run's own errors as ader_step_lts. */
 int ader_adjoint_lts(ader_ctx* ctx, int32_t n_macro, int32_t keep_macro_steps, double t_end, const double* Qbar_dev,
                      const double* Xbar_dev, double* Qbar0_dev, double* Xbar0_dev, int32_t* n_done);
+
+/* Frees the device memory that ader_adjoint_lts left with the context (none:
+ * nothing happens); the next such call allocates again. */
+int ader_release_memory(ader_ctx* ctx);
 
 /* ---- Measurement: the predictor's derivative contraction -----------------
  * Not a step of the scheme: runs, in one timed launch on the context's

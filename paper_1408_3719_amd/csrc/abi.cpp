@@ -3,6 +3,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <stdexcept>
@@ -42,8 +43,9 @@ struct ader_ctx {
   double* delta_buf = nullptr;     // tick-length replay
   int* rec_buf = nullptr;          // schedule record: steps, then positions
   double* rec_delta_buf = nullptr; // schedule record: tick lengths
-  // device blocks the last LTS adjoint left for the next one (Blocks)
+  // device blocks the last LTS adjoint left for the next one (Blocks), on this device
   std::vector<std::pair<char*, size_t>> adj_blocks;
+  int device = 0;
   // status report of the device (Scal, then the instances) in pinned host memory;
   // fresh while nothing has been queued that changes them
   char* rep = nullptr;
@@ -164,6 +166,40 @@ std::vector<T> to_soa(const std::vector<T>& aos, size_t n, size_t f) {
 int h2d(ader_ctx* c, const void* dst, const void* src, size_t bytes) {
   HIPCHK(c, hipMemcpyAsync(const_cast<void*>(dst), src, bytes, hipMemcpyHostToDevice, c->stream));
   return 0;
+}
+
+// Bytes of the blocks that the contexts of this process keep between LTS adjoints
+// (ader_ctx::adj_blocks), per device.
+std::atomic<size_t> g_kept[64];
+std::atomic<size_t>& kept_bytes(const ader_ctx* c) { return g_kept[unsigned(c->device) % 64]; }
+
+// Room for `bytes` more among them, `limit` in all: taken, or false.
+bool claim_kept(ader_ctx* c, size_t bytes, size_t limit) {
+  std::atomic<size_t>& kept = kept_bytes(c);
+  size_t now = kept.load();
+  do {
+    if (now + bytes > limit) return false;
+  } while (!kept.compare_exchange_weak(now, now + bytes));
+  return true;
+}
+
+void free_adj_blocks(ader_ctx* c) {
+  for (const auto& b : c->adj_blocks) {
+    (void)hipFree(b.first);
+    kept_bytes(c) -= b.second;
+  }
+  c->adj_blocks.clear();
+}
+
+// hipMalloc; when memory is short, after the blocks that this context keeps.
+hipError_t device_alloc(ader_ctx* c, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && !c->adj_blocks.empty()) {
+    (void)hipGetLastError();
+    free_adj_blocks(c);
+    e = hipMalloc(p, bytes);
+  }
+  return e;
 }
 
 // Fold finished event pairs into the per-kernel totals (stream synchronised).
@@ -798,6 +834,8 @@ int ader_bind_workspace(ader_ctx* c, void* dev_ptr, size_t bytes) {
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
       c->dev.n_cu = ncu;
+    if (dev != c->device) free_adj_blocks(c);
+    c->device = dev;
   }
   c->dev.staged = aw::named_elements(c->topo, aw::recon_share(c->topo.NE, c->dev.n_cu)) <= aw::STAGED_NAMES;
   const aw::Topology& t = c->topo;
@@ -1092,7 +1130,7 @@ int ader_autotune(ader_ctx* c, int32_t trials, ader_tune* chosen) {
   const int64_t cycles = c->cycles, macro = c->macro_steps;
   set_free(c, false);
   void* snap = nullptr;
-  HIPCHK(c, hipMalloc(&snap, c->ws_bytes));
+  HIPCHK(c, device_alloc(c, &snap, c->ws_bytes));
   c->prof = false;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int r = 0;
@@ -1386,16 +1424,12 @@ aw::LtsView view_at(const ader_ctx* c, const char* saved) {
   return v;
 }
 
-void free_adj_blocks(ader_ctx* c) {
-  for (const auto& b : c->adj_blocks) (void)hipFree(b.first);
-  c->adj_blocks.clear();
-}
-
 // Device memory of one LTS adjoint call. Blocks come from those the context
 // kept from its last call when one of about the size is there, else from
 // hipMalloc; small pieces are handed out in order from a chunk. give_back()
-// leaves the blocks with the context, as many as fit in 1/16 of the device's
-// memory and 1/8 of what is free of it, and frees the others. Allocating and
+// leaves the blocks with the context, as many as fit in 1/8 of the device's free
+// memory and, with those that the process's other contexts keep, in 1/16 of its
+// whole memory, and frees the others. Allocating and
 // freeing the 1.9 GB of a call (4 macro steps at 37.8k elements, M=2) each time
 // is cheap only until a process has passed the whole memory once: from then on
 // the driver clears the pages before it hands them out again, and the call took
@@ -1414,16 +1448,11 @@ struct Blocks {
         best = i;
     if (best < k.size()) {
       used.push_back(k[best]);
+      kept_bytes(c) -= k[best].second;
       k.erase(k.begin() + best);
     } else {
       char* p = nullptr;
-      hipError_t e = hipMalloc((void**)&p, bytes);
-      if (e == hipErrorOutOfMemory && !k.empty()) {
-        (void)hipGetLastError();
-        free_adj_blocks(c);
-        e = hipMalloc((void**)&p, bytes);
-      }
-      HIPCHK(c, e);
+      HIPCHK(c, device_alloc(c, (void**)&p, bytes));
       used.push_back({p, bytes});
     }
     *out = used.back().first;
@@ -1447,9 +1476,8 @@ struct Blocks {
     size_t free_b = 0, total_b = 0, held = 0;
     free_adj_blocks(c);   // not needed by this call
     if (!keep || hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = total_b = 0;
-    const size_t limit = std::min(total_b / 16, free_b / 8);
     for (const auto& u : used) {
-      if (held + u.second <= limit) {
+      if (held + u.second <= free_b / 8 && claim_kept(c, u.second, total_b / 16)) {
         held += u.second;
         c->adj_blocks.push_back(u);
       } else {
@@ -1652,6 +1680,12 @@ int ader_adjoint_lts(ader_ctx* c, int32_t n_macro, int32_t keep_macro_steps, dou
   return ADER_OK;
 }
 
+int ader_release_memory(ader_ctx* c) {
+  if (!c) return ADER_E_ARG;
+  free_adj_blocks(c);
+  return ADER_OK;
+}
+
 int ader_probe_contraction(ader_ctx* c, int32_t use_mfma, int64_t n_elems, int32_t iters, const double* F_dev,
                            double* out_dev, float* ms) {
   if (!c || !F_dev || !out_dev || n_elems <= 0 || n_elems > INT32_MAX || iters < 1) return ADER_E_ARG;
@@ -1696,7 +1730,7 @@ int ader_set_schedule_replay(ader_ctx* c, const int32_t* step_ptr, const int32_t
   drop_graphs(c);              // graphs hold the launch arguments they were captured with
   if (!step_ptr) return ADER_OK;
   const size_t words = (NE + 1) + size_t(n_steps) + NE;
-  HIPCHK(c, hipMalloc(&c->replay_buf, words * sizeof(int)));
+  HIPCHK(c, device_alloc(c, (void**)&c->replay_buf, words * sizeof(int)));
   std::vector<int> host(words, 0);
   std::memcpy(host.data(), step_ptr, (NE + 1) * sizeof(int));
   if (n_steps) std::memcpy(host.data() + NE + 1, steps, size_t(n_steps) * sizeof(int));
@@ -1747,7 +1781,7 @@ int ader_set_delta_replay(ader_ctx* c, const double* deltas, int32_t n) {
   c->dev.replay_delta_n = 0;
   drop_graphs(c);
   if (n == 0) return ADER_OK;
-  HIPCHK(c, hipMalloc(&c->delta_buf, size_t(n) * sizeof(double)));
+  HIPCHK(c, device_alloc(c, (void**)&c->delta_buf, size_t(n) * sizeof(double)));
   HIPCHK(c, hipMemcpyAsync(c->delta_buf, deltas, size_t(n) * sizeof(double), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->dev.replay_delta = c->delta_buf;
@@ -1773,10 +1807,10 @@ int ader_set_schedule_record(ader_ctx* c, int32_t steps_per_element, int32_t mac
   drop_graphs(c);
   if (steps_per_element == 0) return ADER_OK;
   const size_t NE = c->topo.NE;
-  HIPCHK(c, hipMalloc(&c->rec_buf, (NE * size_t(steps_per_element) + NE) * sizeof(int)));
+  HIPCHK(c, device_alloc(c, (void**)&c->rec_buf, (NE * size_t(steps_per_element) + NE) * sizeof(int)));
   HIPCHK(c, hipMemsetAsync(c->rec_buf + NE * size_t(steps_per_element), 0, NE * sizeof(int), c->stream));
   const size_t nd = size_t(macro_steps > 0 ? macro_steps : 1);
-  HIPCHK(c, hipMalloc(&c->rec_delta_buf, nd * sizeof(double)));
+  HIPCHK(c, device_alloc(c, (void**)&c->rec_delta_buf, nd * sizeof(double)));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   d.rec_steps = c->rec_buf;
   d.rec_pos = c->rec_buf + NE * size_t(steps_per_element);

@@ -258,6 +258,10 @@ class Solver(_Base):
             ctypes.c_void_p(q0.data_ptr()), ctypes.c_void_p(x0.data_ptr()), ctypes.byref(done)))
         return q0, x0, done.value
 
+    def release_memory(self):
+        """Give back the device memory that adjoint_lts keeps for its next call."""
+        _check(self.lib, self.ctx, self.lib.ader_release_memory(self.ctx))
+
     def probe_contraction(self, F, iters: int, use_mfma: bool):
         """Time `iters` rounds of the predictor's derivative contraction on the
         fields F (device tensor [n][10][6]) on the vector ALUs or the matrix
