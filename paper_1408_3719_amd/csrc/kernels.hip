@@ -2137,9 +2137,10 @@ int launch_sched(const Dev& d, int list, bool whole, void* s) {
   // least one pass of SCHED_TPB / 8 elements. Each block reserves its list space
   // with one atomic, and atomics on one address take ~12 ns each, so no more
   // blocks than fill the chip: one per CU while that leaves a block up to 4
-  // passes, two beyond (75k elements, M=2: 1024 blocks 13.2 us, 512 11.4, 256
-  // 10.7, 128 15.3; 302k: 30.5, 30.1, 43.6 with 296 blocks).
-  const int fill = d.NE > 256 * 4 * (SCHED_TPB / 8) ? 512 : 256;
+  // passes, two beyond (256 CUs; 75k elements, M=2: 1024 blocks 13.2 us, 512 11.4,
+  // 256 10.7, 128 15.3; 302k: 1024 blocks 30.5, 512 30.1, 296 43.6).
+  const int cu = d.n_cu > 0 ? d.n_cu : 256, passes = 4;
+  const int fill = d.NE > cu * passes * (SCHED_TPB / 8) ? 2 * cu : cu;
   int chunk = d.sched_chunk > 0 ? d.sched_chunk : (d.NE + fill - 1) / fill;
   chunk = chunk < SCHED_TPB / 8 ? SCHED_TPB / 8 : (chunk > SCHED_CHUNK ? SCHED_CHUNK : chunk);
   if (whole) chunk = SCHED_CHUNK;
