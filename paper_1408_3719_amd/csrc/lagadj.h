@@ -143,18 +143,21 @@ struct FluxSide {
     F[2] = q[2] * un + p * N[1];
     F[3] = q[3] * un + p * U;
   }
-  // qb, Nb += the product of (w, unb, cnb) with the Jacobian of (F~ . N, un, c |N_xy|)
+  // qb, Nb += the product of (w, unb, cnb) with the Jacobian of (F~ . N, un, c |N_xy|).
+  // With cnb = 0 the sound speed plays no part: a predicted trace may have a
+  // pressure below zero, and the flux then takes the other side's speed.
   AWHD inline void vjp(const double q[4], const double N[3], double nxy, double inxy, double gam, const double w[4],
                        double unb, double cnb, double qb[4], double Nb[3]) const {
     const double wq = w[0] * q[0] + w[1] * q[1] + w[2] * q[2] + w[3] * q[3];
     const double Ub = wq + p * w[3] + unb, gm = gam - 1.0;
+    const bool speed = cnb != 0.0;
     const double ch = 0.5 * cnb * nxy;   // half the adjoint of c = sqrt(gam p / rho)
-    const double pb = gm * (w[1] * N[0] + w[2] * N[1] + w[3] * U + (ch != 0.0 ? ch * gam * ir * rcp(c) : 0.0));
-    qb[0] += w[0] * un - U * ir * Ub + k * pb - ch * c * ir;
+    const double pb = gm * (w[1] * N[0] + w[2] * N[1] + w[3] * U + (speed ? ch * gam * ir * rcp(c) : 0.0));
+    qb[0] += w[0] * un - U * ir * Ub + k * pb - (speed ? ch * c * ir : 0.0);
     qb[1] += w[1] * un + N[0] * ir * Ub - u * pb;
     qb[2] += w[2] * un + N[1] * ir * Ub - v * pb;
     qb[3] += w[3] * un + pb;
-    const double cn = cnb * c * inxy;
+    const double cn = speed ? cnb * c * inxy : 0.0;
     Nb[0] += u * Ub + p * w[1] + cn * N[0];
     Nb[1] += v * Ub + p * w[2] + cn * N[1];
     Nb[2] += wq + unb;
