@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "common.h"
+
 namespace aw {
 // internal linkage: each kernel file folds these constants into its own code
 namespace {
@@ -184,15 +186,6 @@ __device__ inline void monomial_means(const double x[3], const double y[3], doub
       mm[9] = (sy * (syy + 3.0 * p02) + 2.0 * p03) * sixtieth;
     }
   }
-}
-
-// 1/x to rounding for normal x away from the ends of the range: the hardware
-// estimate and two Newton steps, without the scaling a general division adds.
-__device__ inline double rcp_newton(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = r + r * (1.0 - x * r);
-  r = r + r * (1.0 - x * r);
-  return r;
 }
 
 // Least squares of a stencil by Householder reflections over blocks of rows

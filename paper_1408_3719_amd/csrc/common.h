@@ -311,6 +311,19 @@ int launch_lts_out(const Dev& d, const LtsWork& w, double* Qbar, double* Xbar, v
 int probe_contraction(const Tables* tab, int use_mfma, long n, int iters, const double* F, double* out,
                       void* stream, int blocks);
 
+#if defined(__HIPCC__)
+// 1/x to rounding for normal x away from the ends of the range: the hardware
+// estimate and two Newton steps, without the scaling a general division adds
+// against overflow. 0, infinity and subnormal x give NaN; densities, pressures,
+// areas and normals in use are none of these.
+__device__ inline double rcp_newton(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = r + r * (1.0 - x * r);
+  r = r + r * (1.0 - x * r);
+  return r;
+}
+#endif
+
 // Elements per workgroup of a reconstruction over n elements, a multiple of 4:
 // all 32 lane groups when the launch fills the chip twice over, else fewer, so
 // that a short list still spreads over every CU.

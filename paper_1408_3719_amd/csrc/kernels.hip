@@ -1546,7 +1546,7 @@ __global__ void __launch_bounds__(TPB, 2) k_patch(Dev d, const Tables* __restric
 #pragma unroll
       for (int k = 0; k < 3; ++k) Nn[k] += Nr[k];
     }
-        // inflow-positive memory variables: the flux leaves L and enters R
+    // inflow-positive memory variables: the flux leaves L and enters R
 #pragma unroll
     for (int v = 0; v < 4; ++v) sl[v] = mL[v] - G[v];
 #pragma unroll

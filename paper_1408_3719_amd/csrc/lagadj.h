@@ -70,14 +70,10 @@ AWHD inline void tint01(const Tables& tb, double I[M + 1]) {
   }
 }
 
-// 1/x to rounding, and 1/sqrt(x). On the device the reciprocal is the hardware's
-// estimate with two Newton steps: a general division also scales its operands
-// against overflow, which the densities, pressures and normals here do not need.
+// 1/x to rounding, and 1/sqrt(x).
 AWHD inline double rcp(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  double r = __builtin_amdgcn_rcp(x);
-  r = r + r * (1.0 - x * r);
-  return r + r * (1.0 - x * r);
+  return rcp_newton(x);
 #else
   return 1.0 / x;
 #endif
