@@ -55,12 +55,12 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_1408_3719_amd", "csrc", n) for n in 
 TRAFFIC_SWEEP = (0, 4, 8, 16, 32)
 MEASURED_TRAFFIC = {
     "workload": "explosion",
-    "source_sha256": "9a8b6ba5a837561b330d64f70a288df398708a542e0cd68f2993f1ee46cb8014",
-    "k_reconstruct": {0: 1552, 4: 1606, 8: 1583, 16: 1564, 32: 1557},
-    "k_predict": {0: 1501, 4: 1502, 8: 1502, 16: 1502, 32: 1502},
-    "k_patch": {0: 1042, 4: 1072, 8: 1048, 16: 1042, 32: 1042},
-    "k_update": {0: 724, 4: 726, 8: 724, 16: 724, 32: 724},
-    "k_node": {w: 1775 for w in TRAFFIC_SWEEP},
+    "source_sha256": "d534fb55d41b8127e39eaf3b8270ef04926d4e2676a7b50ce1577ba498689c4b",
+    "k_reconstruct": {0: 1478, 4: 1513, 8: 1500, 16: 1488, 32: 1480},
+    "k_predict": {0: 1502, 4: 1504, 8: 1503, 16: 1502, 32: 1502},
+    "k_patch": {0: 1053, 4: 1092, 8: 1063, 16: 1054, 32: 1054},
+    "k_update": {0: 743, 4: 745, 8: 743, 16: 743, 32: 743},
+    "k_node": {w: 1412 for w in TRAFFIC_SWEEP},
     "k_sched": {w: 88 for w in TRAFFIC_SWEEP},
 }
 
