@@ -118,7 +118,10 @@ int ader_create(const ader_config* cfg, void* hip_stream, ader_ctx** out);
  * clockwise or degenerate triangle, a non-manifold edge, a boundary list
  * that does not match the mesh, or a mesh too small for the central stencil.
  * ADER_E_ARG on an empty mesh or n_elems * n_e * 8 >= 2^31 (32-bit indices of
- * the stencil rows: 13.4 M triangles at M = 3, 22 M at M = 2). */
+ * the stencil rows: 13.4 M triangles at M = 3, 22 M at M = 2).
+ * Any numbering gives the same scheme; elements and nodes that are close in
+ * space should be close in number (along a space-filling curve, say): steps
+ * are then 1.4 to 1.7 times as fast as with a random numbering. */
 int ader_upload_mesh(ader_ctx* ctx, int32_t n_nodes, const double* node_xy,
                      int32_t n_elems, const int32_t* tri,
                      int32_t n_bedges, const int32_t* bedge);
@@ -158,7 +161,8 @@ int ader_upload_state(ader_ctx* ctx, const double* Q_dev, double t0);
 int ader_upload_state_xy(ader_ctx* ctx, const double* Q_dev, const double* node_xy_dev, double t0);
 
 /* Global time stepping up to t_target (at most max_steps steps; <= 0 means
- * no limit): one level, every element updates in every step. */
+ * no limit): one level, every element updates in every step.  After an error
+ * the state, times and statistics are those of the step that failed. */
 int ader_step_gts(ader_ctx* ctx, double t_target, int32_t max_steps, ader_stats* st);
 
 /* Local time stepping up to t_target in at most max_macro_steps macro steps

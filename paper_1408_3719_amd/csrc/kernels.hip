@@ -463,7 +463,7 @@ __device__ inline double group8_sum(double v) {
 // from LDS. With the block least squares of basis.h, per launch against rows
 // fetched by their lanes and Givens rotations: explosion of 302k triangles, M=2,
 // 4 levels 264 -> 163 us; vortex of 75k, M=2, 3 levels 93 -> 69 us; vortex of
-// 19k, M=3 107 -> 98 us; 150k triangles, M=1, global steps 120 -> 69 us; 1,064
+// 4.7k, M=3 63 -> 58 us; 150k triangles, M=1, global steps 120 -> 69 us; 1,064
 // triangles, M=1 13.3 -> 7.5 us. Now bound by FP64 issue in the least squares
 // (10k of 34k cycles of a workgroup) and the latency of the phases before it
 // (index loads, hash table, placing: 17k) at two workgroups per CU.
@@ -471,7 +471,8 @@ __device__ inline double group8_sum(double v) {
 // numbered in another way a round of 32 does not fit, and what is hashed, thrown
 // away and placed for a few lanes costs more than the staging saves: there every
 // lane places its own rows (STAGED = false), the same arithmetic on the same data
-// in the same order. STAGED_NAMES (common.h) has the line between the two.
+// in the same order. STAGED_NAMES (common.h) has the line between the two; the
+// 19k vortex at M=3 is beyond it in curve order too: 107 -> 84 us.
 template <int M>
 struct Stage {
   static constexpr int CAP = M == 1 ? 448 : 640;   // placed elements a round holds (80 bytes each)
@@ -784,7 +785,7 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
 // floor(64/nb) elements per wavefront (an element never straddles two); the
 // spare lanes of a wavefront repeat its first ones, same values to the same
 // places, so that they need no LDS of their own. LDS reads (288 cycles per
-// wavefront and slice at M=2) and the FP64 pipe (40 % busy) share the time at 2
+// wavefront and slice at M=2) and the FP64 pipe (39 % full) share the time at 2
 // workgroups of 4 wavefronts per CU; 3 need 168 registers, which spill, and
 // measured 73 instead of 64 us. Reciprocals by Newton instead of divisions (11
 // instructions, 30 per node) and the spare lanes' LDS given up: 97.5 -> 93.0 us
@@ -1566,8 +1567,8 @@ __global__ void __launch_bounds__(TPB, 2) k_patch(Dev d, const Tables* __restric
 // looks at 64 / nG consecutive edges, so every swept one has its lanes. A patch
 // is a serial chain of nG^2 points behind four dependent loads; on a mesh that
 // leaves the chip short of wavefronts the chain is what counts (9k-triangle
-// explosion, HLL: 18.7 -> 8.0 us per launch; 4.7k vortex, M=2 13.6 -> 8.4; 19k
-// vortex, M=3 20.1 -> 14.2), on a large one the repeated index loads cost more
+// explosion, HLL: 18.7 -> 8.0 us per launch; 4.7k vortex, M=2 13.6 -> 8.0; 19k
+// vortex, M=3 20.1 -> 14 to 15), on a large one the repeated index loads cost more
 // (75k vortex 26.9 us against 22.6 with a lane per edge; 302k explosion 83
 // against 67).
 template <int M, int FLUX>
