@@ -249,6 +249,7 @@ const aw::Inst* rep_inst(const ader_ctx* c) {
 // The device's status, written to pinned memory by a kernel of its own (a copy
 // into pageable memory costs a staging copy more).
 int read_scal(ader_ctx* c, aw::Scal& s) {
+  c->rep_fresh = false;   // until the new one is there
   LCHK(c, aw::launch_report(c->dev, c->rep, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->prof) flush_events(c);
@@ -1036,12 +1037,12 @@ int ader_debug_inject(ader_ctx* c, int32_t what, const void* host, size_t bytes)
     return fail(c, ADER_E_ARG, "memory variables are kept per element edge and cannot be injected");
   Arr a = lookup(c, what);
   if (a.bytes == 0 || bytes != a.bytes) return fail(c, ADER_E_ARG, "size mismatch");
-  c->rep_fresh = false;
   if (what == ADER_DBG_SCAL) {
     aw::Scal s;
     int r = read_scal(c, s);
     if (r) return r;
     std::vector<aw::Inst> in = report_insts(c);
+    c->rep_fresh = false;
     double v[4];
     std::memcpy(v, host, sizeof(v));
     in[0].T = v[0];
@@ -1050,7 +1051,6 @@ int ader_debug_inject(ader_ctx* c, int32_t what, const void* host, size_t bytes)
     s.t_end = v[3];
     if ((r = h2d(c, c->dev.scal, &s, sizeof(s)))) return r;
     if ((r = h2d(c, c->dev.inst, in.data(), sizeof(aw::Inst)))) return r;
-    c->rep_fresh = false;
   } else if (!a.dev) {
     int r = packed_io(c, what, nullptr, host, bytes);
     if (r) return r;
@@ -1067,6 +1067,7 @@ int ader_debug_cycles(ader_ctx* c, int32_t n) {
   if (!c || n < 0) return ADER_E_ARG;
   if (!c->has_state) return fail(c, ADER_E_ORDER, "no state uploaded");
   c->synced = false;
+  c->rep_fresh = false;
   int r = issue_cycles(c, n, c->stream, -1);
   if (r) return r;
   c->cycles += n;
@@ -1080,6 +1081,7 @@ int ader_debug_macro_begin(ader_ctx* c, double t_end, int32_t levels) {
   if (!c->has_state) return fail(c, ADER_E_ORDER, "no state uploaded");
   set_free(c, levels == 0);
   c->synced = false;
+  c->rep_fresh = false;
   LCHK(c, aw::launch_target(c->dev, t_end, c->stream));
   int r = issue_macro_begin(c, levels == 0 ? 0 : 1 << (levels - 1), c->stream);
   if (r) return r;
