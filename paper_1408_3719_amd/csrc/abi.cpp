@@ -827,6 +827,7 @@ int ader_bind_workspace(ader_ctx* c, void* dev_ptr, size_t bytes) {
   if ((reinterpret_cast<uintptr_t>(dev_ptr) & 255) != 0) return fail(c, ADER_E_ARG, "workspace not 256-byte aligned");
   size_t need = carve(c, nullptr);
   if (bytes < need) return fail(c, ADER_E_ARG, "workspace too small");
+  drop_graphs(c);   // they hold the addresses of the workspace bound before
   c->ws = (char*)dev_ptr;
   c->ws_bytes = need;
   carve(c, c->ws);

@@ -118,3 +118,25 @@ def test_a_failed_run_stops_at_the_step_that_failed(batch, before):
     assert a.stats()["macro_steps"] == b.stats()["macro_steps"] > before
     for x, y in zip(_after(a), _after(b)):
         assert np.array_equal(x, y, equal_nan=True)
+
+
+def test_steps_after_another_workspace_is_bound():
+    """The captured steps are those of the workspace that is bound (the one
+    before stays allocated here)."""
+    import ctypes
+
+    import torch
+
+    s, _, Q = _solver(levels=1)
+    s.step_gts(1e9, 5)
+    want = s.download()
+    n = ctypes.c_size_t()
+    assert s.lib.ader_workspace_size(s.ctx, ctypes.byref(n)) == 0
+    other = torch.empty(n.value + 256, dtype=torch.uint8, device=s.device)
+    at = (other.data_ptr() + 255) // 256 * 256
+    assert s.lib.ader_bind_workspace(s.ctx, ctypes.c_void_p(at), n.value) == 0
+    s.upload_state(Q)
+    s.step_gts(1e9, 5)
+    for a, b in zip(s.download(), want):
+        assert np.array_equal(a, b)
+    s.close()
