@@ -55,11 +55,11 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_1408_3719_amd", "csrc", n) for n in 
 TRAFFIC_SWEEP = (0, 4, 8, 16, 32)
 MEASURED_TRAFFIC = {
     "workload": "explosion",
-    "source_sha256": "d534fb55d41b8127e39eaf3b8270ef04926d4e2676a7b50ce1577ba498689c4b",
-    "k_reconstruct": {0: 1478, 4: 1513, 8: 1500, 16: 1488, 32: 1480},
-    "k_predict": {0: 1502, 4: 1504, 8: 1503, 16: 1502, 32: 1502},
-    "k_patch": {0: 1053, 4: 1092, 8: 1063, 16: 1054, 32: 1054},
-    "k_update": {0: 743, 4: 745, 8: 743, 16: 743, 32: 743},
+    "source_sha256": "cfa5c6910e3c31f3c91097ac1069ae7f5f2ffec25a03d9206a3069990cb3bd1a",
+    "k_reconstruct": {0: 1479, 4: 1514, 8: 1500, 16: 1488, 32: 1480},
+    "k_predict": {0: 1503, 4: 1506, 8: 1505, 16: 1504, 32: 1504},
+    "k_patch": {0: 1053, 4: 1092, 8: 1062, 16: 1054, 32: 1053},
+    "k_update": {0: 744, 4: 746, 8: 744, 16: 744, 32: 743},
     "k_node": {w: 1412 for w in TRAFFIC_SWEEP},
     "k_sched": {w: 88 for w in TRAFFIC_SWEEP},
 }

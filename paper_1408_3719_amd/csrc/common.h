@@ -135,7 +135,6 @@ struct Dev {
   // workgroups per CU of the node and patch launches, which sweep every node
   // and edge (0: one grid over all of them; else a persistent grid striding them)
   int sweep_wg_per_cu;
-  int staged;       // reconstruction with the stencil elements of a workgroup placed once, in LDS
   int free_steps;   // 1: free local steps (one macro step of FREE_TICKS to the target)
   Scal* scal;
   Inst* inst;                        // [K]
@@ -171,6 +170,7 @@ struct Dev {
   // replay_delta[m] (clamped to the target time as the computed one)
   const double* replay_delta;
   int replay_delta_n;
+  int staged;   // host: reconstruction with a workgroup's stencil elements placed once, in LDS
   // schedule record (null when off): element i's k-th step at
   // rec_steps[i * rec_cap + k], rec_pos[i] of them; macro step m's tick length
   // at rec_delta[m] (m < rec_delta_cap; one instance)
@@ -337,8 +337,8 @@ constexpr int recon_share(int n, int n_cu) {
 // step with either (us; names: 32 elements unless noted), vortex or explosion,
 // elements numbered along a curve, in rows of the mesh, in runs of n from the
 // curve in random order, at random:
-//   M=1 150k, global: curve (146) 215 staged, 276 direct; runs of 8 (302) 256, 291;
-//     rows (319) 305, 284; random (953) 589, 369
+//   M=1 150k, global: curve (146) 215 staged, 257 direct; runs of 8 (302) 256, 264;
+//     rows (319) 295, 260; random (953) 592, 320
 //   M=2 80k, 3 levels: curve (222) 763, 839; runs of 32 (251) 818, 844; of 16 (397)
 //     848, 849; rows (513) 908, 854; random (2,065) 2,137, 1,044
 //   M=2 400k, 4 levels: curve (226) 2,385, 2,685; runs of 16 (343) 2,978, 2,898;

@@ -472,7 +472,9 @@ __device__ inline double group8_sum(double v) {
 // away and placed for a few lanes costs more than the staging saves: there every
 // lane places its own rows (STAGED = false), the same arithmetic on the same data
 // in the same order. STAGED_NAMES (common.h) has the line between the two; the
-// 19k vortex at M=3 is beyond it in curve order too: 107 -> 84 us.
+// 19k vortex at M=3 is beyond it in curve order too: 107 -> 84 us. Three
+// workgroups per CU at M=1 pay for the staged form only: the other spills 55
+// registers for them (150k triangles in random order 187 -> 140 us with two).
 template <int M>
 struct Stage {
   static constexpr int CAP = M == 1 ? 448 : 640;   // placed elements a round holds (80 bytes each)
@@ -486,7 +488,7 @@ struct Stage {
 constexpr unsigned long long NO_KEY = ~0ull;
 
 template <int M, bool STAGED>
-__global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruct(Dev d, const Tables* __restrict__ tb, Params P,
+__global__ void __launch_bounds__(TPB, M == 1 && STAGED ? 3 : M <= 2 ? 2 : 1) k_reconstruct(Dev d, const Tables* __restrict__ tb, Params P,
                                                      int list, int set_level) {
   using S = Sz<M>;
   using G = Stage<M>;
@@ -508,6 +510,11 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
     const int first = wg * per, last = min(nitems, first + per);
     int round = per;
     for (int base = first; base < last;) {
+      if constexpr (STAGED) {
+        for (int t = tid; t < TAB; t += TPB) key[t] = NO_KEY;
+        if (tid == 0) count = 0;
+        __syncthreads();
+      }
       const int idx = base + grp;
       const bool mine = grp < round && idx < last;
       int i = 0, nt = 0;
@@ -529,9 +536,6 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
       }
       valid = sl < NSTEN && at[0] >= 0;
       if constexpr (STAGED) {
-        for (int t = tid; t < TAB; t += TPB) key[t] = NO_KEY;
-        if (tid == 0) count = 0;
-        __syncthreads();
         const unsigned long long hi = (unsigned long long)(unsigned)nt << 32;
         // The probes of all rows go out together (one LDS round trip for all of
         // them), again and again until every row has found or made its entry;
@@ -595,12 +599,12 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
           o[3] = make_double2(Q[0], Q[1]);
           o[4] = make_double2(Q[2], Q[3]);
         }
+        if (!ok) set_err(d, ERR_PRED);
 #pragma unroll
         for (int c = 0; c < NR; ++c) at[c] = slot_of[pos[c]];
         __syncthreads();
       }
       if (mine) {
-        const double delta = elem_delta(d, i);
         // vertices and average of a stencil element: at a slot, or element j placed now
         auto stencil_element = [&](int j, double X[6], double Q[4]) {
           if constexpr (STAGED) {
@@ -617,7 +621,7 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
             Q[2] = q1.x;
             Q[3] = q1.y;
           } else {
-            ok &= project<M>(d, tb, j, nt, delta, X, Q);
+            ok &= project<M>(d, tb, j, nt, elem_delta(d, i), X, Q);
           }
         };
         const double* ri = rec<M>(d, i);
@@ -766,15 +770,17 @@ __global__ void __launch_bounds__(TPB, M == 1 ? 3 : M == 2 ? 2 : 1) k_reconstruc
               d.ts[i].step = 0;
             } else {
               int over;
-              const int own = level_step(dt, delta, N, nt, d.free_steps, &over);
-              d.ts[i].step = take_step(d, i, own, nt, N, dt, delta, &over);
+              const int own = level_step(dt, elem_delta(d, i), N, nt, d.free_steps, &over);
+              d.ts[i].step = take_step(d, i, own, nt, N, dt, elem_delta(d, i), &over);
               if (over) atomicAdd(&d.scal->overshoots, 1ull);
             }
           }
         }
       }
-      if (!ok) set_err(d, ERR_PRED);
-      if constexpr (STAGED) __syncthreads();   // the next round clears the table
+      if constexpr (STAGED)
+        __syncthreads();   // the next round clears the table
+      else if (!ok)
+        set_err(d, ERR_PRED);
       base += round;
     }
   }
